@@ -32,7 +32,7 @@ ALGO_FLOPS_PER_SLOT = 32
 # slot row), used when it was taken on the current kernel source
 COUNTERS = os.path.join(ROOT, "profiles", "counters_step_cube100_f64.txt")
 STEP_SOURCES = [os.path.join(ROOT, "paper_2105_04150_amd", "csrc", f)
-                for f in ("pdmi_step.h", "pdmi_device.h", "pdmi_internal.h")]
+                for f in ("pdmi_step.h", "pdmi_tile.h", "pdmi_device.h", "pdmi_internal.h")]
 
 
 def kernel_hash() -> str:

@@ -63,8 +63,8 @@ extern "C" {
 
 #define PD_MAP_SLICED 0     /* slots in 64-wide rows, G lanes per node, neighbours gathered from
                                global memory through the L1 cache */
-#define PD_MAP_STAGED 1     /* one lane per node; each wavefront stages runs of consecutive
-                               neighbour records in LDS and reads them from there */
+#define PD_MAP_STAGED 1     /* one lane per node; a workgroup stages the records that its tile of
+                               64 to 256 nodes reaches in LDS and reads them from there */
 
 #define PD_SCHED_CONST 0    /* g(t) = 1 */
 #define PD_SCHED_LINEAR 1   /* g(t) = t */
@@ -99,7 +99,7 @@ typedef struct pd_info {
     int32_t mapping;        /* PD_MAP_SLICED / PD_MAP_STAGED */
     int32_t order;          /* device node order in use: PD_ORDER_NATURAL / PD_ORDER_MORTON */
     double model_bytes_per_step; /* algorithmic HBM bytes of one step (see the design notes) */
-    int32_t waves_per_slice; /* staged mapping: wavefronts sharing one 64-node slice (1 otherwise) */
+    int32_t waves_per_slice; /* staged mapping: the lanes of pd_set_mapping (1 otherwise) */
     int32_t reserved_;
 } pd_info;
 
@@ -433,7 +433,7 @@ int pd_load_state(pd_ctx *ctx, int32_t inst, const pd_state *in);
  *
  * pd_adj_forward advances the problem by nsteps >= 1 steps exactly as pd_step does,
  * recording the pass in which each slot breaks and a device checkpoint of (u, v)
- * every ckpt_every >= 1 steps ((nn + 89) * 48 + nn * 24 bytes each, nn = padded node
+ * every ckpt_every >= 1 steps ((nn + 1) * 48 + nn * 24 bytes each, nn = padded node
  * count; with ckpt_every = 1 every level is kept, v is not, and the reverse pass
  * recomputes nothing).  Any later change to the problem or state (pd_step included)
  * discards the recording.  Asynchronous like pd_step.  *recording (may be NULL)
@@ -465,9 +465,9 @@ int pd_get_break_steps(pd_ctx *ctx, int32_t inst, int32_t *out);
 
 /* Work mapping of the step kernel: PD_MAP_SLICED with `lanes` work-items cooperating on
  * one node's bonds (1, 4, 16 or 64; 0 = library default), or PD_MAP_STAGED with `lanes`
- * wavefronts sharing each 64-node slice (1, 2 or 4; 0 = 1; more than one fills the chip
- * on problems with fewer slices than SIMDs).  Rebuilds the device layout when the
- * mapping changes; the state (u, v, a, broken bonds, step) is kept. */
+ * 1, 2 or 4 (0 = 1; kept and reported as given: the library itself chooses the
+ * wavefronts per 64-node slice, 2 to 8, from the size of the problem).  Rebuilds the device
+ * layout when the mapping changes; the state (u, v, a, broken bonds, step) is kept. */
 int pd_set_mapping(pd_ctx *ctx, int mapping, int lanes);
 
 /* Shorthand for pd_set_mapping(ctx, PD_MAP_SLICED, lanes). */

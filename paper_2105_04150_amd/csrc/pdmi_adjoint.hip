@@ -17,7 +17,7 @@
 // needs no reverse-slot index.  1/L - 1/r = (1/L)(1 - (1+q)^(-1/2)) uses
 // q = |y|^2/|xi|^2 - 1 with the numerator formed without cancellation, eta.(xi + y), and
 // 1/r is 1/L less that.
-#include "pdmi_device.h"
+#include "pdmi_tile.h"
 
 namespace pdmi {
 namespace {
@@ -38,7 +38,7 @@ __device__ __forceinline__ double adj_slot(bool active, const double2 p0, const 
     const double L2 = __builtin_fma(xi2, xi2, __builtin_fma(xi1, xi1, xi0 * xi0));
     const double iL = rsq64<1>(L2);
     const double q = active ? tq * (iL * iL) : 0.0;
-    const double sr = iL * one_minus_rsqrt1p(q);  // s/r = 1/L - 1/r
+    const double sr = iL * one_minus_rsqrt1p(q, series_coef_sregs());  // s/r = 1/L - 1/r
     const double ir = iL - sr;                    // 1/r, no cancellation: sr is about |s| of iL
     const double ir3 = ir * ir * ir;
     const double w0 = Vi * nj[0] - Vj * ni[0], w1 = Vi * nj[1] - Vj * ni[1], w2 = Vi * nj[2] - Vj * ni[2];
@@ -151,189 +151,101 @@ __global__ __launch_bounds__(kBlock) void adjoint_sliced(AdjArgs A)
     adj_node(A, P, node, ni, J, h);
 }
 
-// Orders a wavefront's own LDS writes before its later LDS reads (no workgroup barrier).
-__device__ __forceinline__ void adj_wave_sync()
+// Staged layout: one workgroup a tile (pdmi_tile.h), one lane a node, 2 to 8 wavefronts
+// a slice.  The tile's records (x, u^k), adjoint velocities and per-node weights are copied into LDS
+// once; the per-slot streams (entries, break steps, stiffness, gradient: 28 to 36 bytes a
+// slot, the pass's bound beside latency) come a row pair ahead, 16 bytes a lane and load.
+// Padding entries point at the sentinel (far record, zero adjoint velocity and weights).
+// Partial sums of J meet in LDS in a fixed order.
+template <int KM, bool VOLN>
+__global__ __launch_bounds__(kTileWaves * kWave, 4) void adjoint_lds(AdjArgs A, const TileRec* __restrict__ tiles,
+                                                                     const int2* __restrict__ phases,
+                                                                     const int2* __restrict__ segs,
+                                                                     const int32_t* __restrict__ list)
 {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Staged layout: a workgroup of S wavefronts per 64-node slice, one lane per node;
-// wavefront w takes the slice's pieces w, w + S, ...  For each piece the wavefront
-// stages the range's records (x, u^k), adjoint velocities and per-node weights in its
-// own LDS area one piece ahead (the record and adjoint-velocity buffers end with spare
-// entries, so the fixed windows need no clamping); per-slot break steps, stiffness and
-// the gradient stream by row.  Padding entries point at an LDS sentinel (far record,
-// zero adjoint velocity and weights).  Partial sums of J meet in LDS in a fixed order.
-// The layout tables come as restrict parameters: their loads are then scalar, and a
-// piece's descriptor does not wait behind the vector loads in flight.
-template <int KM, bool VOLN, int S>
-__global__ __launch_bounds__(kWave * S) void adjoint_lds(AdjArgs A, const int2* __restrict__ pieces,
-                                                         const int32_t* __restrict__ slice_piece,
-                                                         const int64_t* __restrict__ slice_ptr,
-                                                         const int32_t* __restrict__ slice_order)
-{
-    constexpr bool KNODE = KM == kKNode;
-    constexpr int kW = (kEntPad / 48 + 2) / 2 * 2;  // staged weights per array (sentinel at kEntPad / 48)
-    constexpr int kRecChunks = kStageChunks + 3;     // records, then the sentinel record
-    constexpr int kNuChunks = kStageChunks / 2 + 2;  // 2 * kStageChunks / 3 adjoint-velocity triples + sentinel
-    constexpr int kEntChunks = kWave;                // one 8-row entry block
-    constexpr int kWChunks = ((VOLN ? kW : 0) + (KNODE ? kW : 0)) / 2;
-    constexpr int kLds = kRecChunks + kNuChunks + kEntChunks + kWChunks;
-    static_assert(kStageChunks == 4 * kWave, "four record loads per piece");
-    __shared__ double2 lds[S * kLds];
-    __shared__ double red[S > 1 ? (S - 1) * 3 * kWave : 1];
-    const int wv = S > 1 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave) : 0;
-    const int lane = threadIdx.x & (kWave - 1);
-    double2* const lrec = lds + wv * kLds;
-    const char* const lrecb = reinterpret_cast<const char*>(lrec);
-    double* const lnu = reinterpret_cast<double*>(lrec + kRecChunks);
-    uint16_t* const lent = reinterpret_cast<uint16_t*>(lrec + kRecChunks + kNuChunks);
-    double* const lvol = reinterpret_cast<double*>(lrec + kRecChunks + kNuChunks + kEntChunks);
-    double* const lna = lvol + (VOLN ? kW : 0);
-
-    int64_t slice = wave_uniform(xcd_remap(blockIdx.x, gridDim.x));
-    if (slice >= A.nslices) return;
-    // the step kernels' processing order (each XCD's share longest first): the grid
-    // ends on short slices when it does not fit the chip in one round
-    if (slice_order) slice = __builtin_amdgcn_readfirstlane(slice_order[slice]);
-    const InstParams P = A.params[A.slice_inst[slice]];
-    const int64_t node = slice * kWave + lane;
+    constexpr bool KNODE = KM == kKNode, STIFF = KM == kKSlot;
+    extern __shared__ double2 lds[];
+    __builtin_amdgcn_s_setprio(3);  // a tile's staging before another's rows
+    const TileRec T = tiles[wave_uniform(xcd_remap(blockIdx.x, gridDim.x))];
+    const TileLane tl(T);
+    const int lane = tl.lane;
+    double2* const lrec = lds;
+    const int R = A.stage_max + 1;
+    double* const lnu = reinterpret_cast<double*>(lrec + 3 * R);
+    double* const lvol = lnu + 3 * R;
+    double* const lna = lvol + (VOLN ? R : 0);
+    if (T.nphases > 0) stage_records(A.rec, list + T.list, T.n, tl.wv, lane, lrec);
+    const InstParams& P = A.params[T.inst];
+    const int64_t node = tl.node(T);
     const double2* __restrict__ rec = reinterpret_cast<const double2*>(A.rec);
     const double2 o0 = rec[3 * node], o1 = rec[3 * node + 1], o2 = rec[3 * node + 2];
     const double ni[3] = {A.nu_in[3 * node], A.nu_in[3 * node + 1], A.nu_in[3 * node + 2]};
     const double Vi = VOLN ? A.vol[node] : P.volume;
     const double ai = KNODE ? A.na[node] : 0.0;
     const double h = A.dt / P.rho;
-    const double2* __restrict__ ent2 = reinterpret_cast<const double2*>(A.ent);
+    const uint32_t* __restrict__ ent = reinterpret_cast<const uint32_t*>(A.ent) + lane;
+    const int2* __restrict__ bstep = reinterpret_cast<const int2*>(A.bstep) + lane;
+    const double2* __restrict__ kslot = reinterpret_cast<const double2*>(A.kslot) + lane;
+    double2* __restrict__ grad = reinterpret_cast<double2*>(A.grad) + lane;
 
     // sentinels: record far from every node; zero adjoint velocity and weights
-    if (lane < 3) lrec[kStageChunks + lane] = lane == 0 ? double2{1e10, 1e10} : lane == 1 ? double2{1e10, 0.0} : double2{0.0, 0.0};
-    if (lane < 4) lnu[kStageChunks + lane] = 0.0;
-    if (VOLN && lane == 0) lvol[kEntPad / 48] = 0.0;
-    if (KNODE && lane == 0) lna[kEntPad / 48] = 0.0;
+    if (threadIdx.x < 3) {
+        lrec[threadIdx.x] = threadIdx.x == 0 ? double2{1e10, 1e10} : threadIdx.x == 1 ? double2{1e10, 0.0} : double2{0.0, 0.0};
+        lnu[threadIdx.x] = 0.0;
+    }
+    if (VOLN && threadIdx.x == 0) lvol[0] = 0.0;
+    if (KNODE && threadIdx.x == 0) lna[0] = 0.0;
 
-    const int p0 = __builtin_amdgcn_readfirstlane(slice_piece[slice]);
-    const int p1 = __builtin_amdgcn_readfirstlane(slice_piece[slice + 1]);
-    auto rows_of = [&](int p) { return (pieces[__builtin_amdgcn_readfirstlane(p)].y >> 8) & 0xff; };
-    int64_t ent = wave_uniform(slice_ptr[slice]);
-    const int pa = p0 + wv;
-    for (int q = p0; q < pa && q < p1; ++q) ent += static_cast<int64_t>(rows_of(q)) * kWave;
-
-    double2 r0, r1, r2, r3, e0;
-    double n0, n1, n2, n3, vs0 = 0.0, vs1 = 0.0, as0 = 0.0, as1 = 0.0;
-    int vlen = 0;
-    auto issue = [&](int p, int64_t e) {
-        const int2 m = pieces[__builtin_amdgcn_readfirstlane(p)];
-        const double2* rs = rec + 3 * static_cast<int64_t>(m.x) + lane;
-        r0 = rs[0];
-        r1 = rs[kWave];
-        r2 = rs[2 * kWave];
-        r3 = rs[3 * kWave];
-        const double* ns = A.nu_in + 3 * static_cast<int64_t>(m.x) + lane;
-        n0 = ns[0];
-        n1 = ns[kWave];
-        n2 = ns[2 * kWave];
-        n3 = ns[3 * kWave];
-        e0 = ent2[e / 8 + lane];
-        if (VOLN || KNODE) {
-            const int len = m.y & 0xff;
-            vlen = len;
-            if (VOLN) {
-                vs0 = A.vol[m.x + min(lane, len - 1)];
-                vs1 = A.vol[m.x + min(lane + kWave, len - 1)];
-            }
-            if (KNODE) {
-                as0 = A.na[m.x + min(lane, len - 1)];
-                as1 = A.na[m.x + min(lane + kWave, len - 1)];
-            }
-        }
-    };
-    auto commit = [&]() {
-        lrec[lane] = r0;
-        lrec[lane + kWave] = r1;
-        lrec[lane + 2 * kWave] = r2;
-        lrec[lane + 3 * kWave] = r3;
-        lnu[lane] = n0;
-        lnu[lane + kWave] = n1;
-        lnu[lane + 2 * kWave] = n2;
-        lnu[lane + 3 * kWave] = n3;
-        reinterpret_cast<double2*>(lent)[lane] = e0;
-        if (VOLN) {
-            if (lane < vlen) lvol[lane] = vs0;
-            if (lane + kWave < vlen) lvol[lane + kWave] = vs1;
-        }
-        if (KNODE) {
-            if (lane < vlen) lna[lane] = as0;
-            if (lane + kWave < vlen) lna[lane + kWave] = as1;
-        }
-    };
-    // one slot of row t of the current piece; its break step, gradient and stiffness were
-    // loaded with the rest of the piece's rows (bs, gr, kr)
     double J[3] = {0.0, 0.0, 0.0};
-    int32_t bs[kPieceRows];
-    double gr[kPieceRows], kr[kPieceRows];
-    auto slot = [&](int t, int64_t ds, uint16_t e) {
-        const uint32_t off = e & kEntOff;  // byte offset of the record; 3 * index = off / 16 for nu
-        const double2 q0 = *reinterpret_cast<const double2*>(lrecb + off);
-        const double2 q1 = *reinterpret_cast<const double2*>(lrecb + off + 16);
-        const double2 q2 = *reinterpret_cast<const double2*>(lrecb + off + 32);
-        const double* nu = lnu + off / 16;
-        const double nj[3] = {nu[0], nu[1], nu[2]};
-        const uint32_t widx = (off * 0xAAABu) >> 21;  // off / 48
-        const bool active = A.k < static_cast<int64_t>(bs[t]);
-        const double kb = KM == kKSlot ? kr[t] : KNODE ? ai * lna[widx] : P.c;
-        const double Vj = VOLN ? lvol[widx] : P.volume;
-        const double d = adj_slot(active, q0, q1, q2, o0.x, o0.y, o1.x, o1.y, o2.x, o2.y, nj, ni, Vi, Vj, kb, h, J);
-        if (active) A.grad[ds] = gr[t] + d;
+    const int32_t k = static_cast<int32_t>(A.k);
+    struct Streams {
+        uint32_t e;
+        int2 bs;
+        double2 kr, gr;
     };
-
-    if (pa < p1) {
-        issue(pa, ent);
-        for (int p = pa; p < p1; p += S) {
-            const int T = rows_of(p);
-            int64_t ent_next = ent + static_cast<int64_t>(T) * kWave;
-            for (int q = p + 1; q < p + S && q < p1; ++q) ent_next += static_cast<int64_t>(rows_of(q)) * kWave;
-            adj_wave_sync();  // the previous piece is no longer read
-            commit();
-            // the piece's per-slot streams, all eight rows of its block at once (rows past T
-            // belong to the next piece or the spare rows and are not used), issued before
-            // the next piece's prefetch: vector-memory loads complete in order, so the rows
-            // wait for these only and the prefetch stays in flight behind them
-#pragma unroll
-            for (int t = 0; t < kPieceRows; ++t) {
-                const int64_t ds = ent + t * kWave + lane;
-                bs[t] = A.bstep[ds];
-                gr[t] = A.grad[ds];
-                if (KM == kKSlot) kr[t] = A.kslot[ds];
-            }
-            if (p + S < p1) issue(p + S, ent_next);
-            adj_wave_sync();  // the piece's LDS copy is complete
-#pragma unroll
-            for (int t = 0; t < kPieceRows; ++t) {
-                if (t >= T) break;
-                slot(t, ent + t * kWave + lane, lent[t * kWave + lane]);
-            }
-            ent = ent_next;
+    auto streams = [&](int t) {
+        const int64_t at = static_cast<int64_t>(t) * kWave;
+        return Streams{ent[at], bstep[at], STIFF ? kslot[at] : double2{0.0, 0.0}, grad[at]};
+    };
+    auto slot = [&](const NodeRec& r, uint32_t idx, bool active, double kr) {
+        const double nj[3] = {lnu[3 * idx], lnu[3 * idx + 1], lnu[3 * idx + 2]};
+        const double kb = STIFF ? kr : KNODE ? ai * lna[idx] : P.c;
+        const double Vj = VOLN ? lvol[idx] : P.volume;
+        return adj_slot(active, r.p0, r.p1, r.p2, o0.x, o0.y, o1.x, o1.y, o2.x, o2.y, nj, ni, Vi, Vj, kb, h, J);
+    };
+    auto stage_weights = [&](const int32_t* l, int n) {
+        stage_triples(A.nu_in, l, n, tl.wv, lane, lnu);
+        if (VOLN) stage_doubles(A.vol, l, n, tl.wv, lane, lvol);
+        if (KNODE) stage_doubles(A.na, l, n, tl.wv, lane, lna);
+    };
+    if (T.nphases > 0) stage_weights(list + T.list, T.n);
+#pragma unroll 1
+    for (int ph = 0; ph < T.nphases; ++ph) {
+        if (ph > 0) {
+            const int2 pd = phases[T.phase + ph];
+            __syncthreads();  // the records before are no longer read
+            stage_records(A.rec, list + pd.x, pd.y, tl.wv, lane, lrec);
+            stage_weights(list + pd.x, pd.y);
         }
+        const int2 pr = tl.pairs(T, segs, ph);
+        Streams a = streams(pr.x);  // spare rows follow the last slice's
+        tile_staged();
+        __builtin_amdgcn_s_setprio(0);
+#pragma unroll 1
+        for (int t = pr.x; t < pr.y; ++t) {
+            const Streams b = streams(t + 1);
+            const uint32_t ia = a.e & kEntIdx, ib = (a.e >> 16) & kEntIdx;
+            const double da = slot(staged_record(lrec, ia), ia, k < a.bs.x, a.kr.x);
+            __builtin_amdgcn_sched_barrier(0);  // the two interleaved do not fit the registers
+            const double db = slot(staged_record(lrec, ib), ib, k < a.bs.y, a.kr.y);
+            // inactive slots keep their gradient (the increment is zero)
+            grad[static_cast<int64_t>(t) * kWave] = double2{a.gr.x + da, a.gr.y + db};
+            a = b;
+        }
+        __builtin_amdgcn_s_setprio(3);
     }
-    if (S > 1) {
-        if (wv > 0) {
-            double* r = red + (wv - 1) * 3 * kWave + lane;
-            r[0] = J[0];
-            r[kWave] = J[1];
-            r[2 * kWave] = J[2];
-        }
-        __syncthreads();  // every wavefront of the workgroup reaches this once
-        if (wv > 0) return;
-#pragma unroll
-        for (int w = 1; w < S; ++w) {
-            const double* r = red + (w - 1) * 3 * kWave + lane;
-            J[0] += r[0];
-            J[1] += r[kWave];
-            J[2] += r[2 * kWave];
-        }
-    }
+    tile_reduce(tl, reinterpret_cast<double*>(lds), J);
+    if (tl.sub > 0 || !tl.has) return;
     adj_node(A, P, node, ni, J, h);
 }
 
@@ -409,18 +321,21 @@ void adj_launch_sliced(const AdjArgs& a, hipStream_t s)
 }
 
 template <int KM, bool VOLN>
-hipError_t adj_launch_kv(const AdjArgs& a, const int32_t* order, bool staged, int lanes, hipStream_t s)
+hipError_t adj_launch_staged(const AdjArgs& a, hipStream_t s)
 {
-    const dim3 grid(static_cast<unsigned>(a.nslices));
-    if (staged) {
-        switch (lanes) {  // wavefronts per slice
-        case 1: hipLaunchKernelGGL((adjoint_lds<KM, VOLN, 1>), grid, dim3(kWave), 0, s, a, a.pieces, a.slice_piece, a.slice_ptr, order); break;
-        case 2: hipLaunchKernelGGL((adjoint_lds<KM, VOLN, 2>), grid, dim3(2 * kWave), 0, s, a, a.pieces, a.slice_piece, a.slice_ptr, order); break;
-        case 4: hipLaunchKernelGGL((adjoint_lds<KM, VOLN, 4>), grid, dim3(4 * kWave), 0, s, a, a.pieces, a.slice_piece, a.slice_ptr, order); break;
-        default: return hipErrorInvalidValue;
-        }
-        return hipGetLastError();
-    }
+    auto* kernel = &adjoint_lds<KM, VOLN>;
+    const size_t bytes = tile_lds(a.stage_max, 48 + 24 + (VOLN ? 8 : 0) + (KM == kKNode ? 8 : 0));
+    const hipError_t e = tile_room(reinterpret_cast<const void*>(kernel), bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.ntiles)), dim3(kTileWaves * kWave), bytes, s, a, a.tiles,
+                       a.phases, a.segs, a.list);
+    return hipGetLastError();
+}
+
+template <int KM, bool VOLN>
+hipError_t adj_launch_kv(const AdjArgs& a, bool staged, int lanes, hipStream_t s)
+{
+    if (staged) return adj_launch_staged<KM, VOLN>(a, s);
     switch (lanes) {
     case 1: adj_launch_sliced<1, KM, VOLN>(a, s); break;
     case 4: adj_launch_sliced<4, KM, VOLN>(a, s); break;
@@ -432,28 +347,21 @@ hipError_t adj_launch_kv(const AdjArgs& a, const int32_t* order, bool staged, in
 }
 
 template <int KM>
-hipError_t adj_launch_k(const AdjArgs& a, const int32_t* order, bool staged, int lanes, hipStream_t s)
+hipError_t adj_launch_k(const AdjArgs& a, bool staged, int lanes, hipStream_t s)
 {
-    return a.vol ? adj_launch_kv<KM, true>(a, order, staged, lanes, s)
-                 : adj_launch_kv<KM, false>(a, order, staged, lanes, s);
+    return a.vol ? adj_launch_kv<KM, true>(a, staged, lanes, s) : adj_launch_kv<KM, false>(a, staged, lanes, s);
 }
 
 unsigned blocks_for(int64_t n) { return static_cast<unsigned>((n + kBlock - 1) / kBlock); }
 
 }  // namespace
 
-hipError_t launch_adjoint_ordered(const AdjArgs& a, const int32_t* slice_order, bool staged, int lanes,
-                                  hipStream_t s)
-{
-    if (a.nslices <= 0) return hipSuccess;
-    if (a.kslot) return adj_launch_k<kKSlot>(a, slice_order, staged, lanes, s);
-    if (a.na) return adj_launch_k<kKNode>(a, slice_order, staged, lanes, s);
-    return adj_launch_k<kKUniform>(a, slice_order, staged, lanes, s);
-}
-
 hipError_t launch_adjoint(const AdjArgs& a, bool staged, int lanes, hipStream_t s)
 {
-    return launch_adjoint_ordered(a, nullptr, staged, lanes, s);
+    if (a.nslices <= 0) return hipSuccess;
+    if (a.kslot) return adj_launch_k<kKSlot>(a, staged, lanes, s);
+    if (a.na) return adj_launch_k<kKNode>(a, staged, lanes, s);
+    return adj_launch_k<kKUniform>(a, staged, lanes, s);
 }
 
 hipError_t launch_bstep_init(int32_t* bstep, const int32_t* col, const uint16_t* ent, int64_t ns, hipStream_t s)

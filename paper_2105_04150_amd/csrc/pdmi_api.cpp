@@ -150,6 +150,7 @@ int pd_set_material(pd_ctx* ctx, int32_t inst, const pd_material* m)
         if (ctx->has_stiff || any_corr) upload_stiffness(ctx, any_corr ? -1 : inst);
         upload_node_weights(ctx);
         if (I.osb) upload_osb(ctx);  // the weighted volumes scale with the node volume
+        fit_stage(ctx);
         ctx->a_valid = false;
         ctx->vv_ahead = false;
         ctx->drop_graphs();
@@ -175,6 +176,7 @@ int pd_set_bond_stiffness(pd_ctx* ctx, int32_t inst, const double* k)
         I.knode.clear();
         upload_stiffness(ctx, mode_change ? -1 : inst);
         upload_node_weights(ctx);
+        fit_stage(ctx);
         ctx->a_valid = false;
         ctx->vv_ahead = false;
         ctx->drop_graphs();
@@ -198,6 +200,7 @@ int pd_set_node_stiffness(pd_ctx* ctx, int32_t inst, const double* k_node)
         I.k_sym = true;  // sqrt(k_i k_j) is the same on both slots of a bond
         upload_stiffness(ctx);
         upload_node_weights(ctx);
+        fit_stage(ctx);
         ctx->a_valid = false;
         ctx->vv_ahead = false;
         ctx->drop_graphs();
@@ -329,6 +332,7 @@ int pd_set_damage_law(pd_ctx* ctx, int32_t inst, int32_t cls, int32_t nb, const 
         else
             I.laws[cls] = L;
         reset_laws(ctx);
+        fit_stage(ctx);
     });
 }
 
@@ -383,6 +387,7 @@ int pd_set_corrections(pd_ctx* ctx, int32_t inst, const pd_corrections* corr)
         I.corr = corr ? *corr : pd_corrections{};
         upload_stiffness(ctx);
         upload_node_weights(ctx);
+        fit_stage(ctx);
         ctx->drop_graphs();
     });
 }

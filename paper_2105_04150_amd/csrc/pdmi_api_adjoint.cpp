@@ -24,6 +24,8 @@ int pd_adj_forward(pd_ctx* ctx, int64_t nsteps, int32_t ckpt_every, int64_t* rec
         set_device(ctx);
         Inst& I = ctx->inst[0];
         check_symmetric(I);
+        ctx->adjoint = true;
+        fit_stage(ctx);
         init_break_steps(ctx, I);
         const int64_t nn = ctx->nn;
         const size_t Rb = rec_bytes(nn), Vb = static_cast<size_t>(3 * nn) * sizeof(double);
@@ -101,10 +103,9 @@ int pd_adj_backward(pd_ctx* ctx, int64_t recording, int64_t m, const int64_t* se
         set_device(ctx);
         hipStream_t st = ctx->stream;
         const int64_t nn = ctx->nn, ns = ctx->ns, S = ctx->tape_every, T = ctx->tape_nsteps, step0 = ctx->tape_step0;
-        // adjoint velocities: nn + 1 triples (the last one, the sentinel's, zero) and spare zero
-        // entries for the staged kernel's fixed-size range windows
+        // adjoint velocities: nn + 1 triples (the last one, the sentinel's, zero)
         const size_t Rb = rec_bytes(nn), Vb = static_cast<size_t>(3 * nn) * sizeof(double),
-                     Nb = (static_cast<size_t>(3 * (nn + 1)) + kStageChunks) * sizeof(double);
+                     Nb = static_cast<size_t>(3 * (nn + 1)) * sizeof(double);
         const int64_t Lmax = std::min(S, T);
         const size_t stride = Rb + (S > 1 ? Vb : 0);
         DevBuf traj, vwork, nu[2], lam, grad, gacc, base, sum, dsn, ddl;
@@ -140,8 +141,12 @@ int pd_adj_backward(pd_ctx* ctx, int64_t recording, int64_t m, const int64_t* se
         a.bstep = ctx->bstep.as<int32_t>();
         a.col = ctx->col.as<int32_t>();
         a.ent = ctx->ent.as<uint16_t>();
-        a.pieces = ctx->pieces.as<int2>();
-        a.slice_piece = ctx->slice_piece.as<int32_t>();
+        a.tiles = ctx->tiles.as<TileRec>();
+        a.phases = ctx->phases.as<int2>();
+        a.segs = ctx->segs.as<int2>();
+        a.list = ctx->list.as<int32_t>();
+        a.ntiles = ctx->ntiles;
+        a.stage_max = static_cast<int32_t>(ctx->stage_max);
         a.kslot = ctx->has_stiff ? ctx->kslot.as<double>() : nullptr;
         a.vol = ctx->has_vol ? ctx->vol.as<double>() : nullptr;
         a.na = ctx->has_knode ? ctx->na.as<double>() : nullptr;
@@ -187,10 +192,7 @@ int pd_adj_backward(pd_ctx* ctx, int64_t recording, int64_t m, const int64_t* se
                 a.nu_in = nu[nin].as<double>();
                 a.nu_out = nu[1 - nin].as<double>();
                 a.k = s0 + s;
-                // staged: the step kernels' slice order (each XCD's share longest first)
-                hip_check(staged ? launch_adjoint_ordered(a, ctx->slice_order.as<int32_t>(), true, ctx->lanes, st)
-                                 : launch_adjoint(a, false, ctx->lanes, st),
-                          "adjoint launch");
+                hip_check(launch_adjoint(a, staged, ctx->lanes, st), "adjoint launch");
                 nin ^= 1;
             }
         }

@@ -122,6 +122,7 @@ int pd_set_model(pd_ctx* ctx, int32_t inst, int model, double K, double G)
         I.osb_G = I.osb ? G : 0.0;
         upload_params(ctx);
         upload_osb(ctx);
+        fit_stage(ctx);
         ctx->a_valid = false;
         ctx->vv_ahead = false;
         ctx->drop_graphs();
@@ -139,14 +140,14 @@ int pd_get_dilation(pd_ctx* ctx, int32_t inst, double* out)
         osb_checks(ctx);
         set_device(ctx);
         // the dilation pass at the current level, breaking nothing
-        hip_check(launch_osb_dilation(step_args(ctx, ctx->cur, 1 - ctx->cur, 0), false, fp32(ctx), ctx->lanes,
+        hip_check(launch_osb_dilation(step_args(ctx, ctx->cur, 1 - ctx->cur, 0), false, fp32(ctx),
                                       ctx->stream),
                   "dilation launch");
         std::vector<double> h(static_cast<size_t>(2 * I.n_pad));
         download(h.data(), ctx->osb, h.size() * 8, I.node_off * 16, ctx->stream);
         sync(ctx);
         for (int64_t l = 0; l < I.n_pad; ++l)
-            if (I.perm[l] >= 0) out[I.perm[l]] = h[2 * l + 1] > 0.0 ? h[2 * l] / h[2 * l + 1] : 0.0;
+            if (I.perm[l] >= 0) out[I.perm[l]] = h[2 * l];
     });
 }
 
@@ -426,10 +427,9 @@ int pd_set_mapping(pd_ctx* ctx, int mapping, int lanes)
         }
         if (lanes == ctx->lanes && mapping == ctx->mapping) return;
         set_device(ctx);
-        if (mapping == ctx->mapping && mapping == PD_MAP_STAGED) {  // same layout, other launch shape
+        if (mapping == ctx->mapping && mapping == PD_MAP_STAGED) {  // other tiles; break steps are kept
             ctx->lanes = lanes;
-            ctx->drop_graphs();
-            ctx->tape_valid = false;  // a recompute would sum partial forces in another order
+            relayout(ctx);
             return;
         }
         HostState S = snapshot(ctx);

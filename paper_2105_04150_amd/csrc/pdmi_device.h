@@ -81,6 +81,21 @@ __device__ __forceinline__ SeriesCoef series_coef_regs()
     return k;
 }
 
+// The same for a rare branch: formed inside it, so that the surrounding loop keeps no registers for them.
+__device__ __forceinline__ SeriesCoef series_coef_sregs()
+{
+    SeriesCoef k;
+    asm volatile("" : "+s"(k.c6), "+s"(k.c5), "+s"(k.c4), "+s"(k.c3), "+s"(k.c2));
+    return k;
+}
+
+// A constant formed in scalar registers where it is used: kept out of a loop's vector registers.
+__device__ __forceinline__ double scalar_const(double c)
+{
+    asm volatile("" : "+s"(c));
+    return c;
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs; renumber them so that each XCD
 // works on one contiguous range of slices (neighbouring nodes share its L2).
 __device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t nb)

@@ -39,9 +39,8 @@ namespace host {
 
 constexpr int kDefaultLanes = 1;
 // spare slot rows after the last slice: the sliced kernel prefetches kRowUnroll rows
-// ahead, the staged kernel reads a full piece of stiffness rows
-constexpr size_t kSpareRows = kRowUnroll > kPieceRows ? kRowUnroll : kPieceRows;
-constexpr int64_t kMaxGap = 12;      // staged ranges absorb gaps of up to this many unused records
+// ahead, the staged kernels two blocks of kPairsAhead row pairs
+constexpr size_t kSpareRows = 4 * kPairsAhead;
 constexpr int64_t kGraphChunk = 64;  // steps per captured graph (even: buffer parity repeats)
 
 struct PdError : std::exception {
@@ -114,9 +113,12 @@ struct Inst {
     std::vector<int32_t> dslot_user; // device slot (instance-local) -> user slot, -1 = padding
     std::vector<int64_t> s_start;    // first device slot (instance-local) of every slice
     std::vector<int64_t> s_T;        // 64-wide slot rows of every slice (sliced layout)
-    std::vector<int2> pieces;        // staged layout: {first device node, len | rows << 8}
-    std::vector<int32_t> slice_piece;  // staged layout: first piece of each slice (+ end), local
-    std::vector<uint8_t> ent_idx;    // staged layout: range index of every device slot
+    // staged layout (tables as on the device, see pdmi_internal.h; indices local to the instance)
+    std::vector<TileRec> tiles;
+    std::vector<int2> phases, segs;
+    std::vector<int32_t> list;
+    std::vector<int64_t> tile_rows;  // slot rows of every tile's longest slice
+    std::vector<uint16_t> ent_idx;   // record index of every device slot in its phase (0: padding)
     std::vector<int64_t> rev_slot;   // user slot of the reverse bond (filled on first use)
     bool k_sym = true;               // both slots of every bond carry the same stiffness
     bool br_sym = true;              // both slots of every bond share the broken flag
@@ -150,19 +152,22 @@ struct pd_ctx {
     bool use_graphs = true;
 
     int64_t nn = 0, ns = 0, nslices = 0;
+    int64_t ntiles = 0, stage_max = 0;  // staged layout: tiles, records of the largest phase
+    int64_t stage_slices = 0;  // slices per tile
+    int64_t stage_two = 0;  // records that fitted a CU twice when the layout was made
+    bool adjoint = false;               // the reverse pass has been asked for: its LDS counts
     bool has_stiff = false, has_vol = false, has_body = false, has_knode = false;
     bool has_nofail = false;         // some slot carries the no-failure bit
     bool has_laws = false;           // some instance has damage laws (smax, laws allocated)
     bool has_osb = false;            // the instances run the state-based linear solid
     bool corr_k = false;             // corrections formed per slot in the kernel (no stiffness stream)
     DevBuf rec[2], um[2], v, a, col, kslot, vol, bhat, slice_ptr, slice_T, slice_inst, params, bc_id, bc,
-        step_base, status, phi, pieces, slice_piece, ent;
+        step_base, status, phi, tiles, phases, segs, list, ent;
     DevBuf force, rset, rsum;        // force readout: F (SoA), node list and sum of a resultant
     DevBuf laws, cls, smax;          // damage laws, per-slot law (several per instance), stretch state
     DevBuf osb, minv;                // state-based model: node pairs {theta/m, 1/m}, 1/m
     DevBuf cfv;                      // corrections per slot: family volume per node
     DevBuf unode;                    // device node of every user node (instances concatenated)
-    DevBuf slice_order;              // staged layout: slices in processing order (locality)
 
     // adjoint: per-slot break steps (recorded by every step while allocated) and the
     // (u, v) checkpoints of the last recorded forward run
@@ -246,10 +251,10 @@ inline unsigned n_threads()
 }
 
 template <typename F>
-void parallel_for(int64_t n, F&& f)
+void parallel_for(int64_t n, F&& f, int64_t least = 4096)
 {
     const unsigned nt = n_threads();
-    if (nt <= 1 || n < 4096) {
+    if (nt <= 1 || n < least) {
         f(int64_t(0), n);
         return;
     }
@@ -285,20 +290,23 @@ inline void sync(pd_ctx* ctx) { hip_check(hipStreamSynchronize(ctx->stream), "hi
 
 inline bool fp32(const pd_ctx* ctx) { return ctx->precision == PD_FP32; }
 
-// Bytes of one node-record buffer: nn records, the sentinel and kRecPad spare records.
-inline size_t rec_bytes(int64_t nn) { return static_cast<size_t>(nn + 1 + kRecPad) * 48; }
+// Bytes of one node-record buffer: nn records and the sentinel.
+inline size_t rec_bytes(int64_t nn) { return static_cast<size_t>(nn + 1) * 48; }
 
 // The state of every instance in user order, kept across a rebuild of the device problem.
 struct HostState {
     std::vector<std::vector<double>> u, v, a;   // per instance, n*3
     std::vector<std::vector<uint8_t>> broken;   // per instance, nnz
     std::vector<std::vector<double>> smax;      // per instance, nnz (empty without damage laws)
+    std::vector<std::vector<int32_t>> bstep;    // per instance, nnz (empty: restart from the broken flags)
 };
 
 // ---- pdmi_layout.cpp
 void family_search(int64_t n, const double* x, double delta, std::vector<int64_t>& row_ptr,
                    std::vector<int32_t>& col);
 void build_layout(pd_ctx* ctx, const HostState* S);
+void relayout(pd_ctx* ctx);
+void fit_stage(pd_ctx* ctx);
 void validate_coords(int64_t n, const double* coords, double horizon);
 double validate_family(int64_t n, const double* x, const int64_t* row_ptr, const int32_t* col);
 void new_problem(pd_ctx* ctx, int32_t ninst, const int64_t* n, const double* const* coords, const double* horizon,
@@ -324,6 +332,8 @@ std::vector<uint8_t> broken_of(pd_ctx* ctx, const Inst& I);
 std::vector<double> soa_of(pd_ctx* ctx, const Inst& I, const DevBuf& buf);
 std::vector<double> u_of(pd_ctx* ctx, const Inst& I);
 HostState snapshot(pd_ctx* ctx);
+std::vector<int32_t> bstep_of(pd_ctx* ctx, const Inst& I);
+void upload_bstep(pd_ctx* ctx, const Inst& I, const int32_t* bstep);
 
 // Whether a per-slot array (nullptr: uniform) is equal on the two slots of every bond.
 template <typename T>
@@ -363,8 +373,4 @@ void set_sum(pd_ctx* ctx, const std::vector<int64_t>& idx, const double* field, 
 
 }  // namespace host
 
-// the reverse pass with the staged layout's slices in the order given (nullptr: dispatch
-// order; defined beside the reverse kernels)
-hipError_t launch_adjoint_ordered(const AdjArgs& a, const int32_t* slice_order, bool staged, int lanes,
-                                  hipStream_t s);
 }  // namespace pdmi

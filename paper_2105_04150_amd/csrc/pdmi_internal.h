@@ -10,9 +10,8 @@
 //                                 bond arithmetic); ping-pong like the records
 //   velocity      v[3][nn]        structure of arrays, f64
 //   acceleration  a[3][nn]        structure of arrays, f64 (velocity Verlet)
-//   sentinel      rec[*][nn]      one extra record far from every node; padding slots point at it,
-//                                 followed by kRecPad zero records so the staged kernel's
-//                                 fixed-size range loads stay in bounds
+//   sentinel      rec[*][nn]      one extra record far from every node; padding slots of the
+//                                 sliced layout point at it
 //   slots         col[ns]         int32 per slot in "slices": a slice is the W = 64/G nodes one
 //                                 wavefront serves (G lanes per node); its slots are stored as
 //                                 T rows of 64 entries, entry (t, w*G + g) = slot t*G + g of the
@@ -27,21 +26,24 @@
 //                                 entry nn (the sentinel) is 0
 //   slices        slice_ptr/T/inst first entry, row count and instance of every slice
 //
-// Staged layout (one lane per node, 64 nodes per slice).  The neighbours of a slice are
-// covered by "ranges" of at most kSegMax consecutive device nodes; each range's slots
-// are cut into "pieces" of at most kPieceRows rows of 64 uint16 entries.  A wavefront
-// copies a piece's node records and entries into LDS, then reads neighbours from there.
-//   pieces        int2 {first node of the range, len | T << 8} per piece
-//   slice_piece   first piece of every slice (+ one past the last)
-//   ent[ns]       uint16 per slot: bits 0..12 = byte offset of the neighbour's record in the
-//                 staged copy (48 x index into the range; kEntPad for padding, the LDS
-//                 sentinel record), bit 13 = softened, bit 14 = no-failure zone, bit 15 =
-//                 broken; slice_ptr gives each slice's first entry.
+// Staged layout (one lane per node, 64 nodes per slice).  Nodes are renumbered into compact
+// slices.  A tile is a group of one to four consecutive slices that one workgroup of
+// kTileWaves wavefronts serves (8, 4 or 2 wavefronts a slice).  The records its bonds reach are listed, a tile
+// copies them into LDS and every slot reads its neighbour there; a list that does not
+// fit is worked off in phases.
+//   tiles         TileRec per tile, in dispatch order
+//   phases        int2 {first entry of the list, records} per phase
+//   list          int32 device node per staged record
+//   segs          int2 {first row pair, row pairs} per phase and slice of the tile
+//   ent[ns]       uint16 per slot: bits 0..11 = index of the neighbour's record in the phase,
+//                 from 1 (0: the sentinel of padding slots), bit 13 = softened, bit 14 =
+//                 no-failure zone, bit 15 = broken (and padding).  Rows come in pairs: the
+//                 slots of a lane's two rows are neighbours, ds = 128 pair + 2 lane + row, in
+//                 this and every other per-slot array.
 //   smax[ns]      f64 per slot (with damage laws): the largest stretch the slot reached
 //                 beyond its law's elastic limit (0 while it has not); cls[ns] uint8: the
 //                 slot's law (bond class) when an instance has several
-//                 The entry array ends with kPieceRows spare rows (whole 8-row blocks are
-//                 loaded).
+//                 The per-slot arrays end with kSpareRows spare rows (pairs are loaded ahead).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -54,17 +56,16 @@ constexpr int kBlock = 256;             // 4 wavefronts per workgroup, one slice
 constexpr int kRowUnroll = 2;           // slot rows per step-kernel iteration; every slice's row
                                         // count is a multiple, and the slot arrays carry this
                                         // many spare rows at the end
-constexpr int kSegMax = 80;             // node records per staged range (LDS slot kSegMax: sentinel)
-constexpr int kPieceRows = 8;           // slot rows per staged piece
-constexpr int kStageChunks = 4 * 64;    // 16-byte record chunks one staged range load covers
-constexpr int kEntPad = kStageChunks * 16;  // entry byte offset of the LDS sentinel record
-constexpr int kRecPad = kStageChunks / 3 + 2;  // zero records after the sentinel
+constexpr int kTileWaves = 8;           // wavefronts of a tile's workgroup
+constexpr int kLdsBytes = 160 * 1024;   // of a CU
+constexpr int kTileSlices = 4;          // most slices of a tile
+constexpr int kPairsAhead = 4;          // row pairs whose entries are loaded ahead of their use
 // slot flags: a bond touching a no-failure zone never breaks (Secs. 5.1, 6, 7)
 // and a bond that has softened under a damage law is marked so its state is read
 constexpr int32_t kColNoFail = 0x40000000;  // sliced word: no-failure bit
 constexpr int32_t kColSoft = 0x20000000;    // sliced word: softened bit
 constexpr int32_t kColNode = 0x1fffffff;    // sliced word: neighbour index bits
-constexpr uint32_t kEntOff = 0x1fff;        // staged entry: record byte offset bits
+constexpr uint32_t kEntIdx = 0x0fff;        // staged entry: record index bits
 constexpr uint32_t kEntSoft = 0x2000;       // staged entry: softened bit
 constexpr uint32_t kEntNoFail = 0x4000;     // staged entry: no-failure bit
 constexpr uint32_t kEntBroken = 0x8000;     // staged entry: broken bit
@@ -81,8 +82,11 @@ struct LawRec {
     int32_t nb;
     int32_t pad_;
 };
-static_assert(3 * kSegMax <= kStageChunks, "a range fits the staged record loads");
-static_assert(kEntPad <= kEntOff, "entry offsets fit 13 bits");
+// Ranges of |d| of the staged kernels' slot arithmetic (FP32 build: ...32): up to the first the
+// short series, whose estimate of S^(-1/2) enters its even terms unrefined (below 9e-13 in
+// all, 1e-13 rms); up to the second the long one (1e-15); closed form beyond.
+constexpr double kMidRange = 2.0e-3, kWideRange = 3.4e-2;
+constexpr double kMidRange32 = 1.0e-2, kWideRange32 = 0.1;  // to 5e-9
 constexpr int32_t kNodeFree = -1;       // bc_id of an unconstrained node
 constexpr int32_t kNodePad = -2;        // bc_id of a padding node (never updated)
 
@@ -92,6 +96,15 @@ constexpr int32_t kNodePad = -2;        // bc_id of a padding node (never update
 // stretch an absolute error near 1e-16; the margin is far wider than both and so narrow
 // that slots rarely land inside it.
 __host__ __device__ inline double decision_margin(double t) { return 1e-9 * (t < 0.0 ? -t : t) + 1e-15; }
+
+// What the workgroup of a tile reads first.
+struct TileRec {
+    int32_t slice, nslices;  // first slice, slices
+    int32_t phase, nphases;  // first phase, phases
+    int32_t list, n;         // the first phase's list entry and records
+    int32_t inst;
+    int32_t seg;             // first entry of segs: phase ph, slice k at seg + ph * nslices + k
+};
 
 struct InstParams {
     double c;        // micromodulus without a stiffness field
@@ -107,18 +120,23 @@ struct InstParams {
     int32_t has_body;
     int32_t nlaw;    // damage laws of the instance (0: the brittle law with q0)
     int32_t law_off; // first law of the instance in StepArgs::laws
-    int32_t pad_;
+    int32_t hi_pos;  // high word of d = q / (2 + q) at which the short series' rows end: the
+                     // decision edge q0 or the series' range
+
     double osb_a;    // state-based linear solid: 3K - 5G
     double osb_b;    // state-based linear solid: 15G
-    // stiffness corrections evaluated per slot (kernels with CORR): flags bit 0 conical
-    // profile 1 - |xi|/delta, bit 1 partial volume clamp((delta + dx/2 - |xi|)/dx, 0, 1),
-    // bit 2 surface factor 2 V0 / (V_i + V_j) over family volumes
-    double cr_idelta;  // 1/delta
-    double cr_pvhi;    // (delta + dx/2)/dx
-    double cr_idx;     // 1/dx
-    double cr_2v0;     // 2 V0
-    int32_t cr_flags;
-    int32_t pad2_;
+    // stiffness corrections evaluated per slot (kernels with CORR): the conical profile
+    // max(1 - |xi|/delta, 0), the partial volume clamp((delta + dx/2 - |xi|)/dx, 0, 1), the
+    // surface factor 2 V0 / (V_i + V_j) over family volumes
+    double cr_idelta;  // 1/delta (0 without the profile)
+    double cr_pvhi;    // (delta + dx/2)/dx (1 without partial volumes)
+    double cr_idx;     // 1/dx (0 without)
+    double cr_2v0;     // 2 V0 (2 without the surface factor, whose family volumes are then 1)
+    uint32_t hi_neg;   // the same below zero (high word as unsigned; only the range)
+    int32_t hi_pos32;  // the FP32 build's, as bits of its d
+    uint32_t hi_neg32;
+    int32_t hi_wpos, hi_wpos32;  // the long series' ends
+    uint32_t hi_wneg, hi_wneg32;
 };
 
 // Constraint of one node: per component d, kind in bits 2d..2d+1 (0 free, 1 displacement,
@@ -152,19 +170,23 @@ struct StepArgs {
     const LawRec* laws;         // damage laws of every instance (nullptr without)
     const uint8_t* cls;         // per slot: law index within the instance (nullptr: 0)
     double* smax;               // per slot: largest stretch beyond the elastic limit
-    double2* osb;               // state-based model: per node {theta / m, 1 / m} (nn + 128 entries)
+    double2* osb;               // state-based model: per node {a, b - a}, a = (3K - 5G) theta / m, b = 15 G / m
     const double* minv;         // state-based model: per node 1 / m (padding 0)
     const double* cfv;          // corrections per slot: family volume per node (padding and the sentinel 1)
+    bool partial;               // and some instance has partial volumes
     const int64_t* slice_ptr;
     const int32_t* slice_T;
     const int32_t* slice_inst;
-    const int32_t* slice_order; // staged step: slice of each workgroup in dispatch order (nullptr: its own)
     const InstParams* params;
     const int32_t* bc_id;
     const BCRec* bc;
-    const int2* pieces;         // staged layout only
-    const int32_t* slice_piece; // staged layout only
-    uint16_t* ent;              // staged layout only
+    const TileRec* tiles;       // staged layout only
+    const int2* phases;
+    const int2* segs;
+    const int32_t* list;
+    uint16_t* ent;
+    int64_t ntiles;
+    int32_t stage_max;          // records of the largest phase
     const int64_t* step_base;   // completed steps when the launch sequence started
     int32_t* status;            // bit 0: a non-finite u or v was produced
     int32_t* bstep;             // per slot: the pass in which the slot broke (written on breaking)
@@ -184,9 +206,12 @@ struct DamageArgs {
     const InstParams* params;
     double* phi;
     int64_t nslices;
-    const int2* pieces;         // staged layout only
-    const int32_t* slice_piece;
+    const TileRec* tiles;       // staged layout only
+    const int2* phases;
+    const int2* segs;
+    const int32_t* list;
     const uint16_t* ent;
+    int64_t ntiles;
     const LawRec* laws;         // damage laws (nullptr without)
     const uint8_t* cls;
     const double* smax;
@@ -201,10 +226,10 @@ hipError_t launch_drift(const StepArgs& a, bool fp32, hipStream_t s);
 
 hipError_t launch_damage(const DamageArgs& a, int lanes, hipStream_t s);
 
-// staged mapping, FP64 or FP32 bond arithmetic, `split` wavefronts per slice
-hipError_t launch_step_staged(const StepArgs& a, int mode, bool fp32, int split, bool ext, hipStream_t s);
-hipError_t launch_step_staged_f64(const StepArgs& a, int mode, int split, bool ext, hipStream_t s);
-hipError_t launch_step_staged_f32(const StepArgs& a, int mode, int split, bool ext, hipStream_t s);
+// staged mapping, FP64 or FP32 bond arithmetic
+hipError_t launch_step_staged(const StepArgs& a, int mode, bool fp32, bool ext, hipStream_t s);
+hipError_t launch_step_staged_f64(const StepArgs& a, int mode, bool ext, hipStream_t s);
+hipError_t launch_step_staged_f32(const StepArgs& a, int mode, bool ext, hipStream_t s);
 
 // out[d] = sum over the m device nodes idx[] of w_i field[i * snode + d * scomp], w_i = wv[i]
 // or w when wv is nullptr, summed in a fixed order (force resultants, set means); with
@@ -223,10 +248,10 @@ hipError_t launch_damage_staged(const DamageArgs& a, hipStream_t s);
 // state-based linear solid (staged layout, FP64 or FP32 bond arithmetic): the dilation
 // pass alone (breaking or a force evaluation), and a whole step (dilation pass, then the
 // force pass with the integrator of `mode`)
-hipError_t launch_osb_dilation(const StepArgs& a, bool breaking, bool fp32, int split, hipStream_t s);
-hipError_t launch_osb_step(const StepArgs& a, int mode, bool fp32, int split, hipStream_t s);
-constexpr int kOsbPad = 128;    // spare pairs after the last node (the pass-2 range copy)
-constexpr int kCorrPad = 128;   // spare family volumes after the last node (the step kernels' copy window)
+hipError_t launch_osb_dilation(const StepArgs& a, bool breaking, bool fp32, hipStream_t s);
+hipError_t launch_osb_step(const StepArgs& a, int mode, bool fp32, hipStream_t s);
+constexpr int kOsbPad = 1;    // the sentinel's pair
+constexpr int kCorrPad = 1;   // the sentinel's family volume
 
 hipError_t launch_advance(int64_t* step_base, int64_t by, hipStream_t s);
 // out[i * ncomp + d] = src[off + dnode[i] * snode + d * scomp], i < n (readout to device memory)
@@ -257,8 +282,12 @@ struct AdjArgs {
     const int32_t* bstep;
     const int32_t* col;         // sliced layout
     const uint16_t* ent;        // staged layout
-    const int2* pieces;
-    const int32_t* slice_piece;
+    const TileRec* tiles;
+    const int2* phases;
+    const int2* segs;
+    const int32_t* list;
+    int64_t ntiles;
+    int32_t stage_max;
     const double* kslot;
     const double* vol;
     const double* na;           // per-node stiffness factors sqrt(k_i) (or nullptr)

@@ -19,30 +19,58 @@ __device__ __forceinline__ double intact_share(const DamageArgs& A, const InstPa
     return 1.0 - law_damage(L, A.smax[ds]);
 }
 
-// Local damage on the staged layout.
+// Local damage on the staged layout: one wavefront a slice.  A chain of loads bounds it, so a
+// block of row pairs has its entries, stretch states and volumes in flight together.
+template <bool LAWS, bool VOLN>
 __global__ __launch_bounds__(kWave) void damage_staged(DamageArgs A)
 {
+    constexpr int B = 8;
     const int lane = threadIdx.x;
-    const int64_t slice = wave_uniform(xcd_remap(blockIdx.x, gridDim.x));
-    if (slice >= A.nslices) return;
-    const InstParams P = A.params[A.slice_inst[slice]];
-    const int64_t node = slice * kWave + lane;
-    const int p0 = A.slice_piece[slice], p1 = A.slice_piece[slice + 1];
-    int64_t ent = A.slice_ptr[slice];
+    const TileRec T = A.tiles[blockIdx.x / kTileSlices];
+    const int k = static_cast<int>(blockIdx.x % kTileSlices);
+    if (k >= T.nslices) return;
+    const InstParams& P = A.params[T.inst];
+    const int64_t node = (static_cast<int64_t>(T.slice) + k) * kWave + lane;
+    const uint32_t* __restrict__ ent = reinterpret_cast<const uint32_t*>(A.ent) + lane;
+    const double2* __restrict__ smax = reinterpret_cast<const double2*>(A.smax) + lane;
     double num = 0.0, den = 0.0;
-    for (int p = p0; p < p1; ++p) {
-        const int2 m = A.pieces[p];
-        const int T = (m.y >> 8) & 0xff;
-        for (int t = 0; t < T; ++t) {
-            const int64_t ds = ent + t * kWave + lane;
-            const uint16_t e = A.ent[ds];
-            const int off = e & kEntOff;
-            if (off == kEntPad) continue;  // padding
-            const double vj = A.vol ? A.vol[m.x + off / 48] : P.volume;
-            den += vj;
-            num += intact_share(A, P, ds, (e & kEntBroken) != 0, (e & kEntSoft) != 0) * vj;
+    for (int ph = 0; ph < T.nphases; ++ph) {
+        const int2 pd = A.phases[T.phase + ph], g = A.segs[T.seg + ph * T.nslices + k];
+        const int end = g.x + g.y;
+#pragma unroll 1
+        for (int t = g.x; t < end; t += B) {
+            uint32_t e[B];
+            double2 sm[B];
+            double v[2 * B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const int64_t at = static_cast<int64_t>(min(t + u, end - 1)) * kWave;
+                e[u] = ent[at];
+                if (LAWS) sm[u] = smax[at];
+            }
+            if (VOLN) {
+#pragma unroll
+                for (int u = 0; u < 2 * B; ++u) {
+                    const int idx = static_cast<int>((u & 1 ? e[u / 2] >> 16 : e[u / 2]) & kEntIdx);
+                    v[u] = A.vol[A.list[pd.x + max(idx, 1) - 1]];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2 * B; ++u) {
+                const uint32_t h = u & 1 ? e[u / 2] >> 16 : e[u / 2] & 0xffffu;
+                if (t + u / 2 >= end || (h & kEntIdx) == 0) continue;  // padding
+                const double vj = VOLN ? v[u] : P.volume;
+                den += vj;
+                if (h & kEntBroken) continue;
+                double share = 1.0;
+                if (LAWS && (h & kEntSoft) != 0 && P.nlaw != 0) {
+                    const int64_t ds = static_cast<int64_t>(t + u / 2) * (2 * kWave) + 2 * lane + (u & 1);
+                    const LawRec& L = A.laws[P.law_off + (P.nlaw > 1 ? A.cls[ds] : 0)];
+                    share = 1.0 - law_damage(L, u & 1 ? sm[u / 2].y : sm[u / 2].x);
+                }
+                num += share * vj;
+            }
         }
-        ent += static_cast<int64_t>(T) * kWave;
     }
     A.phi[node] = den > 0.0 ? 1.0 - num / den : 0.0;
 }
@@ -199,15 +227,23 @@ hipError_t launch_damage(const DamageArgs& a, int lanes, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_step_staged(const StepArgs& a, int mode, bool fp32, int split, bool ext, hipStream_t s)
+hipError_t launch_step_staged(const StepArgs& a, int mode, bool fp32, bool ext, hipStream_t s)
 {
-    return fp32 ? launch_step_staged_f32(a, mode, split, ext, s) : launch_step_staged_f64(a, mode, split, ext, s);
+    return fp32 ? launch_step_staged_f32(a, mode, ext, s) : launch_step_staged_f64(a, mode, ext, s);
 }
 
 hipError_t launch_damage_staged(const DamageArgs& a, hipStream_t s)
 {
-    if (a.nslices <= 0) return hipSuccess;
-    hipLaunchKernelGGL(damage_staged, dim3(static_cast<unsigned>(a.nslices)), dim3(kWave), 0, s, a);
+    if (a.ntiles <= 0) return hipSuccess;
+    const dim3 grid(static_cast<unsigned>(a.ntiles * kTileSlices));
+    if (a.laws && a.smax && a.vol)
+        hipLaunchKernelGGL((damage_staged<true, true>), grid, dim3(kWave), 0, s, a);
+    else if (a.laws && a.smax)
+        hipLaunchKernelGGL((damage_staged<true, false>), grid, dim3(kWave), 0, s, a);
+    else if (a.vol)
+        hipLaunchKernelGGL((damage_staged<false, true>), grid, dim3(kWave), 0, s, a);
+    else
+        hipLaunchKernelGGL((damage_staged<false, false>), grid, dim3(kWave), 0, s, a);
     return hipGetLastError();
 }
 

@@ -152,22 +152,18 @@ static void node_order(Inst& I, int order, double h)
     I.perm = std::move(p);
 }
 
-// Processing order of the staged slices (context-wide indices).  xcd_remap hands each XCD
-// a contiguous share of the dispatch positions; within every share the slices keep their
-// device order but the longer ones (more slot rows, in buckets of 8) go first, so that the
-// last workgroups of a launch are the short ones and the tail of the launch is short.
-// Every slice writes only its own nodes, so results do not depend on the order.
-static std::vector<int32_t> slice_dispatch_order(const std::vector<int32_t>& slice_piece,
-                                                 const std::vector<int2>& pieces)
+// Dispatch order of the staged tiles (context-wide indices).  xcd_remap hands each XCD a
+// contiguous share of the dispatch positions; within every share the tiles keep their
+// device order but those with more slot rows (in buckets of 8) go first, so that the last
+// workgroups of a launch are the short ones and the tail of the launch is short.
+// Every tile writes only its own nodes, so results do not depend on the order.
+static std::vector<int32_t> tile_dispatch_order(const std::vector<int64_t>& rows)
 {
-    const int64_t nsl = static_cast<int64_t>(slice_piece.size()) - 1;
-    std::vector<int32_t> order(static_cast<size_t>(nsl)), rows(static_cast<size_t>(nsl), 0);
-    for (int64_t s = 0; s < nsl; ++s) {
-        order[s] = static_cast<int32_t>(s);
-        for (int32_t q = slice_piece[s]; q < slice_piece[s + 1]; ++q) rows[s] += (pieces[q].y >> 8) & 0xff;
-    }
+    const int64_t nt = static_cast<int64_t>(rows.size());
+    std::vector<int32_t> order(static_cast<size_t>(nt));
+    std::iota(order.begin(), order.end(), 0);
     constexpr int64_t X = 8;  // XCDs, as xcd_remap splits the dispatch
-    const int64_t m = nsl / X, r = nsl % X;
+    const int64_t m = nt / X, r = nt % X;
     int64_t b0 = 0;
     for (int64_t x = 0; x < X; ++x) {
         const int64_t len = m + (x < r ? 1 : 0);
@@ -204,103 +200,368 @@ static std::vector<int32_t> slot_ranks(const Inst& I, double h)
     return order;
 }
 
-// Staged layout of one instance (one lane per node, 64 nodes per slice): per slice, the
-// sorted union of neighbour device indices is cut into ranges of consecutive nodes
-// (at most kSegMax long); each lane's slots in a range, in ascending neighbour order,
-// fill rows of pieces of at most kPieceRows rows.  Fills start (first slot of each slice),
-// pieces, slice_piece, dslot_user and ent_idx; returns the slot count.
-static int64_t build_staged(Inst& I, std::vector<int64_t>& start)
+// A node and its lattice cell, for the recursive bisection into compact slices.
+struct CellNode {
+    int32_t q[3];
+    int32_t id;
+};
+
+// Nodes [lo, hi) into nsl slices of 64 (the last of the instance may be short): cut across
+// the longest extent, at a multiple of `group` slices while a part holds more than one
+// group, so that the slices of a group are neighbours too.  The cut leaves whole groups of
+// about cubic shape on both sides (13 of them across are cut 6 to 7, not in halves: a
+// 100 x 25 x 20 lattice stages 4.1 records a node in place of 4.3, 117 x 33 x 33 at horizon 3.14
+// 4.5 in place of 4.6).  Nodes of one slice end up in ascending order.
+static void bisect(CellNode* p, int64_t lo, int64_t hi, int64_t nsl, int64_t group, int depth)
 {
-    const int64_t nsl = I.nslices;
-    std::vector<std::vector<int2>> spieces(static_cast<size_t>(nsl));
-    std::vector<std::vector<int32_t>> suser(static_cast<size_t>(nsl));
-    std::vector<std::vector<uint8_t>> sidx(static_cast<size_t>(nsl));
-    parallel_for(nsl, [&](int64_t s0, int64_t s1) {
-        std::vector<std::array<int64_t, 3>> sl;  // (device neighbour, lane, user slot)
-        std::vector<std::vector<std::pair<int32_t, uint8_t>>> per_lane(kWave);
-        for (int64_t s = s0; s < s1; ++s) {
-            sl.clear();
-            for (int w = 0; w < kWave; ++w) {
-                const int64_t p = I.perm[s * kWave + w];
-                if (p < 0) continue;
-                for (int64_t b = I.row_ptr[p]; b < I.row_ptr[p + 1]; ++b)
-                    sl.push_back({I.node_off + I.iperm[I.col[b]], w, b});
-            }
-            std::sort(sl.begin(), sl.end());
-            auto& pcs = spieces[s];
-            auto& us = suser[s];
-            auto& ix = sidx[s];
-            size_t k = 0;
-            while (k < sl.size()) {
-                // one range: consecutive device nodes starting at sl[k][0]
-                const int64_t r0 = sl[k][0];
-                size_t e = k;
-                // small gaps are loaded along (cheaper than another piece)
-                while (e < sl.size() && sl[e][0] - r0 < kSegMax && sl[e][0] - sl[e == k ? k : e - 1][0] <= kMaxGap)
-                    ++e;
-                const int64_t len = sl[e - 1][0] - r0 + 1;
-                for (auto& v : per_lane) v.clear();
-                for (size_t q = k; q < e; ++q)
-                    per_lane[sl[q][1]].push_back({static_cast<int32_t>(sl[q][2]), static_cast<uint8_t>(sl[q][0] - r0)});
-                size_t T = 0;
-                for (auto& v : per_lane) T = std::max(T, v.size());
-                for (size_t t0 = 0; t0 < T; t0 += kPieceRows) {
-                    const int rows = static_cast<int>(std::min<size_t>(kPieceRows, T - t0));
-                    pcs.push_back(int2{static_cast<int>(r0), static_cast<int>(len | (rows << 8))});
-                    for (int t = 0; t < rows; ++t)
-                        for (int w = 0; w < kWave; ++w) {
-                            const auto& v = per_lane[w];
-                            if (t0 + t < v.size()) {
-                                us.push_back(v[t0 + t].first);
-                                ix.push_back(v[t0 + t].second);
-                            } else {
-                                us.push_back(-1);
-                                ix.push_back(static_cast<uint8_t>(kSegMax));
-                            }
-                        }
-                }
-                k = e;
-            }
-        }
-    });
-    I.pieces.clear();
-    I.slice_piece.assign(static_cast<size_t>(nsl) + 1, 0);
-    start.assign(static_cast<size_t>(nsl), 0);
-    int64_t nds = 0;
-    for (int64_t s = 0; s < nsl; ++s) {
-        I.slice_piece[s] = static_cast<int32_t>(I.pieces.size());
-        start[s] = nds;
-        I.pieces.insert(I.pieces.end(), spieces[s].begin(), spieces[s].end());
-        nds += static_cast<int64_t>(suser[s].size());
+    if (nsl <= 1) {
+        std::sort(p + lo, p + hi, [](const CellNode& a, const CellNode& b) { return a.id < b.id; });
+        return;
     }
-    I.slice_piece[nsl] = static_cast<int32_t>(I.pieces.size());
-    I.dslot_user.resize(static_cast<size_t>(nds));
-    I.ent_idx.resize(static_cast<size_t>(nds));
-    parallel_for(nsl, [&](int64_t s0, int64_t s1) {
-        for (int64_t s = s0; s < s1; ++s) {
-            std::copy(suser[s].begin(), suser[s].end(), I.dslot_user.begin() + start[s]);
-            std::copy(sidx[s].begin(), sidx[s].end(), I.ent_idx.begin() + start[s]);
+    int32_t mn[3], mx[3];
+    for (int d = 0; d < 3; ++d) mn[d] = mx[d] = p[lo].q[d];
+    for (int64_t i = lo + 1; i < hi; ++i)
+        for (int d = 0; d < 3; ++d) {
+            mn[d] = std::min(mn[d], p[i].q[d]);
+            mx[d] = std::max(mx[d], p[i].q[d]);
         }
+    int ax[3] = {2, 1, 0};  // ties: z first, so that x stays the longest run
+    std::stable_sort(ax, ax + 3, [&](int a, int b) { return mx[a] - mn[a] > mx[b] - mn[b]; });
+    int64_t left = nsl / 2;
+    if (nsl > group) {
+        // edge of a cubic group, axes that are thinner than that set aside
+        const double T = static_cast<double>(nsl) / static_cast<double>(group);
+        double e[3];
+        for (int k = 0; k < 3; ++k) e[k] = mx[ax[k]] - mn[ax[k]] + 1;
+        double edge = std::cbrt(e[0] * e[1] * e[2] / T);
+        if (e[2] < edge) edge = std::sqrt(e[0] * e[1] / T);
+        if (e[1] < edge) edge = e[0] / T;
+        const double across = std::max(2.0, std::round(e[0] / edge));
+        left = std::llround(T * std::floor(0.5 * across) / across) * group;
+        left = std::min(std::max(left, group), (nsl - 1) / group * group);
+    }
+    const int64_t mid = lo + left * kWave;
+    std::nth_element(p + lo, p + mid, p + hi, [&](const CellNode& a, const CellNode& b) {
+        for (int d : {ax[0], ax[1], ax[2]})
+            if (a.q[d] != b.q[d]) return a.q[d] < b.q[d];
+        return a.id < b.id;
     });
-    return nds;
+    if (depth > 0 && hi - lo > 8192) {
+        std::thread t([&] { bisect(p, lo, mid, left, group, depth - 1); });
+        bisect(p, mid, hi, nsl - left, group, depth - 1);
+        t.join();
+    } else {
+        bisect(p, lo, mid, left, group, 0);
+        bisect(p, mid, hi, nsl - left, group, 0);
+    }
+}
+
+// Device-local node order of one instance on the staged layout: compact slices, and within
+// a slice lanes by bank class, so that 16 lanes that read the neighbours at one offset
+// together find them in different banks.
+static void slice_nodes(Inst& I, int64_t group, double h, std::vector<uint8_t>& bank)
+{
+    double lo[3];
+    for (int d = 0; d < 3; ++d) lo[d] = I.x[d];
+    for (int64_t i = 1; i < I.n; ++i)
+        for (int d = 0; d < 3; ++d) lo[d] = std::min(lo[d], I.x[3 * i + d]);
+    std::vector<CellNode> c(static_cast<size_t>(I.n));
+    for (int64_t i = 0; i < I.n; ++i) {
+        for (int d = 0; d < 3; ++d)
+            c[i].q[d] = static_cast<int32_t>(std::min(std::floor((I.x[3 * i + d] - lo[d]) / h + 0.5), 1.0e9));
+        c[i].id = static_cast<int32_t>(i);
+    }
+    // bank class: 48-byte records at indices equal mod 16 share their LDS banks; on a lattice
+    // a 4 x 4 patch of nodes covers all 16 classes
+    bank.resize(static_cast<size_t>(I.n));
+    for (int64_t i = 0; i < I.n; ++i) bank[i] = static_cast<uint8_t>((c[i].q[0] + 12 * c[i].q[1] + 3 * c[i].q[2]) & 15);
+    bisect(c.data(), 0, I.n, (I.n + kWave - 1) / kWave, group, 4);
+    I.perm.resize(static_cast<size_t>(I.n));
+    I.iperm.resize(static_cast<size_t>(I.n));
+    // lanes of a slice: bank class c to lanes c, c + 16, ... as far as they go
+    for (int64_t l0 = 0; l0 < I.n; l0 += kWave) {
+        const int top = static_cast<int>(std::min<int64_t>(kWave, I.n - l0));
+        int next[16];
+        int32_t spill[kWave];
+        int ns = 0;
+        for (int k = 0; k < 16; ++k) next[k] = k;
+        for (int l = 0; l < top; ++l) {
+            const int32_t id = c[l0 + l].id;
+            int& f = next[bank[id]];
+            if (f < top) {
+                I.perm[l0 + f] = id;
+                f += 16;
+            } else {
+                spill[ns++] = id;
+            }
+        }
+        for (int k = 0, m = 0; m < ns; ++m) {
+            while (next[k] >= top) ++k;
+            I.perm[l0 + next[k]] = spill[m];
+            next[k] += 16;
+        }
+    }
+    for (int64_t l = 0; l < I.n; ++l) I.iperm[I.perm[l]] = l;
+}
+
+// Records that fit a workgroup's LDS: beside one other workgroup on the CU, and alone.
+struct StageRoom {
+    int64_t two, one;
+};
+
+// User nodes that the bonds of nsl slices reach, ascending (seen: zeros, and zeros again after).
+static void reached(const Inst& I, int64_t slice, int64_t nsl, std::vector<uint8_t>& seen, std::vector<int32_t>& nodes)
+{
+    nodes.clear();
+    for (int64_t l = slice * kWave; l < (slice + nsl) * kWave; ++l) {
+        const int64_t p = I.perm[l];
+        if (p < 0) continue;
+        for (int64_t b = I.row_ptr[p]; b < I.row_ptr[p + 1]; ++b)
+            if (!seen[I.col[b]]) {
+                seen[I.col[b]] = 1;
+                nodes.push_back(I.col[b]);
+            }
+    }
+    std::sort(nodes.begin(), nodes.end());
+    for (int32_t j : nodes) seen[j] = 0;
+}
+
+// Staged layout of one instance: tiles of up to `group` consecutive slices.  The nodes that
+// a tile's bonds reach are cut into phases of at most room.one records (one phase unless
+// the families are very large); each lane's slots of a phase, in ascending neighbour order,
+// fill its slice's row pairs.  Fills the tile, phase and segment tables, dslot_user and
+// ent_idx (index of the slot's record in its phase, from 1); returns the slot count.
+static int64_t build_staged(Inst& I, int64_t group, const StageRoom& room, const std::vector<uint8_t>& bank)
+{
+    struct Part {
+        int64_t slice = 0, nsl = 0;
+        std::vector<int32_t> nodes;  // user nodes reached, ascending
+        int32_t nphase = 0, per = 0;
+        std::vector<int32_t> at;     // record index of every one in its phase
+        std::vector<int32_t> n;      // records per phase
+        std::vector<int32_t> pairs;  // per phase and slice of the tile
+    };
+    const int64_t ng = (I.nslices + group - 1) / group;
+    std::vector<std::vector<Part>> parts(static_cast<size_t>(ng));
+    parallel_for(ng, [&](int64_t g0, int64_t g1) {
+        std::vector<uint8_t> seen(static_cast<size_t>(I.n), 0);
+        for (int64_t g = g0; g < g1; ++g) {
+            std::vector<Part>& out = parts[g];
+            out.emplace_back();
+            out[0].slice = g * group;
+            out[0].nsl = std::min(group, I.nslices - g * group);
+            reached(I, out[0].slice, out[0].nsl, seen, out[0].nodes);
+            // Two workgroups a CU hide each other's staging: a tile of three or four slices that
+            // does not fit twice is cut in two (node weights on the 1M-node cube: 119 us, uncut
+            // 166).  Two slices stay together (horizon 5.015: 185 us, cut 208).
+            if (out[0].nsl > 2 && static_cast<int64_t>(out[0].nodes.size()) > room.two) {
+                Part a, b;
+                a.slice = out[0].slice;
+                a.nsl = (out[0].nsl + 1) / 2;
+                b.slice = a.slice + a.nsl;
+                b.nsl = out[0].nsl - a.nsl;
+                reached(I, a.slice, a.nsl, seen, a.nodes);
+                reached(I, b.slice, b.nsl, seen, b.nodes);
+                out.clear();
+                out.push_back(std::move(a));
+                out.push_back(std::move(b));
+            }
+            for (Part& P : out) {
+                const int64_t R = static_cast<int64_t>(P.nodes.size());
+                P.nphase = static_cast<int32_t>((R + room.one - 1) / room.one);
+                P.per = P.nphase ? static_cast<int32_t>((R + P.nphase - 1) / P.nphase) : 0;
+                P.at.resize(static_cast<size_t>(R));
+                for (int ph = 0; ph < P.nphase; ++ph) {
+                    // a record goes to the next place of its bank class (index mod 16); the few that
+                    // find their class full take the places left over
+                    const int64_t r0 = static_cast<int64_t>(ph) * P.per, r1 = std::min<int64_t>(R, r0 + P.per);
+                    const int32_t top = static_cast<int32_t>(r1 - r0);
+                    int32_t next[16];
+                    for (int c = 0; c < 16; ++c) next[c] = c;
+                    for (int64_t r = r0; r < r1; ++r) {
+                        int32_t& f = next[bank[P.nodes[r]]];
+                        P.at[r] = f < top ? f : -1;
+                        if (f < top) f += 16;
+                    }
+                    int c = 0;
+                    for (int64_t r = r0; r < r1; ++r) {
+                        if (P.at[r] >= 0) continue;
+                        while (next[c] >= top) ++c;
+                        P.at[r] = next[c];
+                        next[c] += 16;
+                    }
+                    P.n.push_back(top);
+                }
+                P.pairs.assign(static_cast<size_t>(P.nphase * P.nsl), 0);
+                for (int64_t k = 0; k < P.nsl; ++k)
+                    for (int w = 0; w < kWave; ++w) {
+                        const int64_t p = I.perm[(P.slice + k) * kWave + w];
+                        if (p < 0) continue;
+                        const auto last = I.col.begin() + I.row_ptr[p + 1];
+                        auto from = I.col.begin() + I.row_ptr[p];
+                        for (int ph = 0; ph < P.nphase; ++ph) {
+                            const int64_t next = static_cast<int64_t>(ph + 1) * P.per;
+                            const auto to = next < R ? std::lower_bound(from, last, P.nodes[next]) : last;
+                            int32_t& q = P.pairs[ph * P.nsl + k];
+                            q = std::max(q, static_cast<int32_t>((to - from + 1) / 2));
+                            from = to;
+                        }
+                    }
+            }
+        }
+    }, 64);
+    I.tiles.clear();
+    I.phases.clear();
+    I.segs.clear();
+    I.tile_rows.clear();
+    std::vector<const Part*> part;
+    int64_t npair = 0, nlist = 0;
+    for (const auto& ps : parts)
+        for (const Part& P : ps) {
+            part.push_back(&P);
+            I.tiles.push_back(TileRec{static_cast<int>(P.slice), static_cast<int>(P.nsl), static_cast<int>(I.phases.size()),
+                                      P.nphase, static_cast<int>(nlist), P.nphase ? P.n[0] : 0, 0,
+                                      static_cast<int>(I.segs.size())});
+            int64_t total = 0;
+            for (int ph = 0; ph < P.nphase; ++ph) {
+                I.phases.push_back(int2{static_cast<int>(nlist), P.n[ph]});
+                nlist += P.n[ph];
+                for (int64_t k = 0; k < P.nsl; ++k) {
+                    const int32_t q = P.pairs[ph * P.nsl + k];
+                    I.segs.push_back(int2{static_cast<int>(npair), q});
+                    npair += q;
+                    total += 2 * q;
+                }
+            }
+            I.tile_rows.push_back(total);
+        }
+    if (npair * 2 * kWave >= std::numeric_limits<int32_t>::max())
+        fail(PD_ERANGE, "device problem needs 2^31 or more slots");
+    I.list.resize(static_cast<size_t>(nlist));
+    I.dslot_user.resize(static_cast<size_t>(npair * 2 * kWave));
+    I.ent_idx.resize(static_cast<size_t>(npair * 2 * kWave));
+    parallel_for(static_cast<int64_t>(part.size()), [&](int64_t t0, int64_t t1) {
+        std::vector<int32_t> at(static_cast<size_t>(I.n), 0);  // index of a node in the tile's list
+        for (int64_t t = t0; t < t1; ++t) {
+            const Part& P = *part[t];
+            const TileRec& T = I.tiles[t];
+            const int64_t R = static_cast<int64_t>(P.nodes.size());
+            for (int64_t r = 0; r < R; ++r) at[P.nodes[r]] = P.at[r];
+            for (int ph = 0; ph < P.nphase; ++ph) {
+                const int2 S = I.phases[T.phase + ph];
+                const int64_t r0 = static_cast<int64_t>(ph) * P.per, r1 = std::min<int64_t>(R, r0 + P.per);
+                for (int64_t r = r0; r < r1; ++r)
+                    I.list[S.x + P.at[r]] = static_cast<int32_t>(I.node_off + I.iperm[P.nodes[r]]);
+                for (int k = 0; k < T.nslices; ++k) {
+                    const int2 g = I.segs[T.seg + ph * T.nslices + k];
+                    for (int w = 0; w < kWave; ++w) {
+                        const int64_t p = I.perm[(static_cast<int64_t>(T.slice) + k) * kWave + w];
+                        int64_t b = 0, b1 = 0;
+                        if (p >= 0) {
+                            b = I.row_ptr[p];
+                            b1 = I.row_ptr[p + 1];
+                            const auto first = I.col.begin() + b, last = I.col.begin() + b1;
+                            if (ph > 0) b += std::lower_bound(first, last, P.nodes[r0]) - first;
+                            if (r1 < R) b1 = std::lower_bound(first, last, P.nodes[r1]) - I.col.begin();
+                        }
+                        for (int64_t q = 0; q < 2 * static_cast<int64_t>(g.y); ++q) {
+                            const int64_t ds = (g.x + q / 2) * (2 * kWave) + 2 * w + (q & 1);
+                            const bool real = b + q < b1;
+                            I.dslot_user[ds] = real ? static_cast<int32_t>(b + q) : -1;
+                            I.ent_idx[ds] = real ? static_cast<uint16_t>(at[I.col[b + q]] + 1) : 0;
+                        }
+                    }
+                }
+            }
+        }
+    }, 64);
+    return npair * 2 * kWave;
+}
+
+// Records a phase may hold: what fits a workgroup's LDS in every kernel that the problem can
+// run with what it carries now (48 bytes a record, 8 for a weight of its node, 16 for the
+// state-based pair, 24 for the adjoint velocity), beside the partial sums of the largest
+// split and the kernels' static LDS.
+static StageRoom stage_room(const pd_ctx* ctx)
+{
+    bool vol = false, knode = false, corr = false, osb = false;
+    for (const Inst& I : ctx->inst) {
+        vol |= !I.vols.empty();
+        knode |= !I.knode.empty();
+        corr |= I.has_corr;
+        osb |= I.osb;
+    }
+    const int64_t weight = vol || knode || corr ? 8 : 0;
+    int64_t per = 48 + weight;
+    if (osb) per = 64 + weight;
+    if (ctx->adjoint) per = std::max<int64_t>(per, 72 + (vol ? 8 : 0) + (knode ? 8 : 0));
+    const int64_t fixed = 1280;  // the kernels' static LDS, in the hardware's steps
+    return StageRoom{(kLdsBytes / 2 - fixed) / per - 1, std::min<int64_t>((kLdsBytes - fixed) / per - 1, kEntIdx)};
+}
+
+// Slices of a tile, from the slices of all instances: large tiles stage each record for more
+// bonds, but a launch wants about three a CU.  us/step with 4, 2, 1 slices a tile: 1M nodes
+// (15625 slices) 183, 206, 276; 262144 nodes 48, 51, 63; 125000 nodes 35.5, 34.4, 38; 50000
+// nodes 18.9, 18.2, 21; 1000 nodes 14.9, 9.8, 7.5.  With damage laws one: the softened bonds
+// gather in few tiles, whose slot-by-slot work is the launch's tail (127k nodes with a grown
+// crack: 67, 81, 107 us a step with 1, 2, 4).  The mapping's lanes have no say in it.
+static int64_t tile_slices(const pd_ctx* ctx)
+{
+    int64_t nsl = 0;
+    for (const Inst& I : ctx->inst) {
+        if (!I.laws.empty()) return 1;
+        nsl += (I.n + kWave - 1) / kWave;
+    }
+    return nsl >= 3072 ? kTileSlices : nsl >= 512 ? 2 : 1;
+}
+
+// A new layout with the state kept, break steps and the acceleration's validity included.
+void relayout(pd_ctx* ctx)
+{
+    HostState S = snapshot(ctx);
+    for (const Inst& I : ctx->inst) S.bstep.push_back(bstep_of(ctx, I));
+    const bool av = ctx->a_valid;
+    build_layout(ctx, &S);
+    for (size_t ii = 0; ii < ctx->inst.size(); ++ii) upload_bstep(ctx, ctx->inst[ii], S.bstep[ii].data());
+    ctx->a_valid = av;
+}
+
+// After a change of what the kernels stage: a phase that no longer fits is cut anew.
+void fit_stage(pd_ctx* ctx)
+{
+    if (!ctx->built || ctx->mapping != PD_MAP_STAGED) return;
+    const StageRoom r = stage_room(ctx);
+    if ((r.two < ctx->stage_two && ctx->stage_max > r.two) || tile_slices(ctx) != ctx->stage_slices) relayout(ctx);
 }
 
 // Allocate and fill the device problem for ctx->lanes from the instances' user data.
 void build_layout(pd_ctx* ctx, const HostState* S)
 {
-    const int G = ctx->mapping == PD_MAP_STAGED ? 1 : ctx->lanes, W = kWave / G;
+    const bool staged = ctx->mapping == PD_MAP_STAGED;
+    const int G = staged ? 1 : ctx->lanes, W = kWave / G;
     ctx->drop_graphs();
     ctx->tape_valid = false;
     ctx->ck.release();
     ctx->kslot.release();  // slot layout changes: re-uploaded in full below
     int64_t nn = 0, nsl = 0, ns = 0;
     std::vector<int64_t> sp;
-    std::vector<int32_t> sT, sI, spc;
-    std::vector<int2> pcs;
+    std::vector<int32_t> sT, sI, list;
+    std::vector<TileRec> tiles;
+    std::vector<int2> phases, segs;
+    std::vector<int64_t> tile_rows;
+    int64_t stage_max = 0;
+    const StageRoom room = stage_room(ctx);
+    const int64_t group = tile_slices(ctx);
+    ctx->stage_two = room.two;
+    ctx->stage_slices = group;
     for (size_t ii = 0; ii < ctx->inst.size(); ++ii) {
         Inst& I = ctx->inst[ii];
         const double h = spacing_estimate(I);
-        node_order(I, ctx->order, h);
+        std::vector<uint8_t> bank;
+        if (staged)
+            slice_nodes(I, group, h, bank);
+        else
+            node_order(I, ctx->order, h);
         I.n_pad = (I.n + W - 1) / W * W;
         I.perm.resize(static_cast<size_t>(I.n_pad), -1);
         I.node_off = nn;
@@ -311,9 +572,24 @@ void build_layout(pd_ctx* ctx, const HostState* S)
         std::vector<int64_t> start(static_cast<size_t>(I.nslices));
         int64_t nds = 0;
         if (ctx->mapping == PD_MAP_STAGED) {
-            nds = build_staged(I, start);
-            for (int64_t s = 0; s < I.nslices; ++s) spc.push_back(static_cast<int32_t>(pcs.size()) + I.slice_piece[s]);
-            pcs.insert(pcs.end(), I.pieces.begin(), I.pieces.end());
+            nds = build_staged(I, group, room, bank);
+            if (ns + nds >= std::numeric_limits<int32_t>::max())
+                fail(PD_ERANGE, "device problem needs 2^31 or more nodes or slots");
+            for (TileRec t : I.tiles) {
+                t.slice += static_cast<int>(nsl);
+                t.phase += static_cast<int>(phases.size());
+                t.list += static_cast<int>(list.size());
+                t.seg += static_cast<int>(segs.size());
+                t.inst = static_cast<int>(ii);
+                tiles.push_back(t);
+            }
+            for (int2 g : I.segs) segs.push_back(int2{g.x + static_cast<int>(ns / (2 * kWave)), g.y});
+            for (int2 p : I.phases) {
+                phases.push_back(int2{p.x + static_cast<int>(list.size()), p.y});
+                stage_max = std::max<int64_t>(stage_max, p.y);
+            }
+            list.insert(list.end(), I.list.begin(), I.list.end());
+            tile_rows.insert(tile_rows.end(), I.tile_rows.begin(), I.tile_rows.end());
         } else {
             const std::vector<int32_t> ranks = slot_ranks(I, h);
             // slice row counts
@@ -382,13 +658,15 @@ void build_layout(pd_ctx* ctx, const HostState* S)
     ctx->slice_ptr.alloc(sp.size() * sizeof(int64_t));
     ctx->slice_T.alloc(sT.size() * sizeof(int32_t));
     ctx->slice_inst.alloc(sI.size() * sizeof(int32_t));
-    if (ctx->mapping == PD_MAP_STAGED) {
-        spc.push_back(static_cast<int32_t>(pcs.size()));
-        ctx->pieces.alloc(std::max<size_t>(pcs.size(), 1) * sizeof(int2));
-        ctx->slice_piece.alloc(spc.size() * sizeof(int32_t));
+    ctx->ntiles = static_cast<int64_t>(tiles.size());
+    ctx->stage_max = stage_max;
+    if (staged) {
+        ctx->tiles.alloc(tiles.size() * sizeof(TileRec));
+        ctx->phases.alloc(phases.size() * sizeof(int2));
+        ctx->segs.alloc(segs.size() * sizeof(int2));
+        ctx->list.alloc(list.size() * sizeof(int32_t));
     } else {
-        ctx->pieces.release();
-        ctx->slice_piece.release();
+        for (DevBuf* d : {&ctx->tiles, &ctx->phases, &ctx->segs, &ctx->list}) d->release();
     }
     ctx->params.alloc(ctx->inst.size() * sizeof(InstParams));
     ctx->bc_id.alloc(static_cast<size_t>(nn) * sizeof(int32_t));
@@ -408,13 +686,13 @@ void build_layout(pd_ctx* ctx, const HostState* S)
     upload(ctx->slice_T, sT.data(), sT.size() * sizeof(int32_t), 0, ctx->stream);
     upload(ctx->slice_inst, sI.data(), sI.size() * sizeof(int32_t), 0, ctx->stream);
     if (ctx->mapping == PD_MAP_STAGED) {
-        upload(ctx->pieces, pcs.data(), pcs.size() * sizeof(int2), 0, ctx->stream);
-        upload(ctx->slice_piece, spc.data(), spc.size() * sizeof(int32_t), 0, ctx->stream);
-        const std::vector<int32_t> order = slice_dispatch_order(spc, pcs);
-        ctx->slice_order.alloc(order.size() * sizeof(int32_t));
-        upload(ctx->slice_order, order.data(), order.size() * sizeof(int32_t), 0, ctx->stream);
-    } else {
-        ctx->slice_order.release();
+        std::vector<TileRec> sorted;
+        sorted.reserve(tiles.size());
+        for (int32_t t : tile_dispatch_order(tile_rows)) sorted.push_back(tiles[t]);
+        upload(ctx->tiles, sorted.data(), sorted.size() * sizeof(TileRec), 0, ctx->stream);
+        upload(ctx->phases, phases.data(), phases.size() * sizeof(int2), 0, ctx->stream);
+        upload(ctx->segs, segs.data(), segs.size() * sizeof(int2), 0, ctx->stream);
+        upload(ctx->list, list.data(), list.size() * sizeof(int32_t), 0, ctx->stream);
     }
     const int64_t st = ctx->step;
     upload(ctx->step_base, &st, sizeof st, 0, ctx->stream);
@@ -535,6 +813,7 @@ void new_problem(pd_ctx* ctx, int32_t ninst, const int64_t* n, const double* con
     ctx->has_nofail = false;
     ctx->has_laws = false;
     ctx->has_osb = false;
+    ctx->adjoint = false;
     ctx->step = 0;
     ctx->a_valid = false;
     ctx->vv_ahead = false;

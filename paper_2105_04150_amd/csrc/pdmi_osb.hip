@@ -8,101 +8,153 @@
 //   pass 1 (osb_staged<0, ...>): every slot forms its stretch; a slot at or over the
 //     critical stretch breaks (outside no-failure zones, not in a force evaluation); the
 //     node sums |xi| e V over its intact bonds into the dilation theta_i = 3 V / m_i sum and
-//     writes the node pair {theta_i / m_i, 1 / m_i}.
+//     writes the node pair {a_i, b_i - a_i}, a = (3K - 5G) theta / m, b = 15 G / m (a force
+//     evaluation for the dilation readout: theta alone).
 //   pass 2 (osb_staged<1, ...>): every intact slot adds
 //       (t_ij + t_ji) y / |y| V,   t_ij + t_ji = |xi| [(3K - 5G)(A_i + A_j) + 15 G s (B_i + B_j)]
 //     with A = theta / m, B = 1 / m, s = e / |xi| the stretch, then the node integrates
 //     (the same tail as the bond-based step kernels).
 //
-// Both passes use the staged mapping of the bond-based kernels: a slice of 64 nodes, one
-// lane per node, the node records of each piece's range and its slot entries copied
-// straight into LDS; pass 2 copies the range's node pairs beside them.  Influence function
-// 1; a uniform node volume per instance, or per-node volumes copied into LDS beside the
-// records (V_j enters the dilation sum and the force term).  FP64, or the FP32 build: bond arithmetic in
-// single precision from the f32 displacements of the records and the f64 coordinates, the
-// node pairs and the integration (f64 master displacement) as in FP64.
+// Both passes use the tiles of the bond-based step (pdmi_tile.h): a slice of 64 nodes, one
+// lane a node, the records that the tile's bonds reach in LDS; pass 2 copies the node pairs
+// beside them.  Influence function 1; a uniform node volume per instance, or per-node
+// volumes copied into LDS beside the records (V_j enters the dilation sum and the force
+// term).  FP64, or the FP32 build: bond arithmetic in single precision from the f32
+// displacements of the records and the f64 coordinates, the node pairs and the integration
+// (f64 master displacement) as in FP64.
 //
-// Per slot: xi, eta and q = (|y|^2 - |xi|^2)/|xi|^2 as in the bond-based kernels.  The
-// dilation pass needs the stretch s = sqrt(1+q) - 1, the force pass g = 1 - (1+q)^(-1/2)
-// = |y| - |xi| over |y|: with |xi| / |y| = 1 - g and s (1 - g) = g the force term is
-//   (t_ij + t_ji) V y / |y| = V [(3K - 5G)(A_i + A_j)(1 - g) + 15 G (B_i + B_j) g] y,
-// the |xi| of the scalar state cancelling the 1 / |xi| of y / |y|.  Both s and g come
-// from their binomial series for small |q| (no division, no cancellation).
+// Per slot, with S = |y|^2 + |xi|^2, tq = |y|^2 - |xi|^2 and d = tq / S (as in the bond-based
+// kernels; z = d^2):
+//   pass 1: |xi| e = |xi| (|y| - |xi|) = (tq / 2) [1 - d (1/2 + z/8 + z^2/16 + ...)];
+//   pass 2: g = 1 - |xi|/|y| = d [1 - d/2 + d^2/2 - 3d^3/8 + 3d^4/8 - 5d^5/16 + ...], and with
+//     (s / (1 + s)) = g the force term is
+//     (t_ij + t_ji) V y / |y| = V [(a_i + a_j) + g ((b_i - a_i) + (b_j - a_j))] y,
+//     the |xi| of the scalar state cancelling the 1 / |xi| of y / |y|.
+// A share of rows goes by short series (|d| < kMidRange, FP32 build kMidRange32) up to the
+// first block with a slot beyond them or at the decision edge, then by longer ones, and a
+// block with slots beyond those too slot by slot.
 #include "pdmi_step.h"
 
 namespace pdmi {
 namespace {
 
-// sqrt(1+q) - 1.  Series q/2 - q^2/8 + q^3/16 - 5q^4/128 + 7q^5/256 - 21q^6/1024; the first
-// omitted term, 33q^7/2048, is below 2e-16 of the sum for |q| < 4e-3.  Larger |q| takes
-// q / (1 + sqrt(1+q)), which has no cancellation.
-__device__ __forceinline__ double sqrt1p_minus1(double q)
+// sqrt(1+q) - 1 without cancellation, any q.
+template <typename Real>
+__device__ __forceinline__ Real sqrt1p_minus1(Real q)
 {
-    if (fabs(q) < 4.0e-3) {
-        double p = __builtin_fma(-21.0 / 1024.0, q, 7.0 / 256.0);
-        p = __builtin_fma(p, q, -5.0 / 128.0);
-        p = __builtin_fma(p, q, 1.0 / 16.0);
-        p = __builtin_fma(p, q, -1.0 / 8.0);
-        p = __builtin_fma(p, q, 0.5);
-        return q * p;
+    if constexpr (std::is_same_v<Real, float>) {
+        return q * __builtin_amdgcn_rcpf(1.0f + __builtin_sqrtf(1.0f + q));
+    } else {
+        const double r = rsq64<2>(1.0 + q);
+        return q * rcp64(__builtin_fma(1.0 + q, r, 1.0));
     }
-    const double r = rsq64<2>(1.0 + q);
-    return q * rcp64(__builtin_fma(1.0 + q, r, 1.0));
 }
 
-// The FP32 build's sqrt(1+q) - 1: series q/2 - q^2/8 + q^3/16 - 5q^4/128 (the next term is
-// below 2e-11 of the sum for |q| < 4e-3), else q / (1 + sqrt(1+q)).
-__device__ __forceinline__ float sqrt1p_minus1_f32(float q)
+// One slot: its bond vectors and d.
+template <typename Real>
+struct OsbTerm {
+    Real y0, y1, y2, L2, tq, d;
+};
+
+__device__ __forceinline__ OsbTerm<double> osb_term(const NodeRec& n, double X0, double X1, double X2, double U0, double U1,
+                                                    double U2)
 {
-    if (fabsf(q) < 4.0e-3f) {
-        float p = __builtin_fmaf(-5.0f / 128.0f, q, 1.0f / 16.0f);
-        p = __builtin_fmaf(p, q, -1.0f / 8.0f);
-        p = __builtin_fmaf(p, q, 0.5f);
-        return q * p;
-    }
-    return q * __builtin_amdgcn_rcpf(1.0f + __builtin_sqrtf(1.0f + q));
+    const double xi0 = n.p0.x - X0, xi1 = n.p0.y - X1, xi2 = n.p1.x - X2;
+    const double e0 = n.p1.y - U0, e1 = n.p2.x - U1, e2 = n.p2.y - U2;
+    OsbTerm<double> m;
+    m.y0 = xi0 + e0;
+    m.y1 = xi1 + e1;
+    m.y2 = xi2 + e2;
+    m.L2 = __builtin_fma(xi2, xi2, __builtin_fma(xi1, xi1, xi0 * xi0));
+    const double Y2 = __builtin_fma(m.y2, m.y2, __builtin_fma(m.y1, m.y1, m.y0 * m.y0));
+    m.tq = Y2 - m.L2;
+    const double S = Y2 + m.L2;
+    const double r = __builtin_amdgcn_rcp(S);
+    const double d = m.tq * r;
+    m.d = __builtin_fma(d, __builtin_fma(-S, r, 1.0), d);
+    return m;
 }
 
-// The FP32 build's 1 - (1+q)^(-1/2): four series terms, else the closed form.
-__device__ __forceinline__ float one_minus_rsqrt1p_f32(float q)
+__device__ __forceinline__ OsbTerm<float> osb_term32(const NodeRec& n, double X0, double X1, double X2, float U0, float U1,
+                                                     float U2)
 {
-    if (fabsf(q) < 4.0e-3f) {
-        float p = __builtin_fmaf(-35.0f / 128.0f, q, 5.0f / 16.0f);
-        p = __builtin_fmaf(p, q, -3.0f / 8.0f);
-        p = __builtin_fmaf(p, q, 0.5f);
-        return q * p;
-    }
-    return 1.0f - __builtin_amdgcn_rsqf(1.0f + q);
+    const float xi0 = static_cast<float>(n.p0.x - X0), xi1 = static_cast<float>(n.p0.y - X1),
+                xi2 = static_cast<float>(n.p1.x - X2);
+    const uint64_t b1 = __double_as_longlong(n.p1.y), b2 = __double_as_longlong(n.p2.x);
+    const float e0 = __uint_as_float(static_cast<uint32_t>(b1)) - U0, e1 = __uint_as_float(static_cast<uint32_t>(b1 >> 32)) - U1,
+                e2 = __uint_as_float(static_cast<uint32_t>(b2)) - U2;
+    OsbTerm<float> m;
+    m.y0 = xi0 + e0;
+    m.y1 = xi1 + e1;
+    m.y2 = xi2 + e2;
+    const float z0 = xi0 + m.y0, z1 = xi1 + m.y1, z2 = xi2 + m.y2;
+    m.tq = __builtin_fmaf(e2, z2, __builtin_fmaf(e1, z1, e0 * z0));
+    m.L2 = __builtin_fmaf(xi2, xi2, __builtin_fmaf(xi1, xi1, xi0 * xi0));
+    m.d = m.tq * __builtin_amdgcn_rcpf(__builtin_fmaf(2.0f, m.L2, m.tq));
+    return m;
 }
 
-template <bool FP32, int PASS, int MODE, int S, bool VOLN>
-__global__ __launch_bounds__(kWave * S) void osb_staged(StepArgs A, const int2* __restrict__ pieces,
-                                                        const int32_t* __restrict__ slice_piece,
-                                                        const int64_t* __restrict__ slice_ptr)
+// 2 |xi| e / tq = 1 - (1 - sqrt(1 - d^2)) / d and g = d P - (P - 1), P = (1 - d^2)^(-1/2), by their
+// series (WIDE: to kWideRange).
+template <bool WIDE, typename Real>
+__device__ __forceinline__ Real osb_extension(Real d)
 {
-    constexpr int kRecChunks = kStageChunks + 3;             // staged records, then the sentinel
-    constexpr int kEntChunks = kPieceRows * kWave * 2 / 16;  // 16-byte chunks of entries
-    constexpr int kPairChunks = PASS == 1 ? 2 * kWave : 0;   // node pairs of the range (pass 2)
-    constexpr int kVolChunks = VOLN ? 3 * kWave * 4 / 16 : 0;    // node volumes of the range (3 x 64 dwords)
-    constexpr int kLds = kRecChunks + kEntChunks + kPairChunks + kVolChunks;
-    static_assert(!VOLN || kEntPad / 48 < 3 * kWave / 2, "the sentinel's volume index lies in the copy");
-    constexpr int kRed = PASS == 1 ? 3 : 1;
-    static_assert(kEntPad / 48 < kPairChunks || PASS == 0, "the sentinel's pair index lies in the copy");
-    __shared__ double2 lds[S * kLds];
-    __shared__ double red[S > 1 ? (S - 1) * kRed * kWave : 1];
-    const int wv = S > 1 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave) : 0;
-    double2* const lrec = lds + wv * kLds;
-    const char* const lrecb = reinterpret_cast<const char*>(lrec);
-    uint16_t* const lent = reinterpret_cast<uint16_t*>(lrec + kRecChunks);
-    double2* const lpair = lrec + kRecChunks + kEntChunks;
-    double* const lvol = reinterpret_cast<double*>(lrec + kRecChunks + kEntChunks + kPairChunks);
+    const Real z = d * d;
+    Real p = Real(1.0 / 8.0);
+    if constexpr (WIDE) {
+        p = __builtin_elementwise_fma(Real(7.0 / 256.0), z, Real(5.0 / 128.0));
+        p = __builtin_elementwise_fma(p, z, Real(1.0 / 16.0));
+        p = __builtin_elementwise_fma(p, z, Real(1.0 / 8.0));
+    } else if constexpr (!std::is_same_v<Real, float>) {
+        p = __builtin_fma(1.0 / 16.0, z, p);
+    }
+    p = __builtin_elementwise_fma(p, z, Real(0.5));
+    return __builtin_elementwise_fma(-d, p, Real(1));
+}
+template <bool WIDE, typename Real>
+__device__ __forceinline__ Real osb_g(Real d)
+{
+    Real p;
+    if constexpr (WIDE) {
+        const Real z = d * d;
+        p = __builtin_elementwise_fma(Real(63.0 / 256.0), z, Real(35.0 / 128.0));
+        p = __builtin_elementwise_fma(p, z, Real(5.0 / 16.0));
+        p = __builtin_elementwise_fma(p, z, Real(3.0 / 8.0));
+        p = __builtin_elementwise_fma(p, z, Real(0.5));
+        p *= z;  // P - 1
+        return __builtin_elementwise_fma(d, p, d - p);
+    } else if constexpr (std::is_same_v<Real, float>) {
+        p = __builtin_fmaf(-3.0f / 8.0f, d, 0.5f);
+    } else {
+        p = __builtin_fma(-5.0 / 16.0, d, 3.0 / 8.0);
+        p = __builtin_fma(p, d, -3.0 / 8.0);
+        p = __builtin_fma(p, d, 0.5);
+    }
+    p = __builtin_elementwise_fma(p, d, Real(-0.5));
+    p = __builtin_elementwise_fma(p, d, Real(1));
+    return d * p;
+}
 
-    const int lane = threadIdx.x & (kWave - 1);
-    int64_t slice = wave_uniform(xcd_remap(blockIdx.x, gridDim.x));
-    if (slice >= A.nslices) return;
-    if (A.slice_order) slice = __builtin_amdgcn_readfirstlane(A.slice_order[slice]);  // long slices first
-    const InstParams P = A.params[A.slice_inst[slice]];
-    const int64_t node = slice * kWave + lane;
+template <bool FP32, int PASS, int MODE, bool VOLN>
+__global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, const TileRec* __restrict__ tiles,
+                                                                    const int2* __restrict__ phases,
+                                                                    const int2* __restrict__ segs,
+                                                                    const int32_t* __restrict__ list)
+{
+    using Real = std::conditional_t<FP32, float, double>;
+    extern __shared__ double2 lds[];
+    constexpr int B = kPairsAhead;
+    constexpr bool BREAKS = PASS == 0 && MODE != kModeForce;
+    __builtin_amdgcn_s_setprio(3);  // a tile's staging before another's rows
+    const TileRec T = tiles[wave_uniform(xcd_remap(blockIdx.x, gridDim.x))];
+    const TileLane tl(T);
+    const int lane = tl.lane;
+    double2* const lrec = lds;
+    double2* const lpair = lrec + 3 * (A.stage_max + 1);  // pass 2: node pairs
+    double* const lvol = reinterpret_cast<double*>(lpair + (PASS == 1 ? A.stage_max + 1 : 0));
+    if (T.nphases > 0) stage_records(A.rec_in, list + T.list, T.n, tl.wv, lane, lrec);
+    const InstParams& P = A.params[T.inst];
+    const int64_t node = tl.node(T);
     const double2* __restrict__ rin = reinterpret_cast<const double2*>(A.rec_in);
     const double2 o0 = rin[3 * node], o1 = rin[3 * node + 1], o2 = rin[3 * node + 2];
     const double X0 = o0.x, X1 = o0.y, X2 = o1.x;
@@ -110,259 +162,271 @@ __global__ __launch_bounds__(kWave * S) void osb_staged(StepArgs A, const int2* 
     const uint64_t ub1 = __double_as_longlong(o1.y), ub2 = __double_as_longlong(o2.x);
     const float Uf0 = __uint_as_float(static_cast<uint32_t>(ub1)), Uf1 = __uint_as_float(static_cast<uint32_t>(ub1 >> 32)),
                 Uf2 = __uint_as_float(static_cast<uint32_t>(ub2));  // FP32 build
-    const double2* __restrict__ ent2 = reinterpret_cast<const double2*>(A.ent);
-    uint16_t* __restrict__ entw = A.ent;
-    const SeriesCoef sk = series_coef_regs();
-    double2 own = {0.0, 0.0};
-    if (PASS == 1) own = A.osb[node];
-    const double Ai = own.x, Bi = own.y;
-    const double ka = P.osb_a, kb = P.osb_b;
-    const float Aif = static_cast<float>(Ai), Bif = static_cast<float>(Bi), kaf = static_cast<float>(ka),
-                kbf = static_cast<float>(kb), q0f = static_cast<float>(P.q0);
-
-    // sentinel record (padding entries point at it)
-    if (lane < 3) lrec[kStageChunks + lane] = lane == 0 ? double2{1e10, 1e10} : lane == 1 ? double2{1e10, 0.0} : double2{0.0, 0.0};
-
-    const int p0 = __builtin_amdgcn_readfirstlane(slice_piece[slice]);
-    const int p1 = __builtin_amdgcn_readfirstlane(slice_piece[slice + 1]);
-    auto rows_of = [&](int p) { return (pieces[__builtin_amdgcn_readfirstlane(p)].y >> 8) & 0xff; };
-    int64_t ent = wave_uniform(slice_ptr[slice]);
-    const int pa = p0 + wv;
-    for (int q = p0; q < pa && q < p1; ++q) ent += static_cast<int64_t>(rows_of(q)) * kWave;
-
-    typedef __attribute__((address_space(3))) void* lds_ptr;
-    auto dma = [&](int p, int64_t e) {
-        const int2 m = pieces[__builtin_amdgcn_readfirstlane(p)];
-        const double2* rs = rin + 3 * static_cast<int64_t>(m.x) + lane;
-        // one address and one LDS base for the four 1 KB chunks: the instruction's immediate
-        // offset advances the global and the LDS address alike
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 16 * kWave, 0);
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 2 * 16 * kWave, 0);
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 3 * 16 * kWave, 0);
-        __builtin_amdgcn_global_load_lds(ent2 + e / 8 + lane, (lds_ptr)(lent), 16, 0, 0);
-        if (PASS == 1) {  // the pair buffer ends with 2 x 64 spare pairs
-            const double2* ps = A.osb + m.x + lane;
-            __builtin_amdgcn_global_load_lds(ps, (lds_ptr)(lpair), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds(ps, (lds_ptr)(lpair), 16, 16 * kWave, 0);
-        }
-        if (VOLN) {  // per-node volumes: the volume buffer ends with spare entries
-            const float* ws = reinterpret_cast<const float*>(A.vol + m.x) + lane;
-            float* wl = reinterpret_cast<float*>(lvol);
-            __builtin_amdgcn_global_load_lds(ws, (lds_ptr)(wl), 4, 0, 0);
-            __builtin_amdgcn_global_load_lds(ws + kWave, (lds_ptr)(wl + kWave), 4, 0, 0);
-            __builtin_amdgcn_global_load_lds(ws + 2 * kWave, (lds_ptr)(wl + 2 * kWave), 4, 0, 0);
-        }
+    const uint32_t* __restrict__ ent = reinterpret_cast<const uint32_t*>(A.ent) + lane;
+    const double2* __restrict__ pairs_in = A.osb;
+    const double2 own = PASS == 1 ? pairs_in[node] : double2{0.0, 0.0};
+    const Real Pa = static_cast<Real>(own.x), Pd = static_cast<Real>(own.y);
+    const float q0f = static_cast<float>(P.q0);
+    auto bits = [](double range, double range32) {
+        return static_cast<int32_t>(FP32 ? __float_as_uint(static_cast<float>(range32)) : __double_as_longlong(range) >> 32);
     };
+    const int32_t hi_range = bits(kMidRange, kMidRange32), hi_wrange = bits(kWideRange, kWideRange32);
+    const int32_t hi_pos = BREAKS ? (FP32 ? P.hi_pos32 : P.hi_pos) : hi_range;
+    const int32_t hi_wpos = BREAKS ? (FP32 ? P.hi_wpos32 : P.hi_wpos) : hi_wrange;
+    const uint32_t hi_neg = 0x80000000u | static_cast<uint32_t>(hi_range), hi_wneg = 0x80000000u | static_cast<uint32_t>(hi_wrange);
 
-    double D = 0.0;                    // pass 1: sum of |xi|^2 s (V_j) over intact bonds
-    double F0 = 0.0, F1 = 0.0, F2 = 0.0;  // pass 2: force density (uniform volume: without the factor V)
-    float Df = 0.0f, Ff0 = 0.0f, Ff1 = 0.0f, Ff2 = 0.0f;  // the same in the FP32 build
-    constexpr bool BREAK = PASS == 0 && MODE != kModeForce;
-    const int32_t step = static_cast<int32_t>(*A.step_base + A.step_local);
+    // sentinel record, its pair and volume zero
+    if (threadIdx.x < 3) lrec[threadIdx.x] = sentinel_part<FP32>(threadIdx.x);
+    if (PASS == 1 && threadIdx.x == 0) lpair[0] = double2{0.0, 0.0};
+    if (VOLN && threadIdx.x == 0) lvol[0] = 0.0;
 
-    // FP32 build: one slot in single precision (the bond vector formed in f64 and rounded
-    // once, the displacements those of the f32 records)
-    auto slot32 = [&](uint16_t e, int64_t ds) {
-        const bool live = !(e & kEntBroken);
-        const uint32_t off = e & kEntOff;
-        const double2 r0 = *reinterpret_cast<const double2*>(lrecb + off);
-        const double2 r1 = *reinterpret_cast<const double2*>(lrecb + off + 16);
-        const double2 r2 = *reinterpret_cast<const double2*>(lrecb + off + 32);
-        const float xi0 = static_cast<float>(r0.x - X0), xi1 = static_cast<float>(r0.y - X1),
-                    xi2 = static_cast<float>(r1.x - X2);
-        const uint64_t b1 = __double_as_longlong(r1.y), b2 = __double_as_longlong(r2.x);
-        const float e0 = __uint_as_float(static_cast<uint32_t>(b1)) - Uf0,
-                    e1 = __uint_as_float(static_cast<uint32_t>(b1 >> 32)) - Uf1,
-                    e2 = __uint_as_float(static_cast<uint32_t>(b2)) - Uf2;
-        const float y0 = xi0 + e0, y1 = xi1 + e1, y2 = xi2 + e2;
-        const float z0 = xi0 + y0, z1 = xi1 + y1, z2 = xi2 + y2;
-        const float tq = __builtin_fmaf(e2, z2, __builtin_fmaf(e1, z1, e0 * z0));
-        const float L2 = __builtin_fmaf(xi2, xi2, __builtin_fmaf(xi1, xi1, xi0 * xi0));
-        const float q = tq * __builtin_amdgcn_rcpf(L2);
-        const bool brk = BREAK && live && !(e & kEntNoFail) && q >= q0f;
-        const bool alive = live && !brk;
-        const float vj = VOLN ? static_cast<float>(lvol[(off * 0xAAABu) >> 21]) : 1.0f;
+    Real D = 0;                  // pass 1: sum of 2 |xi| e (V_j) over intact bonds
+    Real F0 = 0, F1 = 0, F2 = 0;  // pass 2: force density (uniform volume: without the factor V)
+    auto term = [&](const NodeRec& r) {
+        if constexpr (FP32)
+            return osb_term32(r, X0, X1, X2, Uf0, Uf1, Uf2);
+        else
+            return osb_term(r, X0, X1, X2, U0, U1, U2);
+    };
+    // adds the term of a slot: v = 2 |xi| e in pass 1, g in pass 2
+    auto add = [&](const OsbTerm<Real>& m, uint32_t idx, Real v) {
+        const Real vj = VOLN ? static_cast<Real>(lvol[idx]) : Real(1);
         if (PASS == 0) {
-            Df = __builtin_fmaf(VOLN ? L2 * vj : L2, sqrt1p_minus1_f32(alive ? q : 0.0f), Df);
-            if (brk) {
-                entw[ds] = static_cast<uint16_t>(e | kEntBroken);
-                A.bstep[ds] = step;
-            }
+            D = VOLN ? __builtin_elementwise_fma(vj, v, D) : D + v;
         } else {
-            const float g = one_minus_rsqrt1p_f32(alive ? q : 0.0f);
-            const double2 pj = lpair[(off * 0xAAABu) >> 21];
-            const float a = kaf * (Aif + static_cast<float>(pj.x)), b = kbf * (Bif + static_cast<float>(pj.y));
-            const float c = alive ? __builtin_fmaf(g, b - a, a) : 0.0f;
-            const float coef = VOLN ? c * vj : c;
-            Ff0 = __builtin_fmaf(coef, y0, Ff0);
-            Ff1 = __builtin_fmaf(coef, y1, Ff1);
-            Ff2 = __builtin_fmaf(coef, y2, Ff2);
+            const double2 pj = lpair[idx];
+            Real c = __builtin_elementwise_fma(v, Pd + static_cast<Real>(pj.y), Pa + static_cast<Real>(pj.x));
+            c = idx != 0 ? c : Real(0);  // padding and broken slots
+            const Real coef = VOLN ? vj * c : c;
+            F0 = __builtin_elementwise_fma(coef, m.y0, F0);
+            F1 = __builtin_elementwise_fma(coef, m.y1, F1);
+            F2 = __builtin_elementwise_fma(coef, m.y2, F2);
         }
     };
-
-    auto slot = [&](uint16_t e, int64_t ds) {
-        if constexpr (FP32) {
-            slot32(e, ds);
-            return;
-        }
-        const bool live = !(e & kEntBroken);
-        const uint32_t off = e & kEntOff;
-        const double2 r0 = *reinterpret_cast<const double2*>(lrecb + off);
-        const double2 r1 = *reinterpret_cast<const double2*>(lrecb + off + 16);
-        const double2 r2 = *reinterpret_cast<const double2*>(lrecb + off + 32);
-        const double xi0 = r0.x - X0, xi1 = r0.y - X1, xi2 = r1.x - X2;
-        const double e0 = r1.y - U0, e1 = r2.x - U1, e2 = r2.y - U2;
-        const double y0 = xi0 + e0, y1 = xi1 + e1, y2 = xi2 + e2;
-        // |y|^2 - |xi|^2 from two sums in the same order (exactly zero for an unstretched
-        // bond), as the bond-based kernels form it
-        const double L2 = __builtin_fma(xi2, xi2, __builtin_fma(xi1, xi1, xi0 * xi0));
-        const double tq = __builtin_fma(y2, y2, __builtin_fma(y1, y1, y0 * y0)) - L2;
-        const double q = tq * rcp64_1(L2);  // neither pass needs 1/|xi| itself
-        // a break candidate: q at or above the lower edge of the decision (the rare branch
-        // below decides, on the exact stretch within the margin)
-        const bool cand = BREAK && live && !(e & kEntNoFail) && q >= P.q0;
-        const bool alive = live && !cand;
-        const double vj = VOLN ? lvol[(off * 0xAAABu) >> 21] : 1.0;
-        if (PASS == 0) {
-            const double s = sqrt1p_minus1(alive ? q : 0.0);
-            D = __builtin_fma(VOLN ? L2 * vj : L2, s, D);  // |xi| e = |xi|^2 s; 0 for broken and padding slots
-            if (cand) {
-                if (stretch_exact(xi0, xi1, xi2, y0, y1, y2) >= P.s0) {
-                    entw[ds] = static_cast<uint16_t>(e | kEntBroken);
-                    A.bstep[ds] = step;
-                } else {  // holds: the term the common path left out
-                    D = __builtin_fma(VOLN ? L2 * vj : L2, sqrt1p_minus1(q), D);
+    auto series = [&](const OsbTerm<Real>& m, auto wide) {
+        return PASS == 0 ? m.tq * osb_extension<decltype(wide)::value>(m.d) : osb_g<decltype(wide)::value>(m.d);
+    };
+    auto high = [&](const OsbTerm<Real>& m) {
+        if constexpr (FP32)
+            return static_cast<int32_t>(__float_as_uint(m.d));
+        else
+            return static_cast<int32_t>(__double_as_longlong(m.d) >> 32);
+    };
+    auto one = [&](const NodeRec& r, uint32_t idx, auto wide) {
+        const OsbTerm<Real> m = term(r);
+        add(m, idx, series(m, wide));
+        return high(m);
+    };
+    auto ent_at = [&](int t) { return ent[static_cast<int64_t>(t) * kWave]; };
+    // The pairs [t, end), with a look at every slot at the decision edge or beyond the long
+    // series (force: at all).
+    auto rows_apart = [&](int t, int end, bool force) {
+        uint32_t e2 = ent_at(t), en = t + 1 < end ? ent_at(t + 1) : 0x80008000u;
+        NodeRec r = staged_record(lrec, live_indices<true>(e2) & 0xffffu);
+        int h = 0;
+#pragma unroll 1
+        while (t < end) {
+            const uint32_t e = h ? e2 >> 16 : e2 & 0xffffu;
+            const NodeRec rn = staged_record(lrec, h ? live_indices<true>(en) & 0xffffu : live_indices<true>(e2) >> 16);
+            const OsbTerm<Real> m = term(r);
+            Real v = series(m, std::true_type{});
+            bool live = !(e & kEntBroken);
+            const int32_t hi = high(m);
+            const bool beyond = live && (hi >= hi_wpos || static_cast<uint32_t>(hi) >= hi_wneg || force);
+            if (__builtin_amdgcn_ballot_w64(beyond) != 0 && beyond) {
+                Real q;
+                if constexpr (FP32)
+                    q = m.tq * __builtin_amdgcn_rcpf(m.L2);
+                else
+                    q = m.tq * rcp64(m.L2);
+                if (BREAKS && !(e & kEntNoFail) && !(q < (FP32 ? static_cast<Real>(q0f) : static_cast<Real>(P.q0)))) {
+                    if (FP32 ? q >= static_cast<Real>(q0f) : stretch_exact_rec(r.p0, r.p1, r.p2, X0, X1, X2, U0, U1, U2) >= P.s0) {
+                        const int64_t ds = static_cast<int64_t>(t) * (2 * kWave) + 2 * lane + h;
+                        A.ent[ds] = static_cast<uint16_t>(e | kEntBroken);
+                        A.bstep[ds] = static_cast<int32_t>(*A.step_base + A.step_local);
+                        live = false;
+                    }
+                }
+                if (PASS == 0) {
+                    v = Real(2) * m.L2 * sqrt1p_minus1(q);
+                } else if constexpr (FP32) {
+                    if (!(fabsf(m.d) < static_cast<float>(kWideRange32)))
+                        v = 1.0f - __builtin_amdgcn_rsqf(1.0f + q);
+                } else {
+                    v = one_minus_rsqrt1p(q, series_coef_sregs());
                 }
             }
-        } else {
-            const double g = one_minus_rsqrt1p(alive ? q : 0.0, sk);
-            const double2 pj = lpair[(off * 0xAAABu) >> 21];  // off / 48: the neighbour's pair
-            const double a = ka * (Ai + pj.x), b = kb * (Bi + pj.y);
-            const double c = alive ? __builtin_fma(g, b - a, a) : 0.0;
-            const double coef = VOLN ? c * vj : c;
-            F0 = __builtin_fma(coef, y0, F0);
-            F1 = __builtin_fma(coef, y1, F1);
-            F2 = __builtin_fma(coef, y2, F2);
+            if (live) add(m, e & kEntIdx, v);
+            r = rn;
+            h ^= 1;
+            if (h == 0) {
+                ++t;
+                e2 = en;
+                en = t + 1 < end ? ent_at(t + 1) : 0x80008000u;
+            }
         }
     };
-
-    for (int p = pa; p < p1; p += S) {
-        const int T = rows_of(p);
-        int64_t ent_next = ent + static_cast<int64_t>(T) * kWave;
-        for (int q = p + 1; q < p + S && q < p1; ++q) ent_next += static_cast<int64_t>(rows_of(q)) * kWave;
-        wave_sync();  // the previous piece is no longer read
-        lds_reads_done();
-        dma(p, ent);
-        // s_waitcnt with vmcnt = 0 (expcnt and lgkmcnt at their no-wait maxima): the
-        // piece's direct-to-LDS loads have landed
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        wave_sync();
+    uint32_t en[B];  // the next block's entries
+    auto fetch = [&](int t) {
 #pragma unroll
-        for (int t = 0; t < kPieceRows; t += 2) {
-            if (t >= T) break;
-            const uint16_t ea = lent[t * kWave + lane];
-            slot(ea, ent + t * kWave + lane);
-            if (t + 1 < T) slot(lent[(t + 1) * kWave + lane], ent + (t + 1) * kWave + lane);
-        }
-        ent = ent_next;
-    }
-
-    if (FP32) {
-        D = Df;
-        F0 = Ff0;
-        F1 = Ff1;
-        F2 = Ff2;
-    }
-    if (S > 1) {  // wavefront 0 adds the partial sums of 1..S-1 in that order
-        if (wv > 0) {
-            double* rr = red + (wv - 1) * kRed * kWave + lane;
-            if (PASS == 0) {
-                rr[0] = D;
-            } else {
-                rr[0] = F0;
-                rr[kWave] = F1;
-                rr[2 * kWave] = F2;
+        for (int u = 0; u < B; ++u) en[u] = ent_at(t + u);
+    };
+    // The pairs [t, end), after fetch(t), block by block by the short or the long series, up to
+    // the first block with a slot that it does not cover; that block is taken back.
+    auto rows = [&](int t, int end, auto wide) {
+        const int32_t pos = wide ? hi_wpos : hi_pos;
+        const uint32_t neg = wide ? hi_wneg : hi_neg;
+#pragma unroll 1
+        for (; t < end; t += B) {
+            uint32_t e[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) e[u] = en[u];
+            fetch(t + B);
+            const Real S = D, S0 = F0, S1 = F1, S2 = F2;
+            int32_t himax = std::numeric_limits<int32_t>::min();
+            uint32_t himin = 0;
+            uint32_t v = live_indices<true>(e[0]);
+            NodeRec ra = staged_record(lrec, v & 0xffffu);
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                if (t + u >= end) break;
+                const uint32_t ia = v & 0xffffu, ib = v >> 16;
+                const NodeRec rb = staged_record(lrec, ib);
+                if (u + 1 < B) v = live_indices<true>(t + u + 1 < end ? e[u + 1] : 0x80008000u);
+                __builtin_amdgcn_sched_barrier(0);
+                const int32_t ha = one(ra, ia, wide);
+                if (u + 1 < B) ra = staged_record(lrec, v & 0xffffu);
+                __builtin_amdgcn_sched_barrier(0);
+                const int32_t hb = one(rb, ib, wide);
+                himax = max(max(himax, ha), hb);
+                himin = max(max(himin, static_cast<uint32_t>(ha)), static_cast<uint32_t>(hb));
+            }
+            if (__builtin_amdgcn_ballot_w64(himax >= pos || himin >= neg) != 0) {
+                D = S;
+                F0 = S0;
+                F1 = S1;
+                F2 = S2;
+                return t;
             }
         }
-        __syncthreads();  // every wavefront of the workgroup reaches this once
-        if (wv > 0) return;
-#pragma unroll
-        for (int w = 1; w < S; ++w) {
-            const double* rr = red + (w - 1) * kRed * kWave + lane;
-            if (PASS == 0) {
-                D += rr[0];
-            } else {
-                F0 += rr[0];
-                F1 += rr[kWave];
-                F2 += rr[2 * kWave];
+        return end;
+    };
+    auto share_rows = [&](int2 pr) {  // after fetch(pr.x)
+        int t = rows(pr.x, pr.y, std::false_type{});
+#pragma unroll 1
+        while (t < pr.y) {  // once the short series does not do, the long one for the rest
+            fetch(t);
+            t = rows(t, pr.y, std::true_type{});
+            if (t >= pr.y) break;
+            rows_apart(t, min(t + B, pr.y), false);
+            t += B;
+        }
+    };
+    auto stage_weights = [&](const int32_t* l, int n) {
+        if (PASS == 1) stage_pairs(pairs_in, l, n, tl.wv, lane, lpair);
+        if (VOLN) stage_doubles(A.vol, l, n, tl.wv, lane, lvol);
+    };
+    auto stage_phase = [&](int ph) {  // a later phase, or one staged again
+        const int2 pd = phases[T.phase + ph];
+        __syncthreads();  // the records before are no longer read
+        stage_records(A.rec_in, list + pd.x, pd.y, tl.wv, lane, lrec);
+        stage_weights(list + pd.x, pd.y);
+    };
+
+    if (T.nphases > 0) stage_weights(list + T.list, T.n);
+    int2 pr = int2{0, 0};
+#pragma unroll 1
+    for (int ph = 0; ph < T.nphases; ++ph) {
+        if (ph > 0) stage_phase(ph);
+        pr = tl.pairs(T, segs, ph);
+        fetch(pr.x);
+        tile_staged();
+        __builtin_amdgcn_s_setprio(0);
+        if (pr.x < pr.y) share_rows(pr);
+        __builtin_amdgcn_s_setprio(3);
+    }
+    // squares beyond the range of their type leave no finite sum: every slot in the general form
+    const bool unsound = !(__builtin_isfinite(D) && __builtin_isfinite(F0) && __builtin_isfinite(F1) && __builtin_isfinite(F2));
+    if (T.nphases <= 1 ? __builtin_amdgcn_ballot_w64(unsound) != 0 : __syncthreads_or(unsound) != 0) {
+        D = F0 = F1 = F2 = 0;
+#pragma unroll 1
+        for (int ph = 0; ph < T.nphases; ++ph) {
+            if (T.nphases > 1) {
+                stage_phase(ph);
+                tile_staged();
             }
+            pr = tl.pairs(T, segs, ph);
+            if (pr.x < pr.y) rows_apart(pr.x, pr.y, true);
         }
     }
-    if (PASS == 0) {
-        // theta_i = 3 V D / m_i (per-node volumes: inside D); padding nodes (1/m = 0) write zeros
+    if constexpr (PASS == 0) {
+        double E[1] = {D};
+        tile_reduce(tl, reinterpret_cast<double*>(lds), E);
+        if (tl.sub > 0 || !tl.has) return;
+        // theta_i = 3 V sum / m_i (per-node volumes: inside the sum); padding nodes (1/m = 0) write zeros
         const double b = A.minv[node];
-        const double theta = VOLN ? 3.0 * D * b : (3.0 * P.volume) * D * b;
-        A.osb[node] = double2{theta * b, b};
-        return;
-    }
-    if (VOLN) {
-        node_update<MODE, FP32>(A, P, node, U0, U1, U2, F0, F1, F2);
+        const double theta = VOLN ? 1.5 * E[0] * b : (1.5 * P.volume) * E[0] * b;
+        const double a = P.osb_a * (theta * b);
+        A.osb[node] = MODE == kModeForce && A.force == nullptr ? double2{theta, 0.0} : double2{a, P.osb_b * b - a};
     } else {
-        const double V = P.volume;
-        node_update<MODE, FP32>(A, P, node, U0, U1, U2, V * F0, V * F1, V * F2);
+        double G[3] = {F0, F1, F2};
+        tile_reduce(tl, reinterpret_cast<double*>(lds), G);
+        if (tl.sub > 0 || !tl.has) return;
+        const double V = VOLN ? 1.0 : P.volume;
+        node_update<MODE, FP32>(A, P, node, U0, U1, U2, V * G[0], V * G[1], V * G[2]);
     }
 }
 
 template <bool FP32, int PASS, int MODE, bool VOLN>
-hipError_t launch_osb_pmv(const StepArgs& a, int split, hipStream_t s)
+hipError_t launch_osb_pmv(const StepArgs& a, hipStream_t s)
 {
-    const dim3 grid(static_cast<unsigned>(a.nslices));
-    switch (split) {
-    case 1: hipLaunchKernelGGL((osb_staged<FP32, PASS, MODE, 1, VOLN>), grid, dim3(kWave), 0, s, a, a.pieces, a.slice_piece, a.slice_ptr); break;
-    case 2: hipLaunchKernelGGL((osb_staged<FP32, PASS, MODE, 2, VOLN>), grid, dim3(2 * kWave), 0, s, a, a.pieces, a.slice_piece, a.slice_ptr); break;
-    case 4: hipLaunchKernelGGL((osb_staged<FP32, PASS, MODE, 4, VOLN>), grid, dim3(4 * kWave), 0, s, a, a.pieces, a.slice_piece, a.slice_ptr); break;
-    default: return hipErrorInvalidValue;
-    }
+    auto* kernel = &osb_staged<FP32, PASS, MODE, VOLN>;
+    const size_t bytes = tile_lds(a.stage_max, 48 + (PASS == 1 ? 16 : 0) + (VOLN ? 8 : 0));
+    const hipError_t e = tile_room(reinterpret_cast<const void*>(kernel), bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.ntiles)), dim3(kTileWaves * kWave), bytes, s, a, a.tiles,
+                       a.phases, a.segs, a.list);
     return hipGetLastError();
 }
 
 template <bool FP32, int PASS, int MODE>
-hipError_t launch_osb_pm(const StepArgs& a, int split, hipStream_t s)
+hipError_t launch_osb_pm(const StepArgs& a, hipStream_t s)
 {
-    return a.vol ? launch_osb_pmv<FP32, PASS, MODE, true>(a, split, s) : launch_osb_pmv<FP32, PASS, MODE, false>(a, split, s);
+    return a.vol ? launch_osb_pmv<FP32, PASS, MODE, true>(a, s) : launch_osb_pmv<FP32, PASS, MODE, false>(a, s);
 }
 
 template <bool FP32>
-hipError_t launch_osb_step_p(const StepArgs& a, int mode, int split, hipStream_t s)
+hipError_t launch_osb_step_p(const StepArgs& a, int mode, hipStream_t s)
 {
-    hipError_t e = mode != kModeForce ? launch_osb_pm<FP32, 0, kModeEC>(a, split, s)
-                                      : launch_osb_pm<FP32, 0, kModeForce>(a, split, s);
+    hipError_t e = mode != kModeForce ? launch_osb_pm<FP32, 0, kModeEC>(a, s)
+                                      : launch_osb_pm<FP32, 0, kModeForce>(a, s);
     if (e != hipSuccess) return e;
     switch (mode) {
-    case kModeEC: return launch_osb_pm<FP32, 1, kModeEC>(a, split, s);
-    case kModeVV: return launch_osb_pm<FP32, 1, kModeVV>(a, split, s);
-    case kModeVVInit: return launch_osb_pm<FP32, 1, kModeVVInit>(a, split, s);
-    case kModeFE: return launch_osb_pm<FP32, 1, kModeFE>(a, split, s);
-    case kModeForce: return launch_osb_pm<FP32, 1, kModeForce>(a, split, s);
+    case kModeEC: return launch_osb_pm<FP32, 1, kModeEC>(a, s);
+    case kModeVV: return launch_osb_pm<FP32, 1, kModeVV>(a, s);
+    case kModeVVInit: return launch_osb_pm<FP32, 1, kModeVVInit>(a, s);
+    case kModeFE: return launch_osb_pm<FP32, 1, kModeFE>(a, s);
+    case kModeForce: return launch_osb_pm<FP32, 1, kModeForce>(a, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 }  // namespace
 
-hipError_t launch_osb_dilation(const StepArgs& a, bool breaking, bool fp32, int split, hipStream_t s)
+hipError_t launch_osb_dilation(const StepArgs& args, bool breaking, bool fp32, hipStream_t s)
 {
-    if (a.nslices <= 0) return hipSuccess;
+    StepArgs a = args;
+    a.force = nullptr;  // the readout: theta itself
+    if (a.ntiles <= 0) return hipSuccess;
     if (fp32)
-        return breaking ? launch_osb_pm<true, 0, kModeEC>(a, split, s) : launch_osb_pm<true, 0, kModeForce>(a, split, s);
-    return breaking ? launch_osb_pm<false, 0, kModeEC>(a, split, s) : launch_osb_pm<false, 0, kModeForce>(a, split, s);
+        return breaking ? launch_osb_pm<true, 0, kModeEC>(a, s) : launch_osb_pm<true, 0, kModeForce>(a, s);
+    return breaking ? launch_osb_pm<false, 0, kModeEC>(a, s) : launch_osb_pm<false, 0, kModeForce>(a, s);
 }
 
-hipError_t launch_osb_step(const StepArgs& a, int mode, bool fp32, int split, hipStream_t s)
+hipError_t launch_osb_step(const StepArgs& a, int mode, bool fp32, hipStream_t s)
 {
-    if (a.nslices <= 0) return hipSuccess;
-    return fp32 ? launch_osb_step_p<true>(a, mode, split, s) : launch_osb_step_p<false>(a, mode, split, s);
+    if (a.ntiles <= 0) return hipSuccess;
+    return fp32 ? launch_osb_step_p<true>(a, mode, s) : launch_osb_step_p<false>(a, mode, s);
 }
 
 }  // namespace pdmi

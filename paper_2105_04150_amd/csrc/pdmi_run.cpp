@@ -29,15 +29,20 @@ StepArgs step_args(pd_ctx* ctx, int in, int out, int64_t step_local)
     A.osb = ctx->has_osb ? ctx->osb.as<double2>() : nullptr;
     A.minv = ctx->has_osb ? ctx->minv.as<double>() : nullptr;
     A.cfv = ctx->corr_k ? ctx->cfv.as<double>() : nullptr;
+    A.partial = false;
+    for (const Inst& I : ctx->inst) A.partial |= I.has_corr && I.corr.partial_volumes;
     A.slice_ptr = ctx->slice_ptr.as<int64_t>();
     A.slice_T = ctx->slice_T.as<int32_t>();
     A.slice_inst = ctx->slice_inst.as<int32_t>();
-    A.slice_order = ctx->slice_order.p ? ctx->slice_order.as<int32_t>() : nullptr;
     A.params = ctx->params.as<InstParams>();
     A.bc_id = ctx->bc_id.as<int32_t>();
     A.bc = ctx->bc.as<BCRec>();
-    A.pieces = ctx->pieces.as<int2>();
-    A.slice_piece = ctx->slice_piece.as<int32_t>();
+    A.tiles = ctx->tiles.as<TileRec>();
+    A.phases = ctx->phases.as<int2>();
+    A.segs = ctx->segs.as<int2>();
+    A.list = ctx->list.as<int32_t>();
+    A.ntiles = ctx->ntiles;
+    A.stage_max = static_cast<int32_t>(ctx->stage_max);
     A.ent = ctx->ent.as<uint16_t>();
     A.step_base = ctx->step_base.as<int64_t>();
     A.status = ctx->status.as<int32_t>();
@@ -58,9 +63,9 @@ void launch_one(pd_ctx* ctx, int mode, int in, int out, int64_t step_local)
 {
     const StepArgs A = step_args(ctx, in, out, step_local);
     if (ctx->has_osb)
-        hip_check(launch_osb_step(A, mode, fp32(ctx), ctx->lanes, ctx->stream), "state-based step launch");
+        hip_check(launch_osb_step(A, mode, fp32(ctx), ctx->stream), "state-based step launch");
     else if (ctx->mapping == PD_MAP_STAGED)
-        hip_check(launch_step_staged(A, mode, fp32(ctx), ctx->lanes, ext_kernels(ctx), ctx->stream),
+        hip_check(launch_step_staged(A, mode, fp32(ctx), ext_kernels(ctx), ctx->stream),
                   "step kernel launch");
     else
         hip_check(launch_step(A, ctx->lanes, mode, ctx->has_stiff, ext_kernels(ctx), ctx->stream),
@@ -189,7 +194,7 @@ void check_symmetric(const Inst& I)
 void launch_ec(pd_ctx* ctx, const StepArgs& A)
 {
     if (ctx->mapping == PD_MAP_STAGED)
-        hip_check(launch_step_staged(A, kModeEC, false, ctx->lanes, ext_kernels(ctx), ctx->stream),
+        hip_check(launch_step_staged(A, kModeEC, false, ext_kernels(ctx), ctx->stream),
                   "step kernel launch");
     else
         hip_check(launch_step(A, ctx->lanes, kModeEC, ctx->has_stiff, ext_kernels(ctx), ctx->stream),
@@ -209,8 +214,11 @@ void launch_damage_now(pd_ctx* ctx)
     D.params = ctx->params.as<InstParams>();
     D.phi = ctx->phi.as<double>();
     D.nslices = ctx->nslices;
-    D.pieces = ctx->pieces.as<int2>();
-    D.slice_piece = ctx->slice_piece.as<int32_t>();
+    D.tiles = ctx->tiles.as<TileRec>();
+    D.phases = ctx->phases.as<int2>();
+    D.segs = ctx->segs.as<int2>();
+    D.list = ctx->list.as<int32_t>();
+    D.ntiles = ctx->ntiles;
     D.ent = ctx->ent.as<uint16_t>();
     D.laws = ctx->has_laws ? ctx->laws.as<LawRec>() : nullptr;
     D.cls = ctx->cls.p ? ctx->cls.as<uint8_t>() : nullptr;

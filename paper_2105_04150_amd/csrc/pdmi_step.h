@@ -7,10 +7,11 @@
 // level k+1 into the other, so no wavefront can observe a half-updated field (the race
 // that forces the paper to keep integration in a separate kernel, Sec. 3.3).
 //
-// Mapping: a wavefront serves one slice of W = 64/G nodes; each node's bonds are split
-// over G lanes, each lane sums its bonds sequentially, and the G partial sums meet in a
-// butterfly of cross-lane shuffles.  No atomics and no LDS: a node's force is owned by
-// its slice and the result is deterministic.
+// Mapping (sliced kernels): a wavefront serves one slice of W = 64/G nodes; each node's bonds
+// are split over G lanes, each lane sums its bonds sequentially, and the G partial sums
+// meet in a butterfly of cross-lane shuffles.  No atomics and no LDS: a node's force is
+// owned by its slice and the result is deterministic.  The staged kernel is described at
+// step_staged.
 //
 // Bond arithmetic (per slot b = (i, j), Eqs. microelastic and simpleBond):
 //   xi = x_j - x_i,  eta = u_j - u_i,  y = xi + eta
@@ -40,7 +41,9 @@
 // w = 0).  Problems without zones or laws run the plain kernels.
 #pragma once
 
-#include "pdmi_device.h"
+#include "pdmi_tile.h"
+
+#include <type_traits>
 
 namespace pdmi {
 namespace {
@@ -65,7 +68,7 @@ struct SlotTerm32 {
 __device__ __forceinline__ bool slot_force(bool live, bool breakable, const double2 p0, const double2 p1, const double2 p2,
                                            double X0, double X1, double X2, double U0, double U1, double U2,
                                            double kv, double q0, double& F0, double& F1, double& F2, SlotTerm& st,
-                                           const SeriesCoef& sk = SeriesCoef(), uint64_t* cand_ballot = nullptr)
+                                           const SeriesCoef& sk = SeriesCoef())
 {
     const double xi0 = p0.x - X0, xi1 = p0.y - X1, xi2 = p1.x - X2;
     const double e0 = p1.y - U0, e1 = p2.x - U1, e2 = p2.y - U2;
@@ -84,8 +87,6 @@ __device__ __forceinline__ bool slot_force(bool live, bool breakable, const doub
     const bool below = q < q0;
     const bool cand = breakable && !below;
     const bool alive = live && !cand;
-    // the lanes' candidates as a mask (each ballot of a comparison is its lane mask)
-    if (cand_ballot) *cand_ballot = __builtin_amdgcn_ballot_w64(breakable) & ~__builtin_amdgcn_ballot_w64(below);
     // broken and padding slots (and candidates) evaluate g(0) = 0 and add nothing
     const double coef = (kv * iL) * one_minus_rsqrt1p(alive ? q : 0.0, sk);
     st = SlotTerm{q, coef, y0, y1, y2};
@@ -95,13 +96,111 @@ __device__ __forceinline__ bool slot_force(bool live, bool breakable, const doub
     return cand;
 }
 
+// The same contribution without a branch, for the kernels whose rows run interleaved.
+// With S = |y|^2 + |xi|^2 and d = (|y|^2 - |xi|^2) / S,
+//   (1/|xi|) (1 - |xi|/|y|) = sqrt(2) S^(-1/2) d H(d),   H = 1 + 5/8 d^2 + 63/128 d^4 + ...,
+// an even series about the mean square length: two terms reach as far as six of the series in
+// q (the next, 429/1024 d^6, is below 3e-17 for |d| < kMidRange), one reciprocal square root
+// serves length and stretch, and an unstretched bond gives exactly zero.  With the estimate
+// r of S^(-1/2), e = 1 - S r^2 (below 2^-22), d = tq r^2 and S^(-3/2) = r^3 (1 + 3/2 e) to
+// second order; the correction is summed with the series as 2/3 + e + 2/3 (H - 1), a term
+// t (5/3 - S r^2 + ...), so that coef lacks the factor kMidScale = 3/2 sqrt(2).
+// WIDE (|d| < kWideRange): two more terms and the estimate refined before it enters d and H.
+// d rises with q (d = q / (2 + q)), so its high word orders slots against the decision
+// edge and the series' range.
+constexpr double kMidScale = 2.1213203435596425732;
+template <typename Real>
+struct MidTerm {
+    Real coef, y0, y1, y2;
+    Real L2, tq, d;  // |xi|^2, |y|^2 - |xi|^2
+    int32_t hi;  // high word of d (FP32: its bits)
+};
+struct MidCoef {
+    double c0 = 5.0 / 3.0, c2 = 5.0 / 12.0, c4 = 21.0 / 64.0;
+};
+__device__ __forceinline__ MidCoef mid_coef_regs()
+{
+    MidCoef k;
+    asm volatile("" : "+s"(k.c4), "+s"(k.c0));
+    asm volatile("" : "+v"(k.c2));
+    return k;
+}
+template <bool WIDE>
+__device__ __forceinline__ MidTerm<double> slot_mid(const NodeRec& n, double X0, double X1, double X2, double U0, double U1,
+                                                    double U2, const MidCoef& k)
+{
+    const double xi0 = n.p0.x - X0, xi1 = n.p0.y - X1, xi2 = n.p1.x - X2;
+    const double e0 = n.p1.y - U0, e1 = n.p2.x - U1, e2 = n.p2.y - U2;
+    MidTerm<double> m;
+    m.y0 = xi0 + e0;
+    m.y1 = xi1 + e1;
+    m.y2 = xi2 + e2;
+    const double L2 = __builtin_fma(xi2, xi2, __builtin_fma(xi1, xi1, xi0 * xi0));
+    const double Y2 = __builtin_fma(m.y2, m.y2, __builtin_fma(m.y1, m.y1, m.y0 * m.y0));
+    const double tq = Y2 - L2, S = Y2 + L2;  // the numerator as in slot_force
+    double r = __builtin_amdgcn_rsq(S), d;
+    if constexpr (WIDE) {
+        r = __builtin_fma(0.5 * r, __builtin_fma(-S, r * r, 1.0), r);
+        d = tq * (r * r);
+        const double z = d * d;
+        double h = __builtin_fma(scalar_const(12155.0 / 49152.0), z, scalar_const(143.0 / 512.0));
+        h = __builtin_fma(h, z, k.c4);
+        h = __builtin_fma(h, z, k.c2);
+        m.coef = (d * r) * __builtin_fma(h, z, scalar_const(2.0 / 3.0));
+    } else {
+        const double a = r * r;
+        const double g = __builtin_fma(-S, a, k.c0);
+        d = tq * a;
+        const double z = d * d;
+        m.coef = (d * r) * __builtin_fma(__builtin_fma(k.c4, z, k.c2), z, g);
+    }
+    m.L2 = L2;
+    m.tq = tq;
+    m.d = d;
+    m.hi = static_cast<int32_t>(__double_as_longlong(d) >> 32);
+    return m;
+}
+
+// The FP32 build's: the bond vector formed in f64 and rounded once, tq without cancellation
+// as eta.(xi + y), S = 2 |xi|^2 + tq; the hardware's reciprocal square root is good to single
+// precision, and H needs one term (63/128 d^4 is below 5e-9 for |d| < kMidRange32; WIDE: three).  coef lacks
+// the factor kMidScale32 = sqrt(2).
+constexpr double kMidScale32 = 1.4142135623730950488;
+template <bool WIDE>
+__device__ __forceinline__ MidTerm<float> slot_mid32(const NodeRec& n, double X0, double X1, double X2, float U0, float U1,
+                                                     float U2)
+{
+    const float xi0 = static_cast<float>(n.p0.x - X0), xi1 = static_cast<float>(n.p0.y - X1),
+                xi2 = static_cast<float>(n.p1.x - X2);
+    const uint64_t b1 = __double_as_longlong(n.p1.y), b2 = __double_as_longlong(n.p2.x);
+    const float e0 = __uint_as_float(static_cast<uint32_t>(b1)) - U0, e1 = __uint_as_float(static_cast<uint32_t>(b1 >> 32)) - U1,
+                e2 = __uint_as_float(static_cast<uint32_t>(b2)) - U2;
+    MidTerm<float> m;
+    m.y0 = xi0 + e0;
+    m.y1 = xi1 + e1;
+    m.y2 = xi2 + e2;
+    const float z0 = xi0 + m.y0, z1 = xi1 + m.y1, z2 = xi2 + m.y2;
+    const float tq = __builtin_fmaf(e2, z2, __builtin_fmaf(e1, z1, e0 * z0));
+    m.L2 = __builtin_fmaf(xi2, xi2, __builtin_fmaf(xi1, xi1, xi0 * xi0));
+    m.tq = tq;
+    const float S = __builtin_fmaf(2.0f, m.L2, tq);
+    const float r = __builtin_amdgcn_rsqf(S);
+    const float d = tq * (r * r);
+    const float z = d * d;
+    float h = 0.625f;
+    if (WIDE) h = __builtin_fmaf(__builtin_fmaf(429.0f / 1024.0f, z, 63.0f / 128.0f), z, h);
+    m.coef = (d * r) * __builtin_fmaf(h, z, 1.0f);
+    m.d = d;
+    m.hi = static_cast<int32_t>(__float_as_uint(d));
+    return m;
+}
+
 // FP32 bond arithmetic (same formulas): the bond vector is formed in f64 from the f64
 // coordinates and rounded once, displacements are the f32 values of the records.
 // 1 - (1+q)^(-1/2) uses four series terms (below 1.3e-10 relative for |q| < 4e-3).
 __device__ __forceinline__ bool slot_force32(bool live, bool breakable, const double2 p0, const double2 p1, const double2 p2,
                                              double X0, double X1, double X2, float U0, float U1, float U2,
-                                             float kv, float q0, float& F0, float& F1, float& F2, SlotTerm32& st,
-                                             uint64_t* brk_ballot = nullptr)
+                                             float kv, float q0, float& F0, float& F1, float& F2, SlotTerm32& st)
 {
     const float xi0 = static_cast<float>(p0.x - X0), xi1 = static_cast<float>(p0.y - X1),
                 xi2 = static_cast<float>(p1.x - X2);
@@ -118,7 +217,6 @@ __device__ __forceinline__ bool slot_force32(bool live, bool breakable, const do
     const bool brk = breakable && q >= q0;
     const bool alive = live && !brk;
     // the lanes that break as a mask (each ballot of a comparison is its lane mask)
-    if (brk_ballot) *brk_ballot = __builtin_amdgcn_ballot_w64(breakable) & __builtin_amdgcn_ballot_w64(q >= q0);
     const float qa = alive ? q : 0.0f;
     float g;
     if (fabsf(qa) < 4.0e-3f) {
@@ -138,16 +236,23 @@ __device__ __forceinline__ bool slot_force32(bool live, bool breakable, const do
     return brk;
 }
 
+// Stretch from q without cancellation: s = q / (1 + sqrt(1 + q)).
+__device__ __forceinline__ double stretch_of(double q)
+{
+    const double r = rsq64<2>(1.0 + q);
+    return q * rcp64(__builtin_fma(1.0 + q, r, 1.0));
+}
+
 // Weight of a slot in the bond-model branch (EXT kernels): the slot is live and either at
-// or over the instance's lower decision edge q0, or softened.  q is its q of this pass,
-// nofail / soft its word's flags, sold its stored largest stretch (prefetched by the
+// or over the instance's lower decision edge q0, or softened.  q and s are its q and
+// stretch of this pass, nofail / soft its word's flags, sold its stored largest stretch (prefetched by the
 // caller when soft), exact_s() the slot's exact stretch (stretch_exact; the FP64 build
 // decides on it near every threshold and stores it as a new maximum, the FP32 build
 // decides on q).  Returns w (the bond adds w times its elastic force); sets broke when it
 // breaks now and newly_soft when it softens for the first time.  A zone bond, and every
 // bond in a force evaluation, keeps its damage state as it stands.
 template <int MODE, bool FP32, typename ExactS>
-__device__ double bond_weight(const StepArgs& A, const InstParams& P, int64_t ds, double q, bool nofail, bool soft,
+__device__ double bond_weight(const StepArgs& A, const InstParams& P, int64_t ds, double q, double s, bool nofail, bool soft,
                               double sold, bool& broke, bool& newly_soft, ExactS exact_s)
 {
     broke = false;
@@ -164,9 +269,6 @@ __device__ double bond_weight(const StepArgs& A, const InstParams& P, int64_t ds
     const LawRec& L = P.nlaw == 1 ? A.laws[P.law_off] : A.laws[P.law_off + A.cls[ds]];
     if (!soft) sold = 0.0;
     if (nofail || MODE == kModeForce) return soft ? law_secant(L, sold) : 1.0;
-    // stretch from q without cancellation: s = q / (1 + sqrt(1 + q))
-    const double r = rsq64<2>(1.0 + q);
-    double s = q * rcp64(__builtin_fma(1.0 + q, r, 1.0));
     // the exact stretch wherever rounding could decide: at or near the stored maximum (a
     // new maximum is stored exact) or near the law's elastic limit or last breakpoint
     const double s_first = L.s[0], s_last = L.s[L.nb - 1];
@@ -184,16 +286,32 @@ __device__ double bond_weight(const StepArgs& A, const InstParams& P, int64_t ds
     return law_secant(L, sm);
 }
 
-// Stiffness-correction factor of a slot of reference length L (CORR kernels), in the
-// order profile, partial volume, surface factor; fvi, fvj the family volumes of the two
-// ends.  The flags are the instance's, the same for the whole wavefront.
-__device__ __forceinline__ double corr_factor(const InstParams& P, double L, double fvi, double fvj)
+// Stiffness corrections that a staged kernel forms per slot: the profile and the surface factor,
+// or the partial volume too (its four operations in a slot's 55 are worth a variant).
+constexpr int kCorrNone = 0, kCorrPlain = 1, kCorrPartial = 2;
+
+// The correction factor of a slot of squared reference length L2, without the instance's
+// 2 V0 of the surface factor; V the sum of the two ends' family volumes.  The parameters of a
+// factor that the instance does not have make it 1.  One reciprocal square root
+// t = 1 / (L V) gives both 1 / L = V t and 1 / V = L t.
+template <int CORR>
+__device__ __forceinline__ double corr_factor(const InstParams& P, double L2, double V)
 {
-    double f = 1.0;
-    if (P.cr_flags & 1) f = fmax(__builtin_fma(-L, P.cr_idelta, 1.0), 0.0);
-    if (P.cr_flags & 2) f *= fmin(fmax(__builtin_fma(-L, P.cr_idx, P.cr_pvhi), 0.0), 1.0);
-    if (P.cr_flags & 4) f *= P.cr_2v0 * rcp64_1(fvi + fvj);
-    return f;
+    const double t = rsq64<1>(L2 * (V * V));
+    const double L = L2 * (V * t);
+    double f = fmax(__builtin_fma(-L, P.cr_idelta, 1.0), 0.0);
+    if constexpr (CORR == kCorrPartial) f *= fmin(fmax(__builtin_fma(-L, P.cr_idx, P.cr_pvhi), 0.0), 1.0);
+    return f * (L * t);
+}
+
+template <int CORR>
+__device__ __forceinline__ float corr_factor(const InstParams& P, float L2, float V)
+{
+    const float L = L2 * __builtin_amdgcn_rsqf(L2);
+    float f = fmaxf(__builtin_fmaf(-L, static_cast<float>(P.cr_idelta), 1.0f), 0.0f);
+    if constexpr (CORR == kCorrPartial)
+        f *= fminf(fmaxf(__builtin_fmaf(-L, static_cast<float>(P.cr_idx), static_cast<float>(P.cr_pvhi)), 0.0f), 1.0f);
+    return f * __builtin_amdgcn_rcpf(V);
 }
 
 // Integration and boundary conditions of one node given its force density F (the tail
@@ -372,7 +490,7 @@ __global__ __launch_bounds__(kBlock) void step_f64(StepArgs A)
                 double d0 = 0.0, d1 = 0.0, d2 = 0.0;
                 slot_force(true, false, r0, r1, r2, X0, X1, X2, U0, U1, U2, kv_of(t, j), P.q0, d0, d1, d2, st, sk);
                 bool brk, newly;
-                const double wt = bond_weight<MODE, false>(A, P, ds, st.q, (cw & kColNoFail) != 0, (cw & kColSoft) != 0,
+                const double wt = bond_weight<MODE, false>(A, P, ds, st.q, stretch_of(st.q), (cw & kColNoFail) != 0, (cw & kColSoft) != 0,
                                                            smax_at(t, cw), brk, newly, exact);
                 if (brk) {
                     A.col[ds] = ~cw;
@@ -451,396 +569,305 @@ __global__ __launch_bounds__(kBlock) void step_f64(StepArgs A)
     node_update<MODE>(A, P, node, U0, U1, U2, F0, F1, F2);
 }
 
-// Orders a wavefront's own LDS writes before its later LDS reads (no workgroup barrier).
-__device__ __forceinline__ void wave_sync()
+// Staged step kernel (see pdmi_tile.h for the tile and its staging): one lane a node, 2 to 8
+// wavefronts a slice.  A lane reads its slots' neighbours from LDS, a row ahead of their use;
+// entries (and the per-slot stiffness) stream from global memory a block of row pairs ahead.
+// The common path adds every live slot's term without a branch: broken and padding slots
+// read the sentinel record, whose term is exactly zero.  What the short series does not cover
+// -- a slot at the decision edge, beyond its range, softened -- is seen on the slot's d (or
+// its softened bit) once a block: from there on the wavefront's share goes by the long series
+// (five more operations a slot), and a block that has slots beyond that too slot by slot (rows_apart).
+// The partial forces of a slice's wavefronts meet in LDS in a fixed order.
+// Bound: FP64 vector issue at the clock the chip holds under it.  The 1M-node cube at horizon
+// 3.015 takes 183 us a step, 223 us when each wavefront staged runs of consecutive
+// records itself and took a reciprocal root and a six-term series per slot; at horizon 5.015
+// (216k nodes) 190 and 327, 1000 nodes 7.5 and 14.
+// STIFF per-slot stiffness, VOLN per-node volumes, KNODE per-node stiffness factors, CORR
+// stiffness corrections formed per slot (uniform stiffness and volume), EXT no-failure zones
+// and damage laws.
+template <bool FP32, int MODE, bool STIFF, bool VOLN, bool KNODE, bool EXT, int CORR>
+__global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A, const TileRec* __restrict__ tiles,
+                                                                  const int2* __restrict__ phases,
+                                                                  const int2* __restrict__ segs,
+                                                                  const int32_t* __restrict__ list)
 {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Before a wavefront refills its LDS area with direct global-to-LDS loads: every LDS read
-// it issued earlier has returned its data (s_waitcnt lgkmcnt = 0, vmcnt and expcnt at
-// their no-wait maxima).  The direct loads write LDS through the vector-memory path, which
-// is not ordered behind the wavefront's pending LDS reads, so without this wait a read of
-// the previous piece still queued in the LDS unit could return the next piece's data.
-__device__ __forceinline__ void lds_reads_done() { __builtin_amdgcn_s_waitcnt(0xC07F); }
-
-// Staged step kernel: one workgroup of S wavefronts per 64-node slice, one lane per node.
-// Wavefront w takes the slice's pieces w, w + S, w + 2S, ...  For every piece, the
-// wavefront loads the range's node records and the piece's slot entries straight into
-// its own LDS area (gfx950 global_load_lds_dwordx4, no staging registers, which leaves
-// room for six wavefronts per SIMD to cover the load latency); per-node weights come
-// through registers one piece ahead.  Every slot reads its neighbour from LDS.  Each record crosses the
-// vector-memory path once per piece instead of once per slot.  Per-slot stiffness, when
-// present, streams from global memory (two rows one piece ahead, the rest when the piece
-// starts, which keeps the register count at four wavefronts per SIMD).  Rows are processed in pairs so
-// the LDS reads of one row overlap the arithmetic of the other; an odd last row runs
-// alone.  With S > 1 the partial forces meet in LDS in a fixed order (S > 1 fills the
-// chip on problems with fewer slices than SIMDs).  CORR (uniform volume, no stiffness
-// field): the stiffness corrections are formed per slot from the bond length and the two
-// family volumes (the neighbour's staged beside its record) instead of read from a
-// per-slot stiffness stream.
-template <bool FP32, int MODE, bool STIFF, bool VOLN, bool KNODE, int S, bool EXT, bool CORR = false>
-__global__ __launch_bounds__(kWave * S) void step_staged(StepArgs A, const int2* __restrict__ pieces,
-                                                             const int32_t* __restrict__ slice_piece,
-                                                             const int64_t* __restrict__ slice_ptr)
-{
-    constexpr int kRecChunks = kStageChunks + 3;             // staged records, then the sentinel
-    constexpr int kEntChunks = kPieceRows * kWave * 2 / 16;  // 16-byte chunks of entries
-    // a per-node weight staged beside the records: through registers (VOLN, KNODE), or the
-    // family volumes copied straight to LDS (CORR)
-    constexpr bool WREG = VOLN || KNODE;
-    static_assert(!CORR || (!STIFF && !VOLN && !KNODE), "per-slot corrections: uniform stiffness and volume");
-    // staged weights (doubles): the range and the sentinel's slot; CORR copies a fixed window
-    // of 3 x 64 dwords (the family-volume buffer ends with spare entries)
-    constexpr int kVolWords = WREG ? (kEntPad / 48 + 2) / 2 * 2 : CORR ? 3 * kWave / 2 : 0;
-    static_assert(!CORR || kEntPad / 48 < kVolWords, "the sentinel's weight index lies in the copy");
-    constexpr int kLds = kRecChunks + kEntChunks + kVolWords / 2;
-    static_assert(kStageChunks == 4 * kWave && kEntChunks == kWave, "four record loads and one entry load");
-    __shared__ double2 lds[S * kLds];
-    __shared__ double red[S > 1 ? (S - 1) * 3 * kWave : 1];  // partial forces of wavefronts 1..S-1
-    const int wv = S > 1 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave) : 0;
-    double2* const lrec = lds + wv * kLds;
-    const char* const lrecb = reinterpret_cast<const char*>(lrec);
-    uint16_t* const lent = reinterpret_cast<uint16_t*>(lrec + kRecChunks);
-    double* const lvol = reinterpret_cast<double*>(lrec + kRecChunks + kEntChunks);
-
-    const int lane = threadIdx.x & (kWave - 1);
-    int64_t slice = wave_uniform(xcd_remap(blockIdx.x, gridDim.x));
-    if (slice >= A.nslices) return;
-    if (A.slice_order) slice = __builtin_amdgcn_readfirstlane(A.slice_order[slice]);
-    const int32_t* __restrict__ slice_inst = A.slice_inst;
+    using Real = std::conditional_t<FP32, float, double>;
+    extern __shared__ double2 lds[];
+    constexpr bool NODEW = VOLN || KNODE || CORR != kCorrNone;  // a double per neighbour node staged beside the records
+    constexpr bool WEIGHT = STIFF || NODEW;
+    constexpr int B = STIFF ? 2 : kPairsAhead;     // row pairs of a block
+    constexpr bool BREAKS = MODE != kModeForce;
+    static_assert(CORR == kCorrNone || (!STIFF && !VOLN && !KNODE), "per-slot corrections: uniform stiffness and volume");
+    __builtin_amdgcn_s_setprio(3);
+    const TileRec T = tiles[wave_uniform(xcd_remap(blockIdx.x, gridDim.x))];
+    const TileLane tl(T);
+    const int lane = tl.lane;
+    double2* const lrec = lds;
+    double* const lw = reinterpret_cast<double*>(lrec + 3 * (A.stage_max + 1));
+    const double* __restrict__ wsrc = KNODE ? A.nw : CORR ? A.cfv : A.vol;
+    const uint32_t* __restrict__ ent = reinterpret_cast<const uint32_t*>(A.ent) + lane;
+    const double2* __restrict__ kslot = reinterpret_cast<const double2*>(A.kslot) + lane;
     const InstParams* __restrict__ params = A.params;
-    const InstParams P = params[slice_inst[slice]];
-    const int64_t node = slice * kWave + lane;
+    const MidCoef mc = mid_coef_regs();
+    const bool laws = EXT && A.laws != nullptr;
+
+    if (threadIdx.x < 3) lrec[threadIdx.x] = sentinel_part<FP32>(threadIdx.x);
+    if (NODEW && threadIdx.x == 0) lw[0] = CORR ? 1.0 : 0.0;
+
+    if (T.nphases > 0) stage_records(A.rec_in, list + T.list, T.n, tl.wv, lane, lrec);
+    const InstParams& P = params[T.inst];
+    const int64_t node = tl.node(T);
     const double2* __restrict__ rin = reinterpret_cast<const double2*>(A.rec_in);
     const double2 o0 = rin[3 * node], o1 = rin[3 * node + 1], o2 = rin[3 * node + 2];
     const double X0 = o0.x, X1 = o0.y, X2 = o1.x;
     const double U0 = o1.y, U1 = o2.x, U2 = o2.y;  // FP64 build
     const uint64_t ub1 = __double_as_longlong(o1.y), ub2 = __double_as_longlong(o2.x);
-    const float Uf0 = __uint_as_float(static_cast<uint32_t>(ub1)), Uf1 = __uint_as_float(static_cast<uint32_t>(ub1 >> 32)),
+    const float Uf0 = __uint_as_float(static_cast<uint32_t>(ub1)),
+                Uf1 = __uint_as_float(static_cast<uint32_t>(ub1 >> 32)),
                 Uf2 = __uint_as_float(static_cast<uint32_t>(ub2));  // FP32 build
-    const double cv = P.c * P.volume;
-    // kernels with uniform c and V accumulate sum (1/|xi|) g(q) y (and the bond-model
-    // branch's corrections in the same units) and apply c V once, after the sum (in f64)
-    constexpr bool UNI = !STIFF && !VOLN && !KNODE && !CORR;
-    const float cvf = static_cast<float>(cv), q0f = static_cast<float>(P.q0);
-    uint16_t* __restrict__ entw = A.ent;
-    int32_t* __restrict__ bstep = A.bstep;
-    // the two innermost series coefficients stay in registers
-    const SeriesCoef sk = series_coef_regs();
-    const double2* __restrict__ ent2 = reinterpret_cast<const double2*>(A.ent);
-
-    // sentinel record (padding entries point at it), volume 0
-    if (lane < 3) lrec[kStageChunks + lane] = lane == 0 ? double2{1e10, 1e10} : lane == 1 ? double2{1e10, 0.0} : double2{0.0, 0.0};
-    // (CORR: the copied window fills the sentinel's slot with a positive family volume,
-    // which keeps 1/(V_i + V_j) finite on padding slots)
-    if (WREG && lane == 0) lvol[kEntPad / 48] = 0.0;
-    // staged weight: V_j, or sqrt(k_j) V_j with per-node stiffness (times the own sqrt(k_i)),
-    // or the family volume V_j of the surface correction
-    const double* __restrict__ wsrc = KNODE ? A.nw : CORR ? A.cfv : A.vol;
-    const double ai = KNODE ? A.na[node] : 0.0;
     const double fvi = CORR ? A.cfv[node] : 0.0;
-    // FP32 build: the correction constants in single precision, once
-    const float cr_id = static_cast<float>(P.cr_idelta), cr_ix = static_cast<float>(P.cr_idx),
-                cr_hi = static_cast<float>(P.cr_pvhi), cr_2v0 = static_cast<float>(P.cr_2v0);
+    const float q0f = static_cast<float>(P.q0);
+    const int32_t hi_pos = FP32 ? P.hi_pos32 : P.hi_pos, hi_wpos = FP32 ? P.hi_wpos32 : P.hi_wpos;
+    const uint32_t hi_neg = FP32 ? P.hi_neg32 : P.hi_neg, hi_wneg = FP32 ? P.hi_wneg32 : P.hi_wneg;
+    Real F0 = 0, F1 = 0, F2 = 0;   // sums without kMidScale and the factors shared by the node's bonds
 
-    const int p0 = __builtin_amdgcn_readfirstlane(slice_piece[slice]);
-    const int p1 = __builtin_amdgcn_readfirstlane(slice_piece[slice + 1]);
-    auto rows_of = [&](int p) { return (pieces[__builtin_amdgcn_readfirstlane(p)].y >> 8) & 0xff; };
-    int64_t ent = wave_uniform(slice_ptr[slice]);  // first entry of the current piece
-    const int pa = p0 + wv;                         // this wavefront's first piece
-    for (int q = p0; q < pa && q < p1; ++q) ent += static_cast<int64_t>(rows_of(q)) * kWave;
-    double F0 = 0.0, F1 = 0.0, F2 = 0.0;
-    float Ff0 = 0.0f, Ff1 = 0.0f, Ff2 = 0.0f;
-    // the slots of a row that take the rare branch are kept as its lane mask (scalar), and
-    // the rare branch finds the lanes again (the FP32 bond-model kernels keep per-lane bits)
-    constexpr bool ROWMASK = !FP32 || !EXT;
-    uint64_t cmask = 0;  // candidate lanes of the slot evaluated last
-
-    // staging registers of the next piece (weights and stiffness; records and entries go
-    // straight to LDS)
-    double vs0 = 0.0, vs1 = 0.0;
-    int vlen = 0;
-    constexpr int kKPre = 2;  // stiffness rows fetched a piece ahead; the rest when the piece starts
-    double kcur[kPieceRows], knext[kKPre];
-    auto kcur_at = [&](int t) {  // kcur[t] for a row index only known at run time (no indexed registers)
-        double k = 0.0;
-#pragma unroll
-        for (int u = 0; u < kPieceRows; ++u)
-            if (u == t) k = kcur[u];
-        return k;
+    auto term = [&](const NodeRec& r, auto wide) {
+        if constexpr (FP32)
+            return slot_mid32<decltype(wide)::value>(r, X0, X1, X2, Uf0, Uf1, Uf2);
+        else
+            return slot_mid<decltype(wide)::value>(r, X0, X1, X2, U0, U1, U2, mc);
     };
-
-    // Loads of piece p (first entry e): a fixed 256-chunk window from the range start
-    // (the record buffers end with kRecPad spare records) and the whole 8-row entry block
-    // (rows >= T are never read); volumes from clamped addresses.
-    auto issue = [&](int p, int64_t e) {
-        const int2 m = pieces[__builtin_amdgcn_readfirstlane(p)];
-        if (WREG) {
-            const int len = m.y & 0xff;
-            vlen = len;
-            vs0 = wsrc[m.x + min(lane, len - 1)];
-            vs1 = wsrc[m.x + min(lane + kWave, len - 1)];
-        }
-        if (STIFF)
-#pragma unroll
-            for (int t = 0; t < kKPre; ++t) knext[t] = __builtin_nontemporal_load(A.kslot + e + t * kWave + lane);
-    };
-    typedef __attribute__((address_space(3))) void* lds_ptr;
-    auto dma = [&](int p, int64_t e) {
-        const int2 m = pieces[__builtin_amdgcn_readfirstlane(p)];
-        const double2* rs = rin + 3 * static_cast<int64_t>(m.x) + lane;
-        // one address and one LDS base for the four 1 KB chunks: the instruction's immediate
-        // offset advances the global and the LDS address alike
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 16 * kWave, 0);
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 2 * 16 * kWave, 0);
-        __builtin_amdgcn_global_load_lds(rs, (lds_ptr)(lrec), 16, 3 * 16 * kWave, 0);
-        __builtin_amdgcn_global_load_lds(ent2 + e / 8 + lane, (lds_ptr)(lent), 16, 0, 0);
-        if (CORR) {
-            const float* ws = reinterpret_cast<const float*>(A.cfv + m.x) + lane;
-            float* wl = reinterpret_cast<float*>(lvol);
-            __builtin_amdgcn_global_load_lds(ws, (lds_ptr)(wl), 4, 0, 0);
-            __builtin_amdgcn_global_load_lds(ws + kWave, (lds_ptr)(wl + kWave), 4, 0, 0);
-            __builtin_amdgcn_global_load_lds(ws + 2 * kWave, (lds_ptr)(wl + 2 * kWave), 4, 0, 0);
-        }
-    };
-    auto commit = [&]() {
-        if (WREG) {
-            if (lane < vlen) lvol[lane] = vs0;
-            if (lane + kWave < vlen) lvol[lane + kWave] = vs1;
-        }
-    };
-    // One slot from its staged record into the force accumulators; returns true for a
-    // break candidate (plain kernels) and what the rare branches need in st / st32.
-    auto eval_into = [&](uint16_t e, double kst, bool live, bool breakable, SlotTerm& st, SlotTerm32& st32,
-                         double& G0, double& G1, double& G2, float& Gf0, float& Gf1, float& Gf2) {
-        const uint32_t off = e & kEntOff;  // byte offset of the neighbour's staged record
-        const double2 q0 = *reinterpret_cast<const double2*>(lrecb + off);
-        const double2 q1 = *reinterpret_cast<const double2*>(lrecb + off + 16);
-        const double2 q2 = *reinterpret_cast<const double2*>(lrecb + off + 32);
-        double kv = UNI ? 1.0 : cv;
-        const uint32_t widx = (off * 0xAAABu) >> 21;  // off / 48
-        if (KNODE) {
-            kv = ai * lvol[widx];
-        } else if (STIFF || VOLN) {
-            kv = (STIFF ? kst : P.c) * (VOLN ? lvol[widx] : P.volume);
-        } else if (CORR && !FP32) {  // the bond length as slot_force forms it (the compiler shares the work)
-            const double xa = q0.x - X0, xb = q0.y - X1, xc = q1.x - X2;
-            const double L2 = __builtin_fma(xc, xc, __builtin_fma(xb, xb, xa * xa));
-            kv = cv * corr_factor(P, L2 * rsq64<1>(L2), fvi, lvol[widx]);
-        }
-        float kvf = UNI ? 1.0f : cvf;
-        if (CORR && FP32) {  // the same factors in single precision, from slot_force32's bond vector
-            const float xa = static_cast<float>(q0.x - X0), xb = static_cast<float>(q0.y - X1),
-                        xc = static_cast<float>(q1.x - X2);
-            const float L2 = __builtin_fmaf(xc, xc, __builtin_fmaf(xb, xb, xa * xa));
-            const float L = L2 * __builtin_amdgcn_rsqf(L2);
-            float f = 1.0f;
-            if (P.cr_flags & 1) f = fmaxf(__builtin_fmaf(-L, cr_id, 1.0f), 0.0f);
-            if (P.cr_flags & 2) f *= fminf(fmaxf(__builtin_fmaf(-L, cr_ix, cr_hi), 0.0f), 1.0f);
-            if (P.cr_flags & 4) f *= cr_2v0 * __builtin_amdgcn_rcpf(static_cast<float>(fvi + lvol[widx]));
-            kvf = cvf * f;
-        }
-        if (FP32)
-            return slot_force32(live, breakable, q0, q1, q2, X0, X1, X2, Uf0, Uf1, Uf2,
-                                (STIFF || VOLN || KNODE) ? static_cast<float>(kv) : kvf,
-                                q0f, Gf0, Gf1, Gf2, st32, ROWMASK && !EXT ? &cmask : nullptr);
-        return slot_force(live, breakable, q0, q1, q2, X0, X1, X2, U0, U1, U2, kv, P.q0, G0, G1, G2, st, sk,
-                          ROWMASK && !EXT ? &cmask : nullptr);
-    };
-    auto eval = [&](uint16_t e, double kst, bool live, bool breakable, SlotTerm& st, SlotTerm32& st32) {
-        return eval_into(e, kst, live, breakable, st, st32, F0, F1, F2, Ff0, Ff1, Ff2);
-    };
-    // Plain kernels: true for a break candidate (FP32: a slot that breaks now).  EXT
-    // kernels: true when it takes the bond-model branch.
-    auto row = [&](uint16_t e, double kst, SlotTerm& st, SlotTerm32& st32) {
-        const bool live = !(e & kEntBroken);
-        if constexpr (EXT) {
-            const bool soft = (e & kEntSoft) != 0;
-            // the condition as lane masks (each ballot of a comparison is one), the entry's
-            // taken before the evaluation's branch
-            const uint64_t lm = ROWMASK ? __builtin_amdgcn_ballot_w64(live) : 0;
-            const uint64_t sm = ROWMASK ? __builtin_amdgcn_ballot_w64(soft) : 0;
-            eval(e, kst, live, false, st, st32);
-            const bool over = FP32 ? static_cast<float>(st32.q) >= q0f : st.q >= P.q0;
-            if constexpr (ROWMASK)
-                cmask = lm & (MODE == kModeForce ? sm : (__builtin_amdgcn_ballot_w64(over) | sm));
-            return live && (MODE == kModeForce ? soft : (over || soft));
+    // the factor of a slot that its node's bonds do not share
+    auto weight = [&](uint32_t idx, double k, Real L2) -> Real {
+        if constexpr (CORR != kCorrNone) {
+            return corr_factor<CORR>(P, L2, static_cast<Real>(fvi + lw[idx]));
+        } else if constexpr (NODEW) {
+            const double v = lw[idx];
+            return static_cast<Real>(STIFF ? k * v : v);
         } else {
-            return eval(e, kst, live, MODE != kModeForce && live, st, st32);
+            return static_cast<Real>(STIFF ? k : 1.0);
         }
     };
-    // a slot that broke in this pass: flag it (irreversible) and record the pass
-    auto broke = [&](int64_t ds, uint16_t e) {
-        entw[ds] = static_cast<uint16_t>(e | kEntBroken);
-        bstep[ds] = static_cast<int32_t>(*A.step_base + A.step_local);
+    auto add = [&](Real coef, const MidTerm<Real>& m) {
+        F0 = __builtin_elementwise_fma(coef, m.y0, F0);
+        F1 = __builtin_elementwise_fma(coef, m.y1, F1);
+        F2 = __builtin_elementwise_fma(coef, m.y2, F2);
     };
-    // the exact stretch of a slot from its staged record (FP64 build; the piece is still
-    // in LDS: the rare branches run before the next piece is loaded)
-    auto exact_of = [&](uint16_t e) {
-        return [&, e]() {
-            const uint32_t off = e & kEntOff;
-            return stretch_exact_rec(*reinterpret_cast<const double2*>(lrecb + off),
-                                     *reinterpret_cast<const double2*>(lrecb + off + 16),
-                                     *reinterpret_cast<const double2*>(lrecb + off + 32), X0, X1, X2, U0, U1, U2);
-        };
+    auto one = [&](const NodeRec& r, uint32_t idx, double k, auto wide) {
+        const MidTerm<Real> m = term(r, wide);
+        add(WEIGHT ? m.coef * weight(idx, k, m.L2) : m.coef, m);
+        return m.hi;
     };
-    // bond-model branch (EXT): move the slot's elastic contribution from weight 1 to the
-    // weight its damage state gives
-    auto model = [&](int64_t ds, uint16_t e, const SlotTerm& st, const SlotTerm32& st32) {
-        bool brk, newly;
-        const bool soft = (e & kEntSoft) != 0;
-        const double sold = soft ? A.smax[ds] : 0.0;
-        const double wt = bond_weight<MODE, FP32>(A, P, ds, FP32 ? st32.q : st.q, (e & kEntNoFail) != 0, soft,
-                                                  sold, brk, newly, exact_of(e));
-        if (brk)
-            broke(ds, e);
-        else if (newly)
-            entw[ds] = static_cast<uint16_t>(e | kEntSoft);
-        if (wt != 1.0) {
-            if (FP32) {
-                const float m = static_cast<float>(wt - 1.0) * st32.coef;
-                Ff0 = __builtin_fmaf(m, st32.y0, Ff0);
-                Ff1 = __builtin_fmaf(m, st32.y1, Ff1);
-                Ff2 = __builtin_fmaf(m, st32.y2, Ff2);
-            } else {
-                const double m = (wt - 1.0) * st.coef;
-                F0 = __builtin_fma(m, st.y0, F0);
-                F1 = __builtin_fma(m, st.y1, F1);
-                F2 = __builtin_fma(m, st.y2, F2);
+    auto ent_at = [&](int t) { return ent[static_cast<int64_t>(t) * kWave]; };
+    auto k_at = [&](int t) { return STIFF ? kslot[static_cast<int64_t>(t) * kWave] : double2{0.0, 0.0}; };
+    auto sold_at = [&](int t) {  // stretch state of a pair's slots (softened ones have one)
+        return laws ? *reinterpret_cast<const double2*>(A.smax + static_cast<int64_t>(t) * (2 * kWave) + 2 * lane)
+                    : double2{0.0, 0.0};
+    };
+    // The pairs [t, end), with a look at every slot that is at the decision edge, softened or
+    // beyond the long series (force: at all).  One slot at a time (two interleaved do not fit
+    // the registers), the next one's record in flight; a chunk's words are loaded together.
+    // With softened slots (EXT) the few tiles at a crack are the launch's tail.
+    auto rows_apart = [&](int t, int end, bool force) {
+        constexpr int C = STIFF ? 2 : 4;
+        uint32_t e2[C];
+        double2 k[C], sm[C];
+        NodeRec r;
+        int q = 0, nq = 0;  // slot of the chunk, slots of the chunk
+#pragma unroll 1
+        while (t < end) {
+            if (q == nq) {
+#pragma unroll
+                for (int u = 0; u < C; ++u) {
+                    e2[u] = t + u < end ? ent_at(t + u) : 0x80008000u;
+                    k[u] = k_at(t + u);
+                    sm[u] = sold_at(t + u);
+                }
+                q = 0;
+                nq = 2 * min(C, end - t);
+                r = staged_record(lrec, live_indices<true>(e2[0]) & 0xffffu);
+            }
+            const int h = q & 1;
+            const uint32_t e = h ? e2[0] >> 16 : e2[0] & 0xffffu;
+            const NodeRec rn = staged_record(lrec, h ? live_indices<true>(e2[1]) & 0xffffu : live_indices<true>(e2[0]) >> 16);
+            const MidTerm<Real> m = term(r, std::true_type{});
+            Real coef = m.coef;
+            const bool live = !(e & kEntBroken), soft = EXT && live && (e & kEntSoft) != 0;
+            const bool beyond = live && (m.hi >= hi_wpos || static_cast<uint32_t>(m.hi) >= hi_wneg || force);
+            if (__builtin_amdgcn_ballot_w64(beyond || soft) != 0 && (beyond || soft)) {
+                const int64_t ds = static_cast<int64_t>(t) * (2 * kWave) + 2 * lane + h;
+                auto exact = [&] { return stretch_exact_rec(r.p0, r.p1, r.p2, X0, X1, X2, U0, U1, U2); };
+                auto broke = [&] {  // irreversible; the pass is recorded
+                    A.ent[ds] = static_cast<uint16_t>(e | kEntBroken);
+                    A.bstep[ds] = static_cast<int32_t>(*A.step_base + A.step_local);
+                    coef = 0;
+                };
+                Real q;
+                double s = 0.0;  // the stretch, where damage laws may ask for it
+                if constexpr (FP32) {
+                    const float iL = __builtin_amdgcn_rsqf(m.L2);
+                    q = m.tq * (iL * iL);
+                    if (!(fabsf(m.d) < static_cast<float>(kWideRange32)))  // NaN: the squares overflowed
+                        coef = (1.0f / kMidScale32) * (iL * (1.0f - __builtin_amdgcn_rsqf(1.0f + q)));
+                    if (EXT) s = stretch_of(static_cast<double>(q));
+                } else if (EXT && fabs(m.d) < kWideRange) {
+                    // 1 + s = ((1 + d) / (1 - d))^(1/2) = (1 + d) (1 - d^2)^(-1/2): a softened
+                    // or overstretched slot within the series needs no root and no division
+                    const double z = m.d * m.d;
+                    double p = __builtin_fma(scalar_const(63.0 / 256.0), z, scalar_const(35.0 / 128.0));
+                    p = __builtin_fma(p, z, scalar_const(5.0 / 16.0));
+                    p = __builtin_fma(p, z, scalar_const(3.0 / 8.0));
+                    p = __builtin_fma(p, z, 0.5) * z;
+                    s = __builtin_fma(m.d, p, m.d + p);
+                    q = __builtin_fma(s, s, s + s);
+                } else {
+                    const double iL = rsq64<1>(m.L2);
+                    q = m.tq * (iL * iL);
+                    coef = (1.0 / kMidScale) * (iL * one_minus_rsqrt1p(q, series_coef_sregs()));
+                    if (EXT) s = stretch_of(q);
+                }
+                const bool over = FP32 ? !(q < static_cast<Real>(q0f)) : !(q < static_cast<Real>(P.q0));
+                if constexpr (EXT) {
+                    if (BREAKS ? (over || soft) : soft) {
+                        bool brk, newly;
+                        const double share = bond_weight<MODE, FP32>(A, P, ds, static_cast<double>(q), s, (e & kEntNoFail) != 0, soft,
+                                                                     h ? sm[0].y : sm[0].x, brk, newly, exact);
+                        if (brk)
+                            broke();
+                        else if (newly)
+                            A.ent[ds] = static_cast<uint16_t>(e | kEntSoft);
+                        coef = share != 0.0 && !brk ? coef * static_cast<Real>(share) : Real(0);
+                    }
+                } else if (BREAKS && over && (FP32 ? q >= static_cast<Real>(q0f) : exact() >= P.s0)) {
+                    broke();
+                }
+            }
+            // a broken slot adds nothing, whatever its numbers
+            if (coef != Real(0)) add(WEIGHT ? coef * weight(live ? e & kEntIdx : 0, h ? k[0].y : k[0].x, m.L2) : coef, m);
+            r = rn;
+            ++q;
+            if (h) {
+                ++t;
+#pragma unroll
+                for (int u = 0; u + 1 < C; ++u) {
+                    e2[u] = e2[u + 1];
+                    k[u] = k[u + 1];
+                    sm[u] = sm[u + 1];
+                }
+                e2[C - 1] = 0x80008000u;
             }
         }
     };
-    // rare branch of a flagged slot (kst: its per-slot stiffness), run once the piece's rows
-    // are done (the piece is still staged)
-    auto flagged = [&](int64_t ds, uint16_t e, double kst) {
-        SlotTerm st;
-        SlotTerm32 st32;
-        if constexpr (EXT) {
-            // the slot's terms as the common path formed them (evaluated again, into
-            // scratch accumulators), then its damage state's weight
-            double d0 = 0.0, d1 = 0.0, d2 = 0.0;
-            float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f;
-            eval_into(e, kst, true, false, st, st32, d0, d1, d2, f0, f1, f2);
-            model(ds, e, st, st32);
-        } else if (FP32 || exact_of(e)() >= P.s0) {  // FP64: a candidate decided on the exact stretch
-            broke(ds, e);
-        } else {  // it holds: the contribution the common path left out, evaluated again
-            eval(e, kst, true, false, st, st32);
+    uint32_t en[B];  // the next block's entries and stiffness
+    double2 kn[B];
+    auto fetch = [&](int t) {
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            en[u] = ent_at(t + u);
+            if (STIFF) kn[u] = k_at(t + u);
         }
+    };
+    // The pairs [t, end), after fetch(t), block by block by the short or the long series, up to
+    // the first block that has a softened slot or one that the series does not cover; that
+    // block is taken back.
+    auto rows = [&](int t, int end, auto wide) {
+        const int32_t pos = wide ? hi_wpos : hi_pos;
+        const uint32_t neg = wide ? hi_wneg : hi_neg;
+#pragma unroll 1
+        for (; t < end; t += B) {
+            uint32_t e[B];
+            double2 k[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                e[u] = en[u];
+                if (STIFF) k[u] = kn[u];
+            }
+            fetch(t + B);
+            if constexpr (EXT) {
+                uint32_t soft = 0;  // softened and not broken
+#pragma unroll
+                for (int u = 0; u < B; ++u) soft |= t + u < end ? e[u] & ~(e[u] >> 2) : 0u;
+                if (__builtin_amdgcn_ballot_w64((soft & 0x20002000u) != 0) != 0) return t;
+            }
+            const Real S0 = F0, S1 = F1, S2 = F2;
+            int32_t himax = std::numeric_limits<int32_t>::min();  // of the block's d: the largest high word
+            uint32_t himin = 0;  // and the one furthest below zero (sign bit set: large)
+            uint32_t v = live_indices<EXT>(e[0]);
+            NodeRec ra = staged_record(lrec, v & 0xffffu);
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                if (t + u >= end) break;
+                const uint32_t ia = v & 0xffffu, ib = v >> 16;
+                const NodeRec rb = staged_record(lrec, ib);
+                if (u + 1 < B) v = live_indices<EXT>(t + u + 1 < end ? e[u + 1] : 0x80008000u);
+                __builtin_amdgcn_sched_barrier(0);
+                const int32_t ha = one(ra, ia, STIFF ? k[u].x : 0.0, wide);
+                if (u + 1 < B) ra = staged_record(lrec, v & 0xffffu);
+                __builtin_amdgcn_sched_barrier(0);
+                const int32_t hb = one(rb, ib, STIFF ? k[u].y : 0.0, wide);
+                himax = max(max(himax, ha), hb);
+                himin = max(max(himin, static_cast<uint32_t>(ha)), static_cast<uint32_t>(hb));
+            }
+            if (__builtin_amdgcn_ballot_w64(himax >= pos || himin >= neg) != 0) {
+                F0 = S0;
+                F1 = S1;
+                F2 = S2;
+                return t;
+            }
+        }
+        return end;
+    };
+    auto share_rows = [&](int2 pr) {  // after fetch(pr.x)
+        int t = rows(pr.x, pr.y, std::false_type{});
+#pragma unroll 1
+        while (t < pr.y) {  // once the short series does not do, the long one for the rest
+            fetch(t);
+            t = rows(t, pr.y, std::true_type{});
+            if (t >= pr.y) break;
+            const int to = EXT ? pr.y : min(t + B, pr.y);  // softened slots are seldom alone
+            rows_apart(t, to, false);
+            t = to;
+        }
+    };
+    auto stage_phase = [&](int ph) {  // a later phase, or one staged again
+        const int2 pd = phases[T.phase + ph];
+        __syncthreads();  // the records before are no longer read
+        stage_records(A.rec_in, list + pd.x, pd.y, tl.wv, lane, lrec);
+        if (NODEW) stage_doubles(wsrc, list + pd.x, pd.y, tl.wv, lane, lw);
     };
 
-    if (pa < p1) {
-        issue(pa, ent);
-        for (int p = pa; p < p1; p += S) {
-            const int T = rows_of(p);
-            int64_t ent_next = ent + static_cast<int64_t>(T) * kWave;  // first entry of piece p + S
-            for (int q = p + 1; q < p + S && q < p1; ++q) ent_next += static_cast<int64_t>(rows_of(q)) * kWave;
-            wave_sync();  // the previous piece is no longer read
-            lds_reads_done();
-            dma(p, ent);
-            // s_waitcnt with vmcnt = 0 (expcnt and lgkmcnt at their no-wait maxima): the
-            // piece's direct-to-LDS loads have landed
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            commit();
-            if (STIFF)
-#pragma unroll
-                for (int t = 0; t < kPieceRows; ++t)
-                    kcur[t] = t < kKPre ? knext[t] : __builtin_nontemporal_load(A.kslot + ent + t * kWave + lane);
-            if (p + S < p1) issue(p + S, ent_next);
-            wave_sync();  // the piece's LDS copy is complete
-            // rows of this piece whose slot takes the rare branch: rows in which some lane's
-            // slot does, wave-uniform, or per lane (FP32 bond-model kernels)
-            uint32_t flags = 0;
-#pragma unroll
-            for (int t = 0; t < kPieceRows; t += 2) {
-                if (t >= T) break;
-                const uint16_t ea = lent[t * kWave + lane];
-                if (t + 1 < T) {
-                    const uint16_t eb = lent[(t + 1) * kWave + lane];
-                    SlotTerm sa, sb;
-                    SlotTerm32 sa32, sb32;
-                    const bool ba = row(ea, STIFF ? kcur[t] : 0.0, sa, sa32);
-                    const uint64_t cm_a = cmask;
-                    const bool bb = row(eb, STIFF ? kcur[t + 1] : 0.0, sb, sb32);
-                    if constexpr (ROWMASK)
-                        flags |= (cm_a != 0 ? 1u << t : 0u) | (cmask != 0 ? 2u << t : 0u);
-                    else
-                        flags |= (ba ? 1u << t : 0u) | (bb ? 2u << t : 0u);
-                } else {
-                    SlotTerm sa;
-                    SlotTerm32 sa32;
-                    const bool ba = row(ea, STIFF ? kcur[t] : 0.0, sa, sa32);
-                    if constexpr (ROWMASK)
-                        flags |= cmask != 0 ? 1u << t : 0u;
-                    else
-                        flags |= ba ? 1u << t : 0u;
-                }
-            }
-            if constexpr (!ROWMASK) {
-                if (__builtin_amdgcn_ballot_w64(flags != 0) != 0) {
-#pragma unroll
-                    for (int t = 0; t < kPieceRows; ++t)
-                        if (flags & (1u << t)) flagged(ent + t * kWave + lane, lent[t * kWave + lane], STIFF ? kcur[t] : 0.0);
-                }
-            } else if (__builtin_amdgcn_readfirstlane(flags) != 0) {
-                // the lanes of a marked row that take the rare branch, found again (the same
-                // arithmetic on the same staged record decides the same way)
+    if (NODEW && T.nphases > 0) stage_doubles(wsrc, list + T.list, T.n, tl.wv, lane, lw);
+    int2 pr = int2{0, 0};
 #pragma unroll 1
-                for (int t = 0; t < T; ++t) {
-                    if (!(__builtin_amdgcn_readfirstlane(flags) & (1u << t))) continue;
-                    const uint16_t e = lent[t * kWave + lane];
-                    const double kst = STIFF ? kcur_at(t) : 0.0;
-                    SlotTerm st;
-                    SlotTerm32 st32;
-                    double d0 = 0.0, d1 = 0.0, d2 = 0.0;
-                    float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f;
-                    const bool live = !(e & kEntBroken);
-                    if constexpr (EXT) {
-                        // the slot's terms as the common path formed them, then (for the lanes
-                        // that take the branch) its damage state's weight
-                        eval_into(e, kst, live, false, st, st32, d0, d1, d2, f0, f1, f2);
-                        const bool soft = (e & kEntSoft) != 0;
-                        if (live && (MODE == kModeForce ? soft : (st.q >= P.q0 || soft)))
-                            model(ent + t * kWave + lane, e, st, st32);
-                    } else if (eval_into(e, kst, live, MODE != kModeForce && live, st, st32, d0, d1, d2, f0, f1, f2)) {
-                        flagged(ent + t * kWave + lane, e, kst);
-                    }
-                }
+    for (int ph = 0; ph < T.nphases; ++ph) {
+        if (ph > 0) stage_phase(ph);
+        pr = tl.pairs(T, segs, ph);
+        fetch(pr.x);
+        tile_staged();
+        __builtin_amdgcn_s_setprio(0);
+        if (pr.x < pr.y) share_rows(pr);
+        __builtin_amdgcn_s_setprio(3);
+    }
+    // squares beyond the range of their type leave no finite sum: every slot in the general form
+    const bool unsound = !(__builtin_isfinite(F0) && __builtin_isfinite(F1) && __builtin_isfinite(F2));
+    if (T.nphases <= 1 ? __builtin_amdgcn_ballot_w64(unsound) != 0 : __syncthreads_or(unsound) != 0) {
+        F0 = F1 = F2 = 0;
+#pragma unroll 1
+        for (int ph = 0; ph < T.nphases; ++ph) {
+            if (T.nphases > 1) {
+                stage_phase(ph);
+                tile_staged();
             }
-            ent = ent_next;
+            pr = tl.pairs(T, segs, ph);
+            if (pr.x < pr.y) rows_apart(pr.x, pr.y, true);
         }
     }
-    if (FP32) {
-        F0 = Ff0;
-        F1 = Ff1;
-        F2 = Ff2;
-    }
-    if (S > 1) {  // wavefront 0 adds the partial forces of 1..S-1 in that order
-        if (wv > 0) {
-            double* r = red + (wv - 1) * 3 * kWave + lane;
-            r[0] = F0;
-            r[kWave] = F1;
-            r[2 * kWave] = F2;
-        }
-        __syncthreads();  // every wavefront of the workgroup reaches this once
-        if (wv > 0) return;
-#pragma unroll
-        for (int w = 1; w < S; ++w) {
-            const double* r = red + (w - 1) * 3 * kWave + lane;
-            F0 += r[0];
-            F1 += r[kWave];
-            F2 += r[2 * kWave];
-        }
-    }
-    if (UNI) {
-        F0 *= cv;
-        F1 *= cv;
-        F2 *= cv;
-    }
-    node_update<MODE, FP32>(A, P, node, U0, U1, U2, F0, F1, F2);
+    double G[3] = {F0, F1, F2};
+    tile_reduce(tl, reinterpret_cast<double*>(lds), G);
+    if (tl.sub > 0 || !tl.has) return;
+    const double share = (FP32 ? kMidScale32 : kMidScale) *
+                         (CORR ? P.cr_2v0 : 1.0) * (KNODE ? A.na[node] : STIFF ? (VOLN ? 1.0 : P.volume) : VOLN ? P.c : P.c * P.volume);
+    node_update<MODE, FP32>(A, P, node, U0, U1, U2, share * G[0], share * G[1], share * G[2]);
 }
 
 // ---------------------------------------------------------------- launch templates
@@ -874,47 +901,44 @@ hipError_t launch_step_g(const StepArgs& a, int mode, bool stiff, hipStream_t s)
                 : launch_step_gsv<G, false, false, false, EXT>(a, mode, s);
 }
 
-template <bool FP32, bool STIFF, bool VOLN, bool KNODE, int S, bool EXT, bool CORR = false>
-hipError_t launch_staged_svs(const StepArgs& a, int mode, hipStream_t s)
+template <bool FP32, int MODE, bool STIFF, bool VOLN, bool KNODE, bool EXT, int CORR>
+hipError_t launch_staged_m(const StepArgs& a, hipStream_t s)
 {
-    const dim3 grid(static_cast<unsigned>(a.nslices)), block(kWave * S);
-    switch (mode) {
-#define PD_L(M)                                                                                                   \
-    hipLaunchKernelGGL((step_staged<FP32, M, STIFF, VOLN, KNODE, S, EXT, CORR>), grid, block, 0, s, a, a.pieces, \
-                       a.slice_piece, a.slice_ptr)
-    case kModeEC: PD_L(kModeEC); break;
-    case kModeVV: PD_L(kModeVV); break;
-    case kModeVVInit: PD_L(kModeVVInit); break;
-    case kModeFE: PD_L(kModeFE); break;
-    case kModeForce: PD_L(kModeForce); break;
-#undef PD_L
-    default: return hipErrorInvalidValue;
-    }
+    auto* kernel = &step_staged<FP32, MODE, STIFF, VOLN, KNODE, EXT, CORR>;
+    const size_t bytes = tile_lds(a.stage_max, 48 + (VOLN || KNODE || CORR != kCorrNone ? 8 : 0));
+    const hipError_t e = tile_room(reinterpret_cast<const void*>(kernel), bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.ntiles)), dim3(kTileWaves * kWave), bytes, s, a, a.tiles,
+                       a.phases, a.segs, a.list);
     return hipGetLastError();
 }
 
-template <bool FP32, bool STIFF, bool VOLN, bool KNODE, bool EXT, bool CORR = false>
-hipError_t launch_staged_sv(const StepArgs& a, int mode, int split, hipStream_t s)
+template <bool FP32, bool STIFF, bool VOLN, bool KNODE, bool EXT, int CORR = kCorrNone>
+hipError_t launch_staged_sv(const StepArgs& a, int mode, hipStream_t s)
 {
-    switch (split) {
-    case 1: return launch_staged_svs<FP32, STIFF, VOLN, KNODE, 1, EXT, CORR>(a, mode, s);
-    case 2: return launch_staged_svs<FP32, STIFF, VOLN, KNODE, 2, EXT, CORR>(a, mode, s);
-    case 4: return launch_staged_svs<FP32, STIFF, VOLN, KNODE, 4, EXT, CORR>(a, mode, s);
+    switch (mode) {
+    case kModeEC: return launch_staged_m<FP32, kModeEC, STIFF, VOLN, KNODE, EXT, CORR>(a, s);
+    case kModeVV: return launch_staged_m<FP32, kModeVV, STIFF, VOLN, KNODE, EXT, CORR>(a, s);
+    case kModeVVInit: return launch_staged_m<FP32, kModeVVInit, STIFF, VOLN, KNODE, EXT, CORR>(a, s);
+    case kModeFE: return launch_staged_m<FP32, kModeFE, STIFF, VOLN, KNODE, EXT, CORR>(a, s);
+    case kModeForce: return launch_staged_m<FP32, kModeForce, STIFF, VOLN, KNODE, EXT, CORR>(a, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 template <bool FP32, bool EXT>
-hipError_t launch_staged_n(const StepArgs& a, int mode, int split, hipStream_t s)
+hipError_t launch_staged_n(const StepArgs& a, int mode, hipStream_t s)
 {
     const bool stiff = a.kslot != nullptr, voln = a.vol != nullptr;
-    if (a.cfv) return launch_staged_sv<FP32, false, false, false, EXT, true>(a, mode, split, s);  // corrections per slot
-    if (a.nw) return launch_staged_sv<FP32, false, false, true, EXT>(a, mode, split, s);  // per-node stiffness
+    if (a.cfv)  // corrections per slot
+        return a.partial ? launch_staged_sv<FP32, false, false, false, EXT, kCorrPartial>(a, mode, s)
+                         : launch_staged_sv<FP32, false, false, false, EXT, kCorrPlain>(a, mode, s);
+    if (a.nw) return launch_staged_sv<FP32, false, false, true, EXT>(a, mode, s);  // per-node stiffness
     if (stiff)
-        return voln ? launch_staged_sv<FP32, true, true, false, EXT>(a, mode, split, s)
-                    : launch_staged_sv<FP32, true, false, false, EXT>(a, mode, split, s);
-    return voln ? launch_staged_sv<FP32, false, true, false, EXT>(a, mode, split, s)
-                : launch_staged_sv<FP32, false, false, false, EXT>(a, mode, split, s);
+        return voln ? launch_staged_sv<FP32, true, true, false, EXT>(a, mode, s)
+                    : launch_staged_sv<FP32, true, false, false, EXT>(a, mode, s);
+    return voln ? launch_staged_sv<FP32, false, true, false, EXT>(a, mode, s)
+                : launch_staged_sv<FP32, false, false, false, EXT>(a, mode, s);
 }
 
 }  // namespace

@@ -3,10 +3,10 @@
 
 namespace pdmi {
 
-hipError_t launch_step_staged_f64(const StepArgs& a, int mode, int split, bool ext, hipStream_t s)
+hipError_t launch_step_staged_f64(const StepArgs& a, int mode, bool ext, hipStream_t s)
 {
-    if (a.nslices <= 0) return hipSuccess;
-    return ext ? launch_staged_n<false, true>(a, mode, split, s) : launch_staged_n<false, false>(a, mode, split, s);
+    if (a.ntiles <= 0) return hipSuccess;
+    return ext ? launch_staged_n<false, true>(a, mode, s) : launch_staged_n<false, false>(a, mode, s);
 }
 
 }  // namespace pdmi

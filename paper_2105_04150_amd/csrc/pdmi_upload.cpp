@@ -5,6 +5,20 @@
 namespace pdmi {
 namespace host {
 
+static uint32_t high_word(double x)
+{
+    uint64_t b;
+    std::memcpy(&b, &x, sizeof b);
+    return static_cast<uint32_t>(b >> 32);
+}
+
+static uint32_t float_bits(float x)
+{
+    uint32_t b;
+    std::memcpy(&b, &x, sizeof b);
+    return b;
+}
+
 static InstParams make_params(const Inst& I, int32_t law_off)
 {
     InstParams p{};
@@ -21,6 +35,23 @@ static InstParams make_params(const Inst& I, int32_t law_off)
         for (const LawRec& L : I.laws) qmin = std::min(qmin, L.s[0] * (2.0 + L.s[0]));
         p.q0 = qmin - decision_margin(qmin);
     }
+    // where the kernels' series end and a slot is settled apart: their d = q / (2 + q) carries
+    // 2^-21 of error (FP32 build: a few ulps); the decision itself is made on q.  A threshold
+    // within its margin of zero settles every slot apart.
+    const double d0 = (1.0 - 1.0e-6) * (p.q0 / (2.0 + p.q0));
+    auto ends = [&](double range, int32_t& pos, uint32_t& neg) {
+        neg = 0x80000000u | high_word(range);
+        pos = p.q0 > 0.0 ? static_cast<int32_t>(high_word(d0 < range ? d0 : range)) : std::numeric_limits<int32_t>::min();
+    };
+    auto ends32 = [&](double range, int32_t& pos, uint32_t& neg) {
+        neg = 0x80000000u | float_bits(static_cast<float>(range));
+        pos = p.q0 > 0.0 ? static_cast<int32_t>(float_bits(static_cast<float>(d0 < range ? d0 : range)))
+                         : std::numeric_limits<int32_t>::min();
+    };
+    ends(kMidRange, p.hi_pos, p.hi_neg);
+    ends(kWideRange, p.hi_wpos, p.hi_wneg);
+    ends32(kMidRange32, p.hi_pos32, p.hi_neg32);
+    ends32(kWideRange32, p.hi_wpos32, p.hi_wneg32);
     p.rho = I.rho;
     p.eta = I.eta;
     p.volume = I.volume;
@@ -30,15 +61,15 @@ static InstParams make_params(const Inst& I, int32_t law_off)
         p.osb_a = 3.0 * I.osb_K - 5.0 * I.osb_G;
         p.osb_b = 15.0 * I.osb_G;
     }
+    p.cr_pvhi = 1.0;
+    p.cr_2v0 = 2.0;
     if (I.has_corr) {
-        p.cr_flags = (I.corr.micromodulus == PD_MICRO_CONICAL ? 1 : 0) | (I.corr.partial_volumes ? 2 : 0) |
-                     (I.corr.surface ? 4 : 0);
-        if (I.corr.delta > 0.0) p.cr_idelta = 1.0 / I.corr.delta;
-        if (I.corr.dx > 0.0) {
+        if (I.corr.micromodulus == PD_MICRO_CONICAL) p.cr_idelta = 1.0 / I.corr.delta;
+        if (I.corr.partial_volumes) {
             p.cr_idx = 1.0 / I.corr.dx;
             p.cr_pvhi = (I.corr.delta + 0.5 * I.corr.dx) / I.corr.dx;
         }
-        p.cr_2v0 = 2.0 * I.corr_v0;
+        if (I.corr.surface) p.cr_2v0 = 2.0 * I.corr_v0;
     }
     return p;
 }
@@ -285,7 +316,7 @@ void upload_volumes(pd_ctx* ctx)
 
 // State-based model: 1/m_i per device node, m_i = sum over the whole family of |xi|^2 V_j
 // (influence function 1, reference configuration); padding 0.  The pair
-// buffer {theta/m, 1/m} starts zeroed, with kOsbPad spare pairs.
+// pair buffer starts zeroed, the sentinel's included.
 void upload_osb(pd_ctx* ctx)
 {
     ctx->has_osb = false;
@@ -526,9 +557,9 @@ void upload_col(pd_ctx* ctx, Inst& I, const uint8_t* broken, bool keep_bsteps,
             for (int64_t d = s0; d < s1; ++d) {
                 const int32_t b = I.dslot_user[d];
                 if (b < 0)
-                    e[d] = static_cast<uint16_t>(kEntBroken | kEntPad);
+                    e[d] = static_cast<uint16_t>(kEntBroken);
                 else
-                    e[d] = static_cast<uint16_t>((48 * I.ent_idx[d]) | ((broken && broken[b]) ? kEntBroken : 0) |
+                    e[d] = static_cast<uint16_t>(I.ent_idx[d] | ((broken && broken[b]) ? kEntBroken : 0) |
                                                  ((any_nf && nf[b]) ? kEntNoFail : 0) | (soft(b) ? kEntSoft : 0));
             }
         });
@@ -610,6 +641,25 @@ std::vector<double> u_of(pd_ctx* ctx, const Inst& I)
         for (int d = 0; d < 3; ++d) out[3 * p + d] = rec[6 * l + 3 + d];
     }
     return out;
+}
+
+// Break steps of one instance in user CSR order, and back (padding counts as broken).
+std::vector<int32_t> bstep_of(pd_ctx* ctx, const Inst& I)
+{
+    std::vector<int32_t> h(static_cast<size_t>(I.n_dslots)), out(static_cast<size_t>(I.nnz), kNeverBroke);
+    download(h.data(), ctx->bstep, h.size() * sizeof(int32_t), static_cast<size_t>(I.dslot_off) * sizeof(int32_t), ctx->stream);
+    sync(ctx);
+    for (int64_t d = 0; d < I.n_dslots; ++d)
+        if (I.dslot_user[d] >= 0) out[I.dslot_user[d]] = h[d];
+    return out;
+}
+
+void upload_bstep(pd_ctx* ctx, const Inst& I, const int32_t* bstep)
+{
+    std::vector<int32_t> h(static_cast<size_t>(I.n_dslots), kBrokeBefore);
+    for (int64_t d = 0; d < I.n_dslots; ++d)
+        if (I.dslot_user[d] >= 0) h[d] = bstep[I.dslot_user[d]];
+    upload(ctx->bstep, h.data(), h.size() * sizeof(int32_t), static_cast<size_t>(I.dslot_off) * sizeof(int32_t), ctx->stream);
 }
 
 HostState snapshot(pd_ctx* ctx)
