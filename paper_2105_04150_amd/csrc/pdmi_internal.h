@@ -83,9 +83,9 @@ struct LawRec {
     int32_t pad_;
 };
 // Ranges of |d| of the staged kernels' slot arithmetic (FP32 build: ...32): up to the first the
-// short series, whose estimate of S^(-1/2) enters its even terms unrefined (below 9e-13 in
-// all, 1e-13 rms); up to the second the long one (1e-15); closed form beyond.
-constexpr double kMidRange = 2.0e-3, kWideRange = 3.4e-2;
+// short series (the first term left out is below 1e-15 of the sum), up to the second the long
+// one (the same), closed form beyond.
+constexpr double kMidRange = 3.6e-3, kWideRange = 3.4e-2;
 constexpr double kMidRange32 = 1.0e-2, kWideRange32 = 0.1;  // to 5e-9
 constexpr int32_t kNodeFree = -1;       // bc_id of an unconstrained node
 constexpr int32_t kNodePad = -2;        // bc_id of a padding node (never updated)
@@ -120,9 +120,8 @@ struct InstParams {
     int32_t has_body;
     int32_t nlaw;    // damage laws of the instance (0: the brittle law with q0)
     int32_t law_off; // first law of the instance in StepArgs::laws
-    int32_t hi_pos;  // high word of d = q / (2 + q) at which the short series' rows end: the
-                     // decision edge q0 or the series' range
-
+    int32_t hi_edge;   // staged kernels, FP64: high word of 4 d at the decision edge, d = q / (2 + q)
+    int32_t hi_edge32; // FP32: bits of d there
     double osb_a;    // state-based linear solid: 3K - 5G
     double osb_b;    // state-based linear solid: 15G
     // stiffness corrections evaluated per slot (kernels with CORR): the conical profile
@@ -132,11 +131,6 @@ struct InstParams {
     double cr_pvhi;    // (delta + dx/2)/dx (1 without partial volumes)
     double cr_idx;     // 1/dx (0 without)
     double cr_2v0;     // 2 V0 (2 without the surface factor, whose family volumes are then 1)
-    uint32_t hi_neg;   // the same below zero (high word as unsigned; only the range)
-    int32_t hi_pos32;  // the FP32 build's, as bits of its d
-    uint32_t hi_neg32;
-    int32_t hi_wpos, hi_wpos32;  // the long series' ends
-    uint32_t hi_wneg, hi_wneg32;
 };
 
 // Constraint of one node: per component d, kind in bits 2d..2d+1 (0 free, 1 displacement,

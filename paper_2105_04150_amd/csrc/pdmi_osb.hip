@@ -26,7 +26,7 @@
 // Per slot, with S = |y|^2 + |xi|^2, tq = |y|^2 - |xi|^2 and d = tq / S (as in the bond-based
 // kernels; z = d^2):
 //   pass 1: |xi| e = |xi| (|y| - |xi|) = (tq / 2) [1 - d (1/2 + z/8 + z^2/16 + ...)];
-//   pass 2: g = 1 - |xi|/|y| = d [1 - d/2 + d^2/2 - 3d^3/8 + 3d^4/8 - 5d^5/16 + ...], and with
+//   pass 2: g = 1 - |xi|/|y| = d - (1 - d) (z/2 + 3z^2/8 + 5z^3/16 + ...), and with
 //     (s / (1 + s)) = g the force term is
 //     (t_ij + t_ji) V y / |y| = V [(a_i + a_j) + g ((b_i - a_i) + (b_j - a_j))] y,
 //     the |xi| of the scalar state cancelling the 1 / |xi| of y / |y|.
@@ -95,44 +95,48 @@ __device__ __forceinline__ OsbTerm<float> osb_term32(const NodeRec& n, double X0
 }
 
 // 2 |xi| e / tq = 1 - (1 - sqrt(1 - d^2)) / d and g = d P - (P - 1), P = (1 - d^2)^(-1/2), by their
-// series (WIDE: to kWideRange).
+// series (WIDE: to kWideRange, with the further terms left out where |d| < kMidRange: a
+// slot's form follows from its own d alone, so that a bond's two slots agree).
+template <typename Real>
+__device__ __forceinline__ bool osb_short(Real d)
+{
+    if constexpr (std::is_same_v<Real, float>)
+        return fabsf(d) < static_cast<float>(kMidRange32);
+    else
+        return fabs(d) < kMidRange;
+}
 template <bool WIDE, typename Real>
 __device__ __forceinline__ Real osb_extension(Real d)
 {
+    constexpr bool FP32 = std::is_same_v<Real, float>;
     const Real z = d * d;
-    Real p = Real(1.0 / 8.0);
+    Real p = FP32 ? Real(1.0 / 8.0) : Real(1.0 / 16.0);
     if constexpr (WIDE) {
-        p = __builtin_elementwise_fma(Real(7.0 / 256.0), z, Real(5.0 / 128.0));
-        p = __builtin_elementwise_fma(p, z, Real(1.0 / 16.0));
-        p = __builtin_elementwise_fma(p, z, Real(1.0 / 8.0));
-    } else if constexpr (!std::is_same_v<Real, float>) {
-        p = __builtin_fma(1.0 / 16.0, z, p);
+        Real t = __builtin_elementwise_fma(Real(7.0 / 256.0), z, Real(5.0 / 128.0));
+        if constexpr (FP32) t = __builtin_elementwise_fma(t, z, Real(1.0 / 16.0));
+        t = osb_short(d) ? Real(0) : t;
+        p = __builtin_elementwise_fma(t, z, p);
     }
+    if constexpr (!FP32) p = __builtin_elementwise_fma(p, z, Real(1.0 / 8.0));
     p = __builtin_elementwise_fma(p, z, Real(0.5));
     return __builtin_elementwise_fma(-d, p, Real(1));
 }
 template <bool WIDE, typename Real>
 __device__ __forceinline__ Real osb_g(Real d)
 {
-    Real p;
+    constexpr bool FP32 = std::is_same_v<Real, float>;
+    const Real z = d * d;
+    Real p = FP32 ? Real(3.0 / 8.0) : Real(5.0 / 16.0);
     if constexpr (WIDE) {
-        const Real z = d * d;
-        p = __builtin_elementwise_fma(Real(63.0 / 256.0), z, Real(35.0 / 128.0));
-        p = __builtin_elementwise_fma(p, z, Real(5.0 / 16.0));
-        p = __builtin_elementwise_fma(p, z, Real(3.0 / 8.0));
-        p = __builtin_elementwise_fma(p, z, Real(0.5));
-        p *= z;  // P - 1
-        return __builtin_elementwise_fma(d, p, d - p);
-    } else if constexpr (std::is_same_v<Real, float>) {
-        p = __builtin_fmaf(-3.0f / 8.0f, d, 0.5f);
-    } else {
-        p = __builtin_fma(-5.0 / 16.0, d, 3.0 / 8.0);
-        p = __builtin_fma(p, d, -3.0 / 8.0);
-        p = __builtin_fma(p, d, 0.5);
+        Real t = __builtin_elementwise_fma(Real(63.0 / 256.0), z, Real(35.0 / 128.0));
+        if constexpr (FP32) t = __builtin_elementwise_fma(t, z, Real(5.0 / 16.0));
+        t = osb_short(d) ? Real(0) : t;
+        p = __builtin_elementwise_fma(t, z, p);
     }
-    p = __builtin_elementwise_fma(p, d, Real(-0.5));
-    p = __builtin_elementwise_fma(p, d, Real(1));
-    return d * p;
+    if constexpr (!FP32) p = __builtin_elementwise_fma(p, z, Real(3.0 / 8.0));
+    p = __builtin_elementwise_fma(p, z, Real(0.5));
+    p *= z;  // P - 1
+    return __builtin_elementwise_fma(d, p, d - p);
 }
 
 template <bool FP32, int PASS, int MODE, bool VOLN>
@@ -167,13 +171,11 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
     const double2 own = PASS == 1 ? pairs_in[node] : double2{0.0, 0.0};
     const Real Pa = static_cast<Real>(own.x), Pd = static_cast<Real>(own.y);
     const float q0f = static_cast<float>(P.q0);
-    auto bits = [](double range, double range32) {
-        return static_cast<int32_t>(FP32 ? __float_as_uint(static_cast<float>(range32)) : __double_as_longlong(range) >> 32);
-    };
-    const int32_t hi_range = bits(kMidRange, kMidRange32), hi_wrange = bits(kWideRange, kWideRange32);
-    const int32_t hi_pos = BREAKS ? (FP32 ? P.hi_pos32 : P.hi_pos) : hi_range;
-    const int32_t hi_wpos = BREAKS ? (FP32 ? P.hi_wpos32 : P.hi_wpos) : hi_wrange;
-    const uint32_t hi_neg = 0x80000000u | static_cast<uint32_t>(hi_range), hi_wneg = 0x80000000u | static_cast<uint32_t>(hi_wrange);
+    // where a slot's series end, as high words of its d (hi_edge is of 4 d: two exponents more)
+    const int32_t edge = !BREAKS ? std::numeric_limits<int32_t>::max() : FP32 ? P.hi_edge32 : max(P.hi_edge, 0x00200000) - 0x00200000;
+    constexpr uint32_t range = range_bits<FP32>(0.25 * kMidRange, kMidRange32), wrange = range_bits<FP32>(0.25 * kWideRange, kWideRange32);
+    const int32_t hi_pos = min(static_cast<int32_t>(range), edge), hi_wpos = min(static_cast<int32_t>(wrange), edge);
+    constexpr uint32_t hi_neg = 0x80000000u | range, hi_wneg = 0x80000000u | wrange;
 
     // sentinel record, its pair and volume zero
     if (threadIdx.x < 3) lrec[threadIdx.x] = sentinel_part<FP32>(threadIdx.x);
@@ -247,13 +249,13 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
                         live = false;
                     }
                 }
-                if (PASS == 0) {
-                    v = Real(2) * m.L2 * sqrt1p_minus1(q);
-                } else if constexpr (FP32) {
-                    if (!(fabsf(m.d) < static_cast<float>(kWideRange32)))
+                if (!(__builtin_elementwise_abs(m.d) < static_cast<Real>(FP32 ? kWideRange32 : kWideRange))) {
+                    if (PASS == 0)
+                        v = Real(2) * m.L2 * sqrt1p_minus1(q);
+                    else if constexpr (FP32)
                         v = 1.0f - __builtin_amdgcn_rsqf(1.0f + q);
-                } else {
-                    v = one_minus_rsqrt1p(q, series_coef_sregs());
+                    else
+                        v = one_minus_rsqrt1p(q, series_coef_sregs());
                 }
             }
             if (live) add(m, e & kEntIdx, v);

@@ -98,31 +98,35 @@ __device__ __forceinline__ bool slot_force(bool live, bool breakable, const doub
 
 // The same contribution without a branch, for the kernels whose rows run interleaved.
 // With S = |y|^2 + |xi|^2 and d = (|y|^2 - |xi|^2) / S,
-//   (1/|xi|) (1 - |xi|/|y|) = sqrt(2) S^(-1/2) d H(d),   H = 1 + 5/8 d^2 + 63/128 d^4 + ...,
+//   (1/|xi|) (1 - |xi|/|y|) = sqrt(2) S^(-1/2) d H(d),
+//   H = 1 + 5/8 d^2 + 63/128 d^4 + 429/1024 d^6 + 12155/32768 d^8 + ...,
 // an even series about the mean square length: two terms reach as far as six of the series in
-// q (the next, 429/1024 d^6, is below 3e-17 for |d| < kMidRange), one reciprocal square root
-// serves length and stretch, and an unstretched bond gives exactly zero.  With the estimate
-// r of S^(-1/2), e = 1 - S r^2 (below 2^-22), d = tq r^2 and S^(-3/2) = r^3 (1 + 3/2 e) to
-// second order; the correction is summed with the series as 2/3 + e + 2/3 (H - 1), a term
-// t (5/3 - S r^2 + ...), so that coef lacks the factor kMidScale = 3/2 sqrt(2).
-// WIDE (|d| < kWideRange): two more terms and the estimate refined before it enters d and H.
+// q, one reciprocal square root serves length and stretch, and an unstretched bond gives
+// exactly zero.  The estimate r of S^(-1/2) takes one Newton step, as rsq64<1> does, in the
+// form r (3 - S r^2) = 2 S^(-1/2), so that the term carries 4 d and 16 d^2 and coef lacks the
+// factor kMidScale = sqrt(2) / 8.  Error: 9/8 e^2, e = 1 - S r^2 of the estimate (below 2^-22
+// by its specification: 6.4e-14; 1.6e-14 for 2^-23), the same as slot_force's; without the step
+// two operations fewer a slot (4 % of a step) and up to 2e-12.
+// WIDE: two more terms, left out where |d| < kMidRange.  A slot's form follows from its own d
+// alone, so that the two slots of a bond, whose d are the same number, carry the same
+// coefficient whatever blocks they lie in.
 // d rises with q (d = q / (2 + q)), so its high word orders slots against the decision
 // edge and the series' range.
-constexpr double kMidScale = 2.1213203435596425732;
+constexpr double kMidScale = 0.17677669529663688110;
 template <typename Real>
 struct MidTerm {
     Real coef, y0, y1, y2;
-    Real L2, tq, d;  // |xi|^2, |y|^2 - |xi|^2
+    Real L2, tq, d;  // |xi|^2, |y|^2 - |xi|^2, d (FP64: 4 d)
     int32_t hi;  // high word of d (FP32: its bits)
 };
 struct MidCoef {
-    double c0 = 5.0 / 3.0, c2 = 5.0 / 12.0, c4 = 21.0 / 64.0;
+    double c2 = 5.0 / 128.0, c4 = 63.0 / 32768.0;
 };
 __device__ __forceinline__ MidCoef mid_coef_regs()
 {
     MidCoef k;
-    asm volatile("" : "+s"(k.c4), "+s"(k.c0));
-    asm volatile("" : "+v"(k.c2));
+    asm volatile("" : "+s"(k.c2));
+    asm volatile("" : "+v"(k.c4));
     return k;
 }
 template <bool WIDE>
@@ -138,27 +142,32 @@ __device__ __forceinline__ MidTerm<double> slot_mid(const NodeRec& n, double X0,
     const double L2 = __builtin_fma(xi2, xi2, __builtin_fma(xi1, xi1, xi0 * xi0));
     const double Y2 = __builtin_fma(m.y2, m.y2, __builtin_fma(m.y1, m.y1, m.y0 * m.y0));
     const double tq = Y2 - L2, S = Y2 + L2;  // the numerator as in slot_force
-    double r = __builtin_amdgcn_rsq(S), d;
+    const double r = __builtin_amdgcn_rsq(S);
+    const double r2 = r * __builtin_fma(-S, r * r, 3.0);
+    const double d = tq * (r2 * r2);
+    const double z = d * d;
+    double h = k.c4;
     if constexpr (WIDE) {
-        r = __builtin_fma(0.5 * r, __builtin_fma(-S, r * r, 1.0), r);
-        d = tq * (r * r);
-        const double z = d * d;
-        double h = __builtin_fma(scalar_const(12155.0 / 49152.0), z, scalar_const(143.0 / 512.0));
-        h = __builtin_fma(h, z, k.c4);
-        h = __builtin_fma(h, z, k.c2);
-        m.coef = (d * r) * __builtin_fma(h, z, scalar_const(2.0 / 3.0));
-    } else {
-        const double a = r * r;
-        const double g = __builtin_fma(-S, a, k.c0);
-        d = tq * a;
-        const double z = d * d;
-        m.coef = (d * r) * __builtin_fma(__builtin_fma(k.c4, z, k.c2), z, g);
+        double t = __builtin_fma(scalar_const(12155.0 / 2147483648.0), z, scalar_const(429.0 / 4194304.0));
+        t = fabs(d) < 4.0 * kMidRange ? 0.0 : t;
+        h = __builtin_fma(t, z, h);
     }
+    m.coef = (d * r2) * __builtin_fma(__builtin_fma(h, z, k.c2), z, 1.0);
     m.L2 = L2;
     m.tq = tq;
     m.d = d;
     m.hi = static_cast<int32_t>(__double_as_longlong(d) >> 32);
     return m;
+}
+
+// High word of 4 range (FP32: the bits of range32), for comparison with MidTerm::hi.
+template <bool FP32>
+constexpr uint32_t range_bits(double range, double range32)
+{
+    if constexpr (FP32)
+        return __builtin_bit_cast(uint32_t, static_cast<float>(range32));
+    else
+        return static_cast<uint32_t>(__builtin_bit_cast(uint64_t, 4.0 * range) >> 32);
 }
 
 // The FP32 build's: the bond vector formed in f64 and rounded once, tq without cancellation
@@ -188,7 +197,11 @@ __device__ __forceinline__ MidTerm<float> slot_mid32(const NodeRec& n, double X0
     const float d = tq * (r * r);
     const float z = d * d;
     float h = 0.625f;
-    if (WIDE) h = __builtin_fmaf(__builtin_fmaf(429.0f / 1024.0f, z, 63.0f / 128.0f), z, h);
+    if (WIDE) {
+        float t = __builtin_fmaf(429.0f / 1024.0f, z, 63.0f / 128.0f);
+        t = fabsf(d) < static_cast<float>(kMidRange32) ? 0.0f : t;
+        h = __builtin_fmaf(t, z, h);
+    }
     m.coef = (d * r) * __builtin_fmaf(h, z, 1.0f);
     m.d = d;
     m.hi = static_cast<int32_t>(__float_as_uint(d));
@@ -627,8 +640,11 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 Uf2 = __uint_as_float(static_cast<uint32_t>(ub2));  // FP32 build
     const double fvi = CORR ? A.cfv[node] : 0.0;
     const float q0f = static_cast<float>(P.q0);
-    const int32_t hi_pos = FP32 ? P.hi_pos32 : P.hi_pos, hi_wpos = FP32 ? P.hi_wpos32 : P.hi_wpos;
-    const uint32_t hi_neg = FP32 ? P.hi_neg32 : P.hi_neg, hi_wneg = FP32 ? P.hi_wneg32 : P.hi_wneg;
+    // where a slot's series end, as high words of its d: the ranges, above zero the decision edge too
+    const int32_t edge = !BREAKS ? std::numeric_limits<int32_t>::max() : FP32 ? P.hi_edge32 : P.hi_edge;
+    constexpr uint32_t range = range_bits<FP32>(kMidRange, kMidRange32), wrange = range_bits<FP32>(kWideRange, kWideRange32);
+    const int32_t hi_pos = min(static_cast<int32_t>(range), edge), hi_wpos = min(static_cast<int32_t>(wrange), edge);
+    constexpr uint32_t hi_neg = 0x80000000u | range, hi_wneg = 0x80000000u | wrange;
     Real F0 = 0, F1 = 0, F2 = 0;   // sums without kMidScale and the factors shared by the node's bonds
 
     auto term = [&](const NodeRec& r, auto wide) {
@@ -710,20 +726,21 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                     if (!(fabsf(m.d) < static_cast<float>(kWideRange32)))  // NaN: the squares overflowed
                         coef = (1.0f / kMidScale32) * (iL * (1.0f - __builtin_amdgcn_rsqf(1.0f + q)));
                     if (EXT) s = stretch_of(static_cast<double>(q));
-                } else if (EXT && fabs(m.d) < kWideRange) {
+                } else if (EXT && fabs(m.d) < 4.0 * kWideRange) {
                     // 1 + s = ((1 + d) / (1 - d))^(1/2) = (1 + d) (1 - d^2)^(-1/2): a softened
                     // or overstretched slot within the series needs no root and no division
-                    const double z = m.d * m.d;
+                    const double d = 0.25 * m.d, z = d * d;
                     double p = __builtin_fma(scalar_const(63.0 / 256.0), z, scalar_const(35.0 / 128.0));
                     p = __builtin_fma(p, z, scalar_const(5.0 / 16.0));
                     p = __builtin_fma(p, z, scalar_const(3.0 / 8.0));
                     p = __builtin_fma(p, z, 0.5) * z;
-                    s = __builtin_fma(m.d, p, m.d + p);
+                    s = __builtin_fma(d, p, d + p);
                     q = __builtin_fma(s, s, s + s);
                 } else {
                     const double iL = rsq64<1>(m.L2);
                     q = m.tq * (iL * iL);
-                    coef = (1.0 / kMidScale) * (iL * one_minus_rsqrt1p(q, series_coef_sregs()));
+                    if (!(fabs(m.d) < 4.0 * kWideRange))
+                        coef = (1.0 / kMidScale) * (iL * one_minus_rsqrt1p(q, series_coef_sregs()));
                     if (EXT) s = stretch_of(q);
                 }
                 const bool over = FP32 ? !(q < static_cast<Real>(q0f)) : !(q < static_cast<Real>(P.q0));

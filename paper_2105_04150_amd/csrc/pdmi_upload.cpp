@@ -35,23 +35,13 @@ static InstParams make_params(const Inst& I, int32_t law_off)
         for (const LawRec& L : I.laws) qmin = std::min(qmin, L.s[0] * (2.0 + L.s[0]));
         p.q0 = qmin - decision_margin(qmin);
     }
-    // where the kernels' series end and a slot is settled apart: their d = q / (2 + q) carries
-    // 2^-21 of error (FP32 build: a few ulps); the decision itself is made on q.  A threshold
-    // within its margin of zero settles every slot apart.
-    const double d0 = (1.0 - 1.0e-6) * (p.q0 / (2.0 + p.q0));
-    auto ends = [&](double range, int32_t& pos, uint32_t& neg) {
-        neg = 0x80000000u | high_word(range);
-        pos = p.q0 > 0.0 ? static_cast<int32_t>(high_word(d0 < range ? d0 : range)) : std::numeric_limits<int32_t>::min();
-    };
-    auto ends32 = [&](double range, int32_t& pos, uint32_t& neg) {
-        neg = 0x80000000u | float_bits(static_cast<float>(range));
-        pos = p.q0 > 0.0 ? static_cast<int32_t>(float_bits(static_cast<float>(d0 < range ? d0 : range)))
-                         : std::numeric_limits<int32_t>::min();
-    };
-    ends(kMidRange, p.hi_pos, p.hi_neg);
-    ends(kWideRange, p.hi_wpos, p.hi_wneg);
-    ends32(kMidRange32, p.hi_pos32, p.hi_neg32);
-    ends32(kWideRange32, p.hi_wpos32, p.hi_wneg32);
+    // the staged kernels look at a slot apart where its d = q / (2 + q), which carries a few ulps
+    // of error (FP32 build: below 1e-6 with that of q), may have reached the decision edge; the
+    // decision itself is made on q.  A threshold within its margin of zero settles every slot
+    // apart, an infinite one (q0 NaN) none.
+    const double d0 = (1.0 - 1.0e-6) * (std::isfinite(p.q0) ? p.q0 / (2.0 + p.q0) : 1.0);
+    p.hi_edge = d0 > 0.0 ? static_cast<int32_t>(high_word(4.0 * d0)) : std::numeric_limits<int32_t>::min();
+    p.hi_edge32 = d0 > 0.0 ? static_cast<int32_t>(float_bits(static_cast<float>(d0))) : std::numeric_limits<int32_t>::min();
     p.rho = I.rho;
     p.eta = I.eta;
     p.volume = I.volume;
