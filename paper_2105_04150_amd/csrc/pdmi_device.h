@@ -168,7 +168,8 @@ __device__ __forceinline__ double rcp64_1(double x)
 // law's force c s[0] rho(sm), rho interpolated linearly between breakpoints, over the
 // elastic force c sm.  The bond force is this ratio times c s (unloading and reloading
 // follow the secant to the origin).
-__device__ __forceinline__ double law_secant(const LawRec& L, double sm)
+template <typename Law>
+__device__ __forceinline__ double law_secant(Law& L, double sm)
 {
     // segment of sm, chosen by selects (no indexed loads: a law shared by the wavefront
     // stays in scalar registers)

@@ -480,8 +480,7 @@ static int64_t build_staged(Inst& I, int64_t group, const StageRoom& room, const
 
 // Records a phase may hold: what fits a workgroup's LDS in every kernel that the problem can
 // run with what it carries now (48 bytes a record, 8 for a weight of its node, 16 for the
-// state-based pair, 24 for the adjoint velocity), beside the partial sums of the largest
-// split and the kernels' static LDS.
+// state-based pair, 24 for the adjoint velocity).
 static StageRoom stage_room(const pd_ctx* ctx)
 {
     bool vol = false, knode = false, corr = false, osb = false;
@@ -495,7 +494,7 @@ static StageRoom stage_room(const pd_ctx* ctx)
     int64_t per = 48 + weight;
     if (osb) per = 64 + weight;
     if (ctx->adjoint) per = std::max<int64_t>(per, 72 + (vol ? 8 : 0) + (knode ? 8 : 0));
-    const int64_t fixed = 1280;  // the kernels' static LDS, in the hardware's steps
+    const int64_t fixed = 1280;  // the step kernel's lists of slots to settle (1 KB), in the hardware's steps
     return StageRoom{(kLdsBytes / 2 - fixed) / per - 1, std::min<int64_t>((kLdsBytes - fixed) / per - 1, kEntIdx)};
 }
 

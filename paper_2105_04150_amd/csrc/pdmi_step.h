@@ -107,7 +107,8 @@ __device__ __forceinline__ bool slot_force(bool live, bool breakable, const doub
 // factor kMidScale = sqrt(2) / 8.  Error: 9/8 e^2, e = 1 - S r^2 of the estimate (below 2^-22
 // by its specification: 6.4e-14; 1.6e-14 for 2^-23), the same as slot_force's; without the step
 // two operations fewer a slot (4 % of a step) and up to 2e-12.
-// WIDE: two more terms, left out where |d| < kMidRange.  A slot's form follows from its own d
+// LEVEL 1: two more terms, left out where |d| < kMidRange.  LEVEL 2: the closed form too, from
+// kWideRange on (NaN: squares beyond the type's range).  A slot's form follows from its own d
 // alone, so that the two slots of a bond, whose d are the same number, carry the same
 // coefficient whatever blocks they lie in.
 // d rises with q (d = q / (2 + q)), so its high word orders slots against the decision
@@ -116,7 +117,8 @@ constexpr double kMidScale = 0.17677669529663688110;
 template <typename Real>
 struct MidTerm {
     Real coef, y0, y1, y2;
-    Real L2, tq, d;  // |xi|^2, |y|^2 - |xi|^2, d (FP64: 4 d)
+    Real L2, d;  // |xi|^2, d (FP64: 4 d)
+    Real q;      // level 2 only
     int32_t hi;  // high word of d (FP32: its bits)
 };
 struct MidCoef {
@@ -129,7 +131,7 @@ __device__ __forceinline__ MidCoef mid_coef_regs()
     asm volatile("" : "+v"(k.c4));
     return k;
 }
-template <bool WIDE>
+template <int LEVEL>
 __device__ __forceinline__ MidTerm<double> slot_mid(const NodeRec& n, double X0, double X1, double X2, double U0, double U1,
                                                     double U2, const MidCoef& k)
 {
@@ -147,14 +149,19 @@ __device__ __forceinline__ MidTerm<double> slot_mid(const NodeRec& n, double X0,
     const double d = tq * (r2 * r2);
     const double z = d * d;
     double h = k.c4;
-    if constexpr (WIDE) {
+    if constexpr (LEVEL > 0) {
         double t = __builtin_fma(scalar_const(12155.0 / 2147483648.0), z, scalar_const(429.0 / 4194304.0));
         t = fabs(d) < 4.0 * kMidRange ? 0.0 : t;
         h = __builtin_fma(t, z, h);
     }
     m.coef = (d * r2) * __builtin_fma(__builtin_fma(h, z, k.c2), z, 1.0);
+    if constexpr (LEVEL > 1) {
+        const double iL = rsq64<1>(L2);
+        m.q = tq * (iL * iL);
+        const double c = scalar_const(1.0 / kMidScale) * (iL * (1.0 - rsq64<2>(1.0 + m.q)));
+        m.coef = fabs(d) < 4.0 * kWideRange ? m.coef : c;
+    }
     m.L2 = L2;
-    m.tq = tq;
     m.d = d;
     m.hi = static_cast<int32_t>(__double_as_longlong(d) >> 32);
     return m;
@@ -172,10 +179,10 @@ constexpr uint32_t range_bits(double range, double range32)
 
 // The FP32 build's: the bond vector formed in f64 and rounded once, tq without cancellation
 // as eta.(xi + y), S = 2 |xi|^2 + tq; the hardware's reciprocal square root is good to single
-// precision, and H needs one term (63/128 d^4 is below 5e-9 for |d| < kMidRange32; WIDE: three).  coef lacks
+// precision, and H needs one term (63/128 d^4 is below 5e-9 for |d| < kMidRange32; from there three).  coef lacks
 // the factor kMidScale32 = sqrt(2).
 constexpr double kMidScale32 = 1.4142135623730950488;
-template <bool WIDE>
+template <int LEVEL>
 __device__ __forceinline__ MidTerm<float> slot_mid32(const NodeRec& n, double X0, double X1, double X2, float U0, float U1,
                                                      float U2)
 {
@@ -191,18 +198,23 @@ __device__ __forceinline__ MidTerm<float> slot_mid32(const NodeRec& n, double X0
     const float z0 = xi0 + m.y0, z1 = xi1 + m.y1, z2 = xi2 + m.y2;
     const float tq = __builtin_fmaf(e2, z2, __builtin_fmaf(e1, z1, e0 * z0));
     m.L2 = __builtin_fmaf(xi2, xi2, __builtin_fmaf(xi1, xi1, xi0 * xi0));
-    m.tq = tq;
     const float S = __builtin_fmaf(2.0f, m.L2, tq);
     const float r = __builtin_amdgcn_rsqf(S);
     const float d = tq * (r * r);
     const float z = d * d;
     float h = 0.625f;
-    if (WIDE) {
+    if constexpr (LEVEL > 0) {
         float t = __builtin_fmaf(429.0f / 1024.0f, z, 63.0f / 128.0f);
         t = fabsf(d) < static_cast<float>(kMidRange32) ? 0.0f : t;
         h = __builtin_fmaf(t, z, h);
     }
     m.coef = (d * r) * __builtin_fmaf(h, z, 1.0f);
+    if constexpr (LEVEL > 1) {
+        const float iL = __builtin_amdgcn_rsqf(m.L2);
+        m.q = tq * (iL * iL);
+        const float c = (1.0f / static_cast<float>(kMidScale32)) * (iL * (1.0f - __builtin_amdgcn_rsqf(1.0f + m.q)));
+        m.coef = fabsf(d) < static_cast<float>(kWideRange32) ? m.coef : c;
+    }
     m.d = d;
     m.hi = static_cast<int32_t>(__float_as_uint(d));
     return m;
@@ -261,42 +273,53 @@ __device__ __forceinline__ double stretch_of(double q)
 // stretch of this pass, nofail / soft its word's flags, sold its stored largest stretch (prefetched by the
 // caller when soft), exact_s() the slot's exact stretch (stretch_exact; the FP64 build
 // decides on it near every threshold and stores it as a new maximum, the FP32 build
-// decides on q).  Returns w (the bond adds w times its elastic force); sets broke when it
-// breaks now and newly_soft when it softens for the first time.  A zone bond, and every
+// decides on q).  The bond adds `share` times its elastic force; it breaks now, softens for
+// the first time, or reaches a new maximum smax, which the caller stores.  A zone bond, and every
 // bond in a force evaluation, keeps its damage state as it stands.
+struct BondWeight {
+    double share = 1.0, smax = 0.0;
+    bool broke = false, newly_soft = false, grew = false;
+};
 template <int MODE, bool FP32, typename ExactS>
-__device__ double bond_weight(const StepArgs& A, const InstParams& P, int64_t ds, double q, double s, bool nofail, bool soft,
-                              double sold, bool& broke, bool& newly_soft, ExactS exact_s)
+__device__ __forceinline__ BondWeight bond_weight(const StepArgs& A, const InstParams& P, int64_t ds, double q, double s, bool nofail,
+                                                  bool soft, double sold, ExactS exact_s)
 {
-    broke = false;
-    newly_soft = false;
-    if (P.nlaw == 0) {  // the brittle law with the instance's s0
-        if (nofail || MODE == kModeForce) return 1.0;
-        if (FP32)
-            broke = static_cast<float>(q) >= static_cast<float>(P.q0);
-        else
-            broke = q >= P.q0 && exact_s() >= P.s0;
-        return broke ? 0.0 : 1.0;
-    }
-    // a single law per instance is the same for the whole wavefront (scalar loads)
-    const LawRec& L = P.nlaw == 1 ? A.laws[P.law_off] : A.laws[P.law_off + A.cls[ds]];
+    // a single law per instance is the same for the whole wavefront (scalar loads, which the
+    // constant address space asks for: the kernel's own stores rule them out otherwise)
+    const auto& one = *(const __attribute__((address_space(4))) LawRec*)(A.laws + P.law_off);
+    const LawRec* const own = A.laws + P.law_off + (P.nlaw > 1 ? A.cls[ds] : 0);
+    auto secant = [&](double sm) { return P.nlaw == 1 ? law_secant(one, sm) : law_secant(*own, sm); };
+    BondWeight w;
     if (!soft) sold = 0.0;
-    if (nofail || MODE == kModeForce) return soft ? law_secant(L, sold) : 1.0;
+    if (nofail || MODE == kModeForce) {
+        if (soft) w.share = secant(sold);
+        return w;
+    }
+    double s_first = P.s0, s_last = P.s0;  // the brittle law with the instance's s0
+    if (P.nlaw == 1) {
+        s_first = one.s[0];
+        s_last = one.s[one.nb - 1];
+    } else if (P.nlaw > 1) {
+        s_first = own->s[0];
+        s_last = own->s[own->nb - 1];
+    } else if (FP32) {  // which the FP32 build decides on q
+        s = static_cast<float>(q) >= static_cast<float>(P.q0) ? s_last : 0.0;
+    }
     // the exact stretch wherever rounding could decide: at or near the stored maximum (a
     // new maximum is stored exact) or near the law's elastic limit or last breakpoint
-    const double s_first = L.s[0], s_last = L.s[L.nb - 1];
     if (!FP32 && (s >= sold - decision_margin(sold) || fabs(s - s_first) <= decision_margin(s_first) ||
                   fabs(s - s_last) <= decision_margin(s_last)))
         s = exact_s();
-    const double sm = s > sold ? s : sold;
-    if (sm >= s_last) {
-        broke = true;
-        return 0.0;
+    w.smax = s > sold ? s : sold;
+    if (w.smax >= s_last) {
+        w.broke = true;
+        w.share = 0.0;
+    } else if (w.smax > s_first) {
+        w.grew = w.smax > sold;
+        w.newly_soft = !soft;
+        w.share = secant(w.smax);
     }
-    if (!(sm > s_first)) return 1.0;
-    if (sm > sold) A.smax[ds] = sm;
-    newly_soft = !soft;
-    return law_secant(L, sm);
+    return w;
 }
 
 // Stiffness corrections that a staged kernel forms per slot: the profile and the surface factor,
@@ -502,13 +525,14 @@ __global__ __launch_bounds__(kBlock) void step_f64(StepArgs A)
                 SlotTerm st;
                 double d0 = 0.0, d1 = 0.0, d2 = 0.0;
                 slot_force(true, false, r0, r1, r2, X0, X1, X2, U0, U1, U2, kv_of(t, j), P.q0, d0, d1, d2, st, sk);
-                bool brk, newly;
-                const double wt = bond_weight<MODE, false>(A, P, ds, st.q, stretch_of(st.q), (cw & kColNoFail) != 0, (cw & kColSoft) != 0,
-                                                           smax_at(t, cw), brk, newly, exact);
-                if (brk) {
+                const BondWeight bw = bond_weight<MODE, false>(A, P, ds, st.q, stretch_of(st.q), (cw & kColNoFail) != 0,
+                                                               (cw & kColSoft) != 0, smax_at(t, cw), exact);
+                const double wt = bw.share;
+                if (bw.grew) A.smax[ds] = bw.smax;
+                if (bw.broke) {
                     A.col[ds] = ~cw;
                     A.bstep[ds] = step;
-                } else if (newly) {
+                } else if (bw.newly_soft) {
                     A.col[ds] = cw | kColSoft;
                 }
                 if (wt != 1.0) {
@@ -585,16 +609,14 @@ __global__ __launch_bounds__(kBlock) void step_f64(StepArgs A)
 // Staged step kernel (see pdmi_tile.h for the tile and its staging): one lane a node, 2 to 8
 // wavefronts a slice.  A lane reads its slots' neighbours from LDS, a row ahead of their use;
 // entries (and the per-slot stiffness) stream from global memory a block of row pairs ahead.
-// The common path adds every live slot's term without a branch: broken and padding slots
-// read the sentinel record, whose term is exactly zero.  What the short series does not cover
-// -- a slot at the decision edge, beyond its range, softened -- is seen on the slot's d (or
-// its softened bit) once a block: from there on the wavefront's share goes by the long series
-// (five more operations a slot), and a block that has slots beyond that too slot by slot (rows_apart).
+// The common path adds every live bond's term without a branch: broken, padding and softened
+// slots read the sentinel record, whose term is exactly zero.  What a level of the series
+// does not cover is seen on the slots' d once a block, which is then taken again at
+// the level it asks for.  The last level covers every d and leaves out the slots at the
+// decision edge.  Those and the softened ones are kept as bits of each lane's window of
+// 32 row pairs and settled after it (the tiles at a crack are the launch's tail).
 // The partial forces of a slice's wavefronts meet in LDS in a fixed order.
-// Bound: FP64 vector issue at the clock the chip holds under it.  The 1M-node cube at horizon
-// 3.015 takes 183 us a step, 223 us when each wavefront staged runs of consecutive
-// records itself and took a reciprocal root and a six-term series per slot; at horizon 5.015
-// (216k nodes) 190 and 327, 1000 nodes 7.5 and 14.
+// Bound: FP64 vector issue at the clock the chip holds under it.
 // STIFF per-slot stiffness, VOLN per-node volumes, KNODE per-node stiffness factors, CORR
 // stiffness corrections formed per slot (uniform stiffness and volume), EXT no-failure zones
 // and damage laws.
@@ -617,6 +639,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     const int lane = tl.lane;
     double2* const lrec = lds;
     double* const lw = reinterpret_cast<double*>(lrec + 3 * (A.stage_max + 1));
+    uint16_t* const litem = reinterpret_cast<uint16_t*>(lw + (NODEW ? A.stage_max + 1 : 0)) + tl.wv * kWave;  // see settle
     const double* __restrict__ wsrc = KNODE ? A.nw : CORR ? A.cfv : A.vol;
     const uint32_t* __restrict__ ent = reinterpret_cast<const uint32_t*>(A.ent) + lane;
     const double2* __restrict__ kslot = reinterpret_cast<const double2*>(A.kslot) + lane;
@@ -640,23 +663,23 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 Uf2 = __uint_as_float(static_cast<uint32_t>(ub2));  // FP32 build
     const double fvi = CORR ? A.cfv[node] : 0.0;
     const float q0f = static_cast<float>(P.q0);
-    // where a slot's series end, as high words of its d: the ranges, above zero the decision edge too
+    // where the levels end, as high words of a slot's d: their ranges, above zero the decision edge too
     const int32_t edge = !BREAKS ? std::numeric_limits<int32_t>::max() : FP32 ? P.hi_edge32 : P.hi_edge;
     constexpr uint32_t range = range_bits<FP32>(kMidRange, kMidRange32), wrange = range_bits<FP32>(kWideRange, kWideRange32);
-    const int32_t hi_pos = min(static_cast<int32_t>(range), edge), hi_wpos = min(static_cast<int32_t>(wrange), edge);
-    constexpr uint32_t hi_neg = 0x80000000u | range, hi_wneg = 0x80000000u | wrange;
+    constexpr uint32_t neg = 0x80000000u | range, wneg = 0x80000000u | wrange;
+    constexpr uint32_t nan_neg = FP32 ? 0xff800000u : 0xfff00000u;
     Real F0 = 0, F1 = 0, F2 = 0;   // sums without kMidScale and the factors shared by the node's bonds
 
-    auto term = [&](const NodeRec& r, auto wide) {
+    auto term = [&](const NodeRec& r, auto level) {
         if constexpr (FP32)
-            return slot_mid32<decltype(wide)::value>(r, X0, X1, X2, Uf0, Uf1, Uf2);
+            return slot_mid32<decltype(level)::value>(r, X0, X1, X2, Uf0, Uf1, Uf2);
         else
-            return slot_mid<decltype(wide)::value>(r, X0, X1, X2, U0, U1, U2, mc);
+            return slot_mid<decltype(level)::value>(r, X0, X1, X2, U0, U1, U2, mc);
     };
     // the factor of a slot that its node's bonds do not share
-    auto weight = [&](uint32_t idx, double k, Real L2) -> Real {
+    auto weight = [&](uint32_t idx, double k, Real L2, double fv) -> Real {
         if constexpr (CORR != kCorrNone) {
-            return corr_factor<CORR>(P, L2, static_cast<Real>(fvi + lw[idx]));
+            return corr_factor<CORR>(P, L2, static_cast<Real>(fv + lw[idx]));
         } else if constexpr (NODEW) {
             const double v = lw[idx];
             return static_cast<Real>(STIFF ? k * v : v);
@@ -669,127 +692,53 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
         F1 = __builtin_elementwise_fma(coef, m.y1, F1);
         F2 = __builtin_elementwise_fma(coef, m.y2, F2);
     };
-    auto one = [&](const NodeRec& r, uint32_t idx, double k, auto wide) {
-        const MidTerm<Real> m = term(r, wide);
-        add(WEIGHT ? m.coef * weight(idx, k, m.L2) : m.coef, m);
+    auto one = [&](const NodeRec& r, uint32_t idx, double k, auto level) {
+        const MidTerm<Real> m = term(r, level);
+        add(WEIGHT ? m.coef * weight(idx, k, m.L2, fvi) : m.coef, m);
         return m.hi;
-    };
-    auto ent_at = [&](int t) { return ent[static_cast<int64_t>(t) * kWave]; };
-    auto k_at = [&](int t) { return STIFF ? kslot[static_cast<int64_t>(t) * kWave] : double2{0.0, 0.0}; };
-    auto sold_at = [&](int t) {  // stretch state of a pair's slots (softened ones have one)
-        return laws ? *reinterpret_cast<const double2*>(A.smax + static_cast<int64_t>(t) * (2 * kWave) + 2 * lane)
-                    : double2{0.0, 0.0};
-    };
-    // The pairs [t, end), with a look at every slot that is at the decision edge, softened or
-    // beyond the long series (force: at all).  One slot at a time (two interleaved do not fit
-    // the registers), the next one's record in flight; a chunk's words are loaded together.
-    // With softened slots (EXT) the few tiles at a crack are the launch's tail.
-    auto rows_apart = [&](int t, int end, bool force) {
-        constexpr int C = STIFF ? 2 : 4;
-        uint32_t e2[C];
-        double2 k[C], sm[C];
-        NodeRec r;
-        int q = 0, nq = 0;  // slot of the chunk, slots of the chunk
-#pragma unroll 1
-        while (t < end) {
-            if (q == nq) {
-#pragma unroll
-                for (int u = 0; u < C; ++u) {
-                    e2[u] = t + u < end ? ent_at(t + u) : 0x80008000u;
-                    k[u] = k_at(t + u);
-                    sm[u] = sold_at(t + u);
-                }
-                q = 0;
-                nq = 2 * min(C, end - t);
-                r = staged_record(lrec, live_indices<true>(e2[0]) & 0xffffu);
-            }
-            const int h = q & 1;
-            const uint32_t e = h ? e2[0] >> 16 : e2[0] & 0xffffu;
-            const NodeRec rn = staged_record(lrec, h ? live_indices<true>(e2[1]) & 0xffffu : live_indices<true>(e2[0]) >> 16);
-            const MidTerm<Real> m = term(r, std::true_type{});
-            Real coef = m.coef;
-            const bool live = !(e & kEntBroken), soft = EXT && live && (e & kEntSoft) != 0;
-            const bool beyond = live && (m.hi >= hi_wpos || static_cast<uint32_t>(m.hi) >= hi_wneg || force);
-            if (__builtin_amdgcn_ballot_w64(beyond || soft) != 0 && (beyond || soft)) {
-                const int64_t ds = static_cast<int64_t>(t) * (2 * kWave) + 2 * lane + h;
-                auto exact = [&] { return stretch_exact_rec(r.p0, r.p1, r.p2, X0, X1, X2, U0, U1, U2); };
-                auto broke = [&] {  // irreversible; the pass is recorded
-                    A.ent[ds] = static_cast<uint16_t>(e | kEntBroken);
-                    A.bstep[ds] = static_cast<int32_t>(*A.step_base + A.step_local);
-                    coef = 0;
-                };
-                Real q;
-                double s = 0.0;  // the stretch, where damage laws may ask for it
-                if constexpr (FP32) {
-                    const float iL = __builtin_amdgcn_rsqf(m.L2);
-                    q = m.tq * (iL * iL);
-                    if (!(fabsf(m.d) < static_cast<float>(kWideRange32)))  // NaN: the squares overflowed
-                        coef = (1.0f / kMidScale32) * (iL * (1.0f - __builtin_amdgcn_rsqf(1.0f + q)));
-                    if (EXT) s = stretch_of(static_cast<double>(q));
-                } else if (EXT && fabs(m.d) < 4.0 * kWideRange) {
-                    // 1 + s = ((1 + d) / (1 - d))^(1/2) = (1 + d) (1 - d^2)^(-1/2): a softened
-                    // or overstretched slot within the series needs no root and no division
-                    const double d = 0.25 * m.d, z = d * d;
-                    double p = __builtin_fma(scalar_const(63.0 / 256.0), z, scalar_const(35.0 / 128.0));
-                    p = __builtin_fma(p, z, scalar_const(5.0 / 16.0));
-                    p = __builtin_fma(p, z, scalar_const(3.0 / 8.0));
-                    p = __builtin_fma(p, z, 0.5) * z;
-                    s = __builtin_fma(d, p, d + p);
-                    q = __builtin_fma(s, s, s + s);
-                } else {
-                    const double iL = rsq64<1>(m.L2);
-                    q = m.tq * (iL * iL);
-                    if (!(fabs(m.d) < 4.0 * kWideRange))
-                        coef = (1.0 / kMidScale) * (iL * one_minus_rsqrt1p(q, series_coef_sregs()));
-                    if (EXT) s = stretch_of(q);
-                }
-                const bool over = FP32 ? !(q < static_cast<Real>(q0f)) : !(q < static_cast<Real>(P.q0));
-                if constexpr (EXT) {
-                    if (BREAKS ? (over || soft) : soft) {
-                        bool brk, newly;
-                        const double share = bond_weight<MODE, FP32>(A, P, ds, static_cast<double>(q), s, (e & kEntNoFail) != 0, soft,
-                                                                     h ? sm[0].y : sm[0].x, brk, newly, exact);
-                        if (brk)
-                            broke();
-                        else if (newly)
-                            A.ent[ds] = static_cast<uint16_t>(e | kEntSoft);
-                        coef = share != 0.0 && !brk ? coef * static_cast<Real>(share) : Real(0);
-                    }
-                } else if (BREAKS && over && (FP32 ? q >= static_cast<Real>(q0f) : exact() >= P.s0)) {
-                    broke();
-                }
-            }
-            // a broken slot adds nothing, whatever its numbers
-            if (coef != Real(0)) add(WEIGHT ? coef * weight(live ? e & kEntIdx : 0, h ? k[0].y : k[0].x, m.L2) : coef, m);
-            r = rn;
-            ++q;
-            if (h) {
-                ++t;
-#pragma unroll
-                for (int u = 0; u + 1 < C; ++u) {
-                    e2[u] = e2[u + 1];
-                    k[u] = k[u + 1];
-                    sm[u] = sm[u + 1];
-                }
-                e2[C - 1] = 0x80008000u;
-            }
-        }
     };
     uint32_t en[B];  // the next block's entries and stiffness
     double2 kn[B];
     auto fetch = [&](int t) {
 #pragma unroll
         for (int u = 0; u < B; ++u) {
-            en[u] = ent_at(t + u);
-            if (STIFF) kn[u] = k_at(t + u);
+            en[u] = ent[static_cast<int64_t>(t + u) * kWave];
+            if (STIFF) kn[u] = kslot[static_cast<int64_t>(t + u) * kWave];
         }
     };
-    // The pairs [t, end), after fetch(t), block by block by the short or the long series, up to
-    // the first block that has a softened slot or one that the series does not cover; that
-    // block is taken back.
-    auto rows = [&](int t, int end, auto wide) {
-        const int32_t pos = wide ? hi_wpos : hi_pos;
-        const uint32_t neg = wide ? hi_wneg : hi_neg;
+    uint64_t todo = 0;  // slots of the window from pair `base` on that are settled after it
+    int base = 0;
+    // FP32: their sum in double precision, beside the others' single one (a softening law
+    // amplifies a force's rounding by up to 60)
+    double E0 = 0, E1 = 0, E2 = 0;
+    auto& S0 = [&]() -> auto& { if constexpr (FP32) return E0; else return F0; }();
+    auto& S1 = [&]() -> auto& { if constexpr (FP32) return E1; else return F1; }();
+    auto& S2 = [&]() -> auto& { if constexpr (FP32) return E2; else return F2; }();
+    // softened and not broken slots of a block
+    auto mark_soft = [&](const uint32_t (&e)[B], int t, int end) {
+        if (!laws) return;
+        uint32_t s[B], any = 0;
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            s[u] = t + u < end ? e[u] & ~(e[u] >> 2) & 0x20002000u : 0u;
+            any |= s[u];
+        }
+        if (__builtin_amdgcn_ballot_w64(any != 0) == 0) return;
+        uint32_t bits = 0;
+#pragma unroll
+        for (int u = 0; u < B; ++u) bits |= ((s[u] >> 13 & 1u) | (s[u] >> 28 & 2u)) << (2 * u);
+        todo |= static_cast<uint64_t>(bits) << (2 * (t - base));
+    };
+    // The pairs [t, end), after fetch(t), block by block at level 0 or 1, up to the first block with
+    // a slot that the level does not cover; that block is taken back, and `need` is the level
+    // that covers it.  ZONES: level 1 with the decision edge ignored on slots that may not break
+    // (three more operations a slot): where a zone's bonds are over it, its tiles stay there.
+    int need = 0;
+    constexpr int kZones = 3;
+    auto rows = [&](int t, int end, auto level) {
+        constexpr bool wide = decltype(level)::value > 0, ZONES = decltype(level)::value == kZones;
+        using Level = std::integral_constant<int, wide ? 1 : 0>;
+        const int32_t pos = min(static_cast<int32_t>(wide ? wrange : range), edge);
 #pragma unroll 1
         for (; t < end; t += B) {
             uint32_t e[B];
@@ -800,13 +749,12 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 if (STIFF) k[u] = kn[u];
             }
             fetch(t + B);
-            if constexpr (EXT) {
-                uint32_t soft = 0;  // softened and not broken
-#pragma unroll
-                for (int u = 0; u < B; ++u) soft |= t + u < end ? e[u] & ~(e[u] >> 2) : 0u;
-                if (__builtin_amdgcn_ballot_w64((soft & 0x20002000u) != 0) != 0) return t;
-            }
-            const Real S0 = F0, S1 = F1, S2 = F2;
+            if constexpr (EXT) mark_soft(e, t, end);
+            auto high = [&](int32_t hi, uint32_t shifted) {  // shifted: the no-failure bit in the sign's place
+                if constexpr (!ZONES) return hi;
+                return __builtin_elementwise_sub_sat(hi, (static_cast<int32_t>(wrange) - pos) & (static_cast<int32_t>(shifted) >> 31));
+            };
+            const Real B0 = F0, B1 = F1, B2 = F2;
             int32_t himax = std::numeric_limits<int32_t>::min();  // of the block's d: the largest high word
             uint32_t himin = 0;  // and the one furthest below zero (sign bit set: large)
             uint32_t v = live_indices<EXT>(e[0]);
@@ -818,35 +766,225 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 const NodeRec rb = staged_record(lrec, ib);
                 if (u + 1 < B) v = live_indices<EXT>(t + u + 1 < end ? e[u + 1] : 0x80008000u);
                 __builtin_amdgcn_sched_barrier(0);
-                const int32_t ha = one(ra, ia, STIFF ? k[u].x : 0.0, wide);
+                const int32_t ha = one(ra, ia, STIFF ? k[u].x : 0.0, Level{});
                 if (u + 1 < B) ra = staged_record(lrec, v & 0xffffu);
                 __builtin_amdgcn_sched_barrier(0);
-                const int32_t hb = one(rb, ib, STIFF ? k[u].y : 0.0, wide);
-                himax = max(max(himax, ha), hb);
+                const int32_t hb = one(rb, ib, STIFF ? k[u].y : 0.0, Level{});
+                himax = max(max(himax, high(ha, e[u] << 17)), high(hb, e[u] << 1));
                 himin = max(max(himin, static_cast<uint32_t>(ha)), static_cast<uint32_t>(hb));
             }
-            if (__builtin_amdgcn_ballot_w64(himax >= pos || himin >= neg) != 0) {
-                F0 = S0;
-                F1 = S1;
-                F2 = S2;
+            if (__builtin_amdgcn_ballot_w64(himax >= pos || himin >= (wide ? wneg : neg)) != 0) {
+                F0 = B0;
+                F1 = B1;
+                F2 = B2;
+                need = __builtin_amdgcn_ballot_w64(himax >= min(static_cast<int32_t>(wrange), edge) || himin >= wneg) != 0 ? 2 : 1;
+                if constexpr (EXT && !ZONES && BREAKS) {
+                    uint32_t zone = 0;
+#pragma unroll
+                    for (int u = 0; u < B; ++u) zone |= e[u] & 0x40004000u;
+                    if (need == 2 && __builtin_amdgcn_ballot_w64(zone != 0) != 0) need = kZones;
+                }
                 return t;
             }
         }
-        return end;
+        return t;
     };
-    auto share_rows = [&](int2 pr) {  // after fetch(pr.x)
-        int t = rows(pr.x, pr.y, std::false_type{});
+    // One block or more from pair t on at level 2, one slot at a time (two interleaved do not fit
+    // the registers), as long as blocks have slots beyond the long series.
+    auto rows_general = [&](int t, int end) {
 #pragma unroll 1
-        while (t < pr.y) {  // once the short series does not do, the long one for the rest
-            fetch(t);
-            t = rows(t, pr.y, std::true_type{});
+        for (bool on = true; on && t < end; t += B) {
+            uint32_t e[B];
+            double2 k[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                e[u] = en[u];
+                if (STIFF) k[u] = kn[u];
+            }
+            fetch(t + B);
+            if constexpr (EXT) mark_soft(e, t, end);
+            int32_t himax = std::numeric_limits<int32_t>::min();
+            uint32_t himin = 0, bits = 0;
+#pragma unroll 1
+            for (int u = 0; u < 2 * B; ++u) {
+                const bool in = t + (u >> 1) < end;
+                const uint32_t h = in ? e[0] & 0xffffu : kEntBroken;
+                const double kh = STIFF ? k[0].x : 0.0;
+                // the next slot's entry and stiffness
+                if (u & 1) {
+#pragma unroll
+                    for (int w = 0; w + 1 < B; ++w) {
+                        e[w] = e[w + 1];
+                        if (STIFF) k[w] = k[w + 1];
+                    }
+                } else {
+                    e[0] >>= 16;
+                    if (STIFF) k[0].x = k[0].y;
+                }
+                const bool live = !(h & (EXT ? kEntBroken | kEntSoft : kEntBroken));
+                const uint32_t idx = live ? h & kEntIdx : 0u;
+                const MidTerm<Real> m = term(staged_record(lrec, idx), std::integral_constant<int, 2>{});
+                const bool over = BREAKS && live && !(EXT && (h & kEntNoFail)) &&
+                                  (m.hi >= edge || static_cast<uint32_t>(m.hi) >= nan_neg);
+                bits |= over ? 1u << u : 0u;
+                // a slot that is not live adds nothing, whatever its numbers
+                if (live && !over) add(WEIGHT ? m.coef * weight(idx, kh, m.L2, fvi) : m.coef, m);
+                const int32_t hi = live ? m.hi : 0;
+                himax = max(himax, hi);
+                himin = max(himin, static_cast<uint32_t>(hi));
+            }
+            todo |= static_cast<uint64_t>(bits) << (2 * (t - base));
+            on = __builtin_amdgcn_ballot_w64(himax >= static_cast<int32_t>(wrange) || himin >= wneg) != 0;
+        }
+        return t;
+    };
+    // The marked slots of the window: a break candidate is decided on its exact stretch, a
+    // softened one takes the weight of its damage state.  They are few and lie in few lanes (at a
+    // crack 9 of a wavefront's 2000, up to 7 in one lane), so they are listed and taken 64 at
+    // a time, one a lane whoever owns it; each owner then collects its sums in slot order.
+    // A slot of each lane in turn took a pass of 400 instructions for every slot of the
+    // fullest lane: 117 x 33 x 33 nodes with a grown crack 61.8 us a step, listed 43.4.
+    auto settle = [&] {
+        if (__builtin_amdgcn_ballot_w64(todo != 0) == 0) return false;
+        const int count = __builtin_popcountll(todo);
+        int upto = count;  // marked slots of the lanes up to this one
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int o = __shfl_up(upto, d);
+            upto += lane >= d ? o : 0;
+        }
+        const int total = __builtin_amdgcn_readlane(upto, kWave - 1);
+        int at = upto - count;  // the lane's next slot in the list
+#pragma unroll 1
+        for (int i0 = 0; i0 < total; i0 += kWave) {
+            {
+                uint64_t left = todo;
+                int i = at;
+#pragma unroll 1
+                while (left != 0 && i < i0 + kWave) {
+                    litem[i++ - i0] = static_cast<uint16_t>(lane | __builtin_ctzll(left) << 8);
+                    left &= left - 1;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            const bool on = i0 + lane < total;
+            const uint32_t item = on ? litem[lane] : 0u;
+            const int owner = item & 63u;
+            const uint32_t bit = item >> 8;
+            const int64_t ds = static_cast<int64_t>(base + static_cast<int>(bit >> 1)) * (2 * kWave) + 2 * owner + (bit & 1u);
+            const uint32_t word = A.ent[ds];
+            const double sold = laws ? A.smax[ds] : 0.0, k = STIFF ? A.kslot[ds] : 0.0;
+            const double x0 = __shfl(X0, owner), x1 = __shfl(X1, owner), x2 = __shfl(X2, owner);
+            const double fv = CORR ? __shfl(fvi, owner) : 0.0;
+            const uint32_t e = on ? word : kEntBroken;
+            const bool live = !(e & kEntBroken), soft = EXT && live && (e & kEntSoft) != 0;
+            const uint32_t idx = live ? e & kEntIdx : 0u;
+            const NodeRec r = staged_record(lrec, idx);
+            MidTerm<Real> m;
+            double u0 = 0.0, u1 = 0.0, u2 = 0.0;
+            if constexpr (FP32) {
+                m = slot_mid32<2>(r, x0, x1, x2, __shfl(Uf0, owner), __shfl(Uf1, owner), __shfl(Uf2, owner));
+            } else {
+                u0 = __shfl(U0, owner), u1 = __shfl(U1, owner), u2 = __shfl(U2, owner);
+                m = slot_mid<2>(r, x0, x1, x2, u0, u1, u2, mc);
+            }
+            Real q = m.q;
+            double coef = live ? static_cast<double>(m.coef) : 0.0;
+            auto exact = [&] { return stretch_exact_rec(r.p0, r.p1, r.p2, x0, x1, x2, u0, u1, u2); };  // FP64 build
+            double s = 0.0;  // the stretch, where damage laws may ask for it
+            if constexpr (EXT) {
+                if constexpr (FP32) {
+                    s = stretch_of(static_cast<double>(q));
+                } else if (fabs(m.d) < 4.0 * kWideRange) {
+                    // 1 + s = ((1 + d) / (1 - d))^(1/2) = (1 + d) (1 - d^2)^(-1/2): a slot within
+                    // the series needs no root and no division
+                    const double d = 0.25 * m.d, z = d * d;
+                    double p = __builtin_fma(scalar_const(63.0 / 256.0), z, scalar_const(35.0 / 128.0));
+                    p = __builtin_fma(p, z, scalar_const(5.0 / 16.0));
+                    p = __builtin_fma(p, z, scalar_const(3.0 / 8.0));
+                    p = __builtin_fma(p, z, 0.5) * z;
+                    s = __builtin_fma(d, p, d + p);
+                    q = __builtin_fma(s, s, s + s);
+                } else {
+                    s = stretch_of(q);
+                }
+            }
+            const bool over = !(q < (FP32 ? static_cast<Real>(q0f) : static_cast<Real>(P.q0)));
+            BondWeight bw;
+            if constexpr (EXT) {
+                if (live && (BREAKS ? (over || soft) : soft))
+                    bw = bond_weight<MODE, FP32>(A, P, ds, static_cast<double>(q), s, (e & kEntNoFail) != 0, soft, sold, exact);
+            } else if (BREAKS && live && over) {
+                bw.broke = FP32 ? q >= static_cast<Real>(q0f) : exact() >= P.s0;
+            }
+            if (bw.broke) {  // irreversible; the pass is recorded
+                A.ent[ds] = static_cast<uint16_t>(e | kEntBroken);
+                A.bstep[ds] = static_cast<int32_t>(*A.step_base + A.step_local);
+            } else if (EXT && bw.newly_soft) {
+                A.ent[ds] = static_cast<uint16_t>(e | kEntSoft);
+            }
+            if (EXT && bw.grew) A.smax[ds] = bw.smax;
+            coef = bw.broke || bw.share == 0.0 ? 0.0 : coef * bw.share;
+            double f0 = 0.0, f1 = 0.0, f2 = 0.0;
+            if (coef != 0.0) {
+                if (WEIGHT) coef *= static_cast<double>(weight(idx, k, m.L2, fv));
+                f0 = coef * static_cast<double>(m.y0);
+                f1 = coef * static_cast<double>(m.y1);
+                f2 = coef * static_cast<double>(m.y2);
+            }
+            // back to the owners
+#pragma unroll 1
+            for (;;) {
+                const bool mine = todo != 0 && at < i0 + kWave;
+                if (__builtin_amdgcn_ballot_w64(mine) == 0) break;
+                const double g0 = __shfl(f0, at - i0), g1 = __shfl(f1, at - i0), g2 = __shfl(f2, at - i0);
+                S0 += mine ? g0 : 0.0;
+                S1 += mine ? g1 : 0.0;
+                S2 += mine ? g2 : 0.0;
+                if (mine) {
+                    todo &= todo - 1;
+                    ++at;
+                }
+            }
+        }
+        return true;
+    };
+    // The sentinel's term is exactly zero as long as its distance does not round; a node beyond
+    // that takes its slots at level 2 from the start.
+    constexpr double kFar = FP32 ? 1e15 : 1e80;
+    auto near = [&](double x) { return fabs(x) < kFar; };
+    const bool moderate = near(X0) && near(X1) && near(X2) && (FP32 ? near(Uf0) && near(Uf1) && near(Uf2) : near(U0) && near(U1) && near(U2));
+    const int first = __builtin_amdgcn_ballot_w64(!moderate) != 0 ? 2 : 0;
+    auto share_rows = [&](int2 pr) {  // after fetch(pr.x)
+        int t = pr.x, level = first, usual = first > 1 ? 2 : 1;
+        base = pr.x;
+#pragma unroll 1
+        for (;;) {
+            const int stop = min(pr.y, base + 32);
+            if (level == 2) {
+                t = rows_general(t, stop);
+                level = usual;
+            } else {
+                if (level == 0)
+                    t = rows(t, stop, std::integral_constant<int, 0>{});
+                else if (EXT && BREAKS && level == kZones)
+                    t = rows(t, stop, std::integral_constant<int, kZones>{});
+                else
+                    t = rows(t, stop, std::integral_constant<int, 1>{});
+                if (t < stop) {
+                    level = need;
+                    if (EXT && level == kZones) usual = kZones;
+                    fetch(t);
+                }
+            }
+            if (t < stop) continue;
+            const bool settled = settle();
+            base = t;
             if (t >= pr.y) break;
-            const int to = EXT ? pr.y : min(t + B, pr.y);  // softened slots are seldom alone
-            rows_apart(t, to, false);
-            t = to;
+            if (settled) fetch(t);  // (not kept in registers meanwhile)
         }
     };
-    auto stage_phase = [&](int ph) {  // a later phase, or one staged again
+    auto stage_phase = [&](int ph) {  // a later phase
         const int2 pd = phases[T.phase + ph];
         __syncthreads();  // the records before are no longer read
         stage_records(A.rec_in, list + pd.x, pd.y, tl.wv, lane, lrec);
@@ -865,21 +1003,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
         if (pr.x < pr.y) share_rows(pr);
         __builtin_amdgcn_s_setprio(3);
     }
-    // squares beyond the range of their type leave no finite sum: every slot in the general form
-    const bool unsound = !(__builtin_isfinite(F0) && __builtin_isfinite(F1) && __builtin_isfinite(F2));
-    if (T.nphases <= 1 ? __builtin_amdgcn_ballot_w64(unsound) != 0 : __syncthreads_or(unsound) != 0) {
-        F0 = F1 = F2 = 0;
-#pragma unroll 1
-        for (int ph = 0; ph < T.nphases; ++ph) {
-            if (T.nphases > 1) {
-                stage_phase(ph);
-                tile_staged();
-            }
-            pr = tl.pairs(T, segs, ph);
-            if (pr.x < pr.y) rows_apart(pr.x, pr.y, true);
-        }
-    }
-    double G[3] = {F0, F1, F2};
+    double G[3] = {F0 + E0, F1 + E1, F2 + E2};
     tile_reduce(tl, reinterpret_cast<double*>(lds), G);
     if (tl.sub > 0 || !tl.has) return;
     const double share = (FP32 ? kMidScale32 : kMidScale) *
@@ -922,7 +1046,7 @@ template <bool FP32, int MODE, bool STIFF, bool VOLN, bool KNODE, bool EXT, int 
 hipError_t launch_staged_m(const StepArgs& a, hipStream_t s)
 {
     auto* kernel = &step_staged<FP32, MODE, STIFF, VOLN, KNODE, EXT, CORR>;
-    const size_t bytes = tile_lds(a.stage_max, 48 + (VOLN || KNODE || CORR != kCorrNone ? 8 : 0));
+    const size_t bytes = tile_lds(a.stage_max, 48 + (VOLN || KNODE || CORR != kCorrNone ? 8 : 0), kTileWaves * kWave * sizeof(uint16_t));
     const hipError_t e = tile_room(reinterpret_cast<const void*>(kernel), bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.ntiles)), dim3(kTileWaves * kWave), bytes, s, a, a.tiles,

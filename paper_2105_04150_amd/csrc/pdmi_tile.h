@@ -69,10 +69,10 @@ __device__ __forceinline__ void tile_reduce(const TileLane& tl, double* lds, dou
 }
 
 // Dynamic LDS of a tile kernel with `per` bytes a record: the phase's records and the
-// sentinel, at least the partial sums of tile_reduce.
-inline size_t tile_lds(int32_t stage_max, size_t per)
+// sentinel and `more` bytes, at least the partial sums of tile_reduce.
+inline size_t tile_lds(int32_t stage_max, size_t per, size_t more = 0)
 {
-    const size_t b = (static_cast<size_t>(stage_max) + 1) * per, red = kTileWaves * 3 * kWave * sizeof(double);
+    const size_t b = (static_cast<size_t>(stage_max) + 1) * per + more, red = kTileWaves * 3 * kWave * sizeof(double);
     return b > red ? b : red;
 }
 
@@ -156,12 +156,12 @@ __device__ __forceinline__ double2 sentinel_part(int j)
 
 // Record indices of a lane's row pair from its two entries (low and high half); broken and
 // padding entries (sign bit) become record 0, the sentinel.  FLAGS: entries may carry the
-// softened and no-failure bits.
+// no-failure bit and the softened one, which leads to the sentinel too.
 typedef short short2v __attribute__((ext_vector_type(2)));
 template <bool FLAGS>
 __device__ __forceinline__ uint32_t live_indices(uint32_t e2)
 {
-    if (FLAGS) e2 &= 0x8fff8fffu;
+    if (FLAGS) e2 = (e2 | (e2 & 0x20002000u) << 2) & 0x8fff8fffu;
     short2v v;
     __builtin_memcpy(&v, &e2, sizeof v);
     const short2v zero = {0, 0};

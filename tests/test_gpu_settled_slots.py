@@ -1,0 +1,101 @@
+"""Slots that the staged kernels settle one by one (softened, over the threshold, beyond the
+series), against the sliced kernel on the same state: shares of more than 32 row pairs, blocks that
+change level within a share, zones, and nodes whose bonds are all broken."""
+import numpy as np
+import pytest
+
+from parity import say
+
+pytestmark = pytest.mark.gpu
+
+DX = 1.0e-3
+LAW = ((2.3e-4, 2.42e-4, 1.45e-3), (1.0, 0.25, 0.0))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    from paper_2105_04150_amd import _binding as B
+    B.load()
+
+
+def _lattice(dims):
+    k, j, i = np.meshgrid(*[np.arange(d) for d in dims[::-1]], indexing="ij")
+    return DX * np.stack([i.ravel(), j.ravel(), k.ravel()], axis=1).astype(np.float64)
+
+
+def _state(dims, peak):
+    """Stretch growing from zero at one end of x to `peak` at the other, and a random part."""
+    rng = np.random.default_rng(11)
+    x = _lattice(dims)
+    u = np.zeros_like(x)
+    u[:, 0] = peak * x[:, 0] ** 2 / (2.0 * x[:, 0].max())
+    u += 0.1 * peak * DX * rng.uniform(-1, 1, x.shape)
+    return x, u
+
+
+def _run(mapping, x, u, m, law, zones, s0, steps, field):
+    import paper_2105_04150_amd as pd
+    with pd.Simulation(0, pd.PD_FP64) as sim:
+        sim.set_mapping(mapping)
+        sim.build_family(x, m * DX)
+        sim.set_integrator("euler_cromer", 1.0e-8)
+        sim.set_material(2400.0, 1.0e19, s0, 0.0, DX ** 3)
+        if field:
+            row_ptr, _ = sim.family()
+            sim.set_bond_stiffness(1.0e19 * np.ones(row_ptr[-1]))
+        if law:
+            sim.set_damage_law(0, *LAW)
+        if zones:
+            sim.set_no_fail(np.nonzero(x[:, 1] < 1.5 * DX)[0])
+        sim.set_state(u=u)
+        f = [sim.force()]
+        sim.step(steps)
+        f.append(sim.force())
+        return f, sim.u(), sim.broken().astype(bool), sim.max_stretch() if law else None
+
+
+@pytest.mark.parametrize("dims,m", [((24, 7, 6), 3.015), ((14, 13, 12), 8.015)])
+@pytest.mark.parametrize("law,zones,s0,peak,field", [
+    (True, False, 1.0, 4.0e-4, False),
+    (True, True, 1.0, 3.0e-3, False),
+    (True, True, 1.0, 3.0e-3, True),
+    (False, True, 5.0e-3, 2.0e-2, False),   # zone bonds far beyond the threshold
+    (False, False, 0.2, 0.6, False),        # both series and the closed form, some break
+    (False, False, 1.0e-3, 1.05e-3, True),
+])
+def test_settled_slots_match_the_sliced_kernel(dims, m, law, zones, s0, peak, field):
+    x, u = _state(dims, peak)
+    steps = 6
+    a, b = (_run(k, x, u, m, law, zones, s0, steps, field) for k in ("staged", "sliced"))
+    say(f"[settled] {dims} m {m} law {law} zones {zones}: broken {a[2].mean():.3f}"
+        + (f" softened {(a[3] > 0).mean():.3f}" if law else ""))
+    assert np.array_equal(a[2], b[2])
+    # both kernels: the rounding of |y|^2 - |xi|^2, 4 units of 2^-52 over the smallest stretch that counts
+    tol = 1e-13 + 8 * 2.0 ** -52 / min(peak, 2.3e-4)
+    for fa, fb in zip(a[0], b[0]):
+        assert np.abs(fa - fb).max() <= tol * np.abs(fb).max()
+    assert np.abs(a[1] - b[1]).max() <= 1e-13 * np.abs(b[1]).max()
+    if law:
+        assert np.array_equal(a[3] > 0, b[3] > 0)
+        assert np.abs(a[3] - b[3]).max() <= 1e-12
+
+
+@pytest.mark.parametrize("build,far", [("f64", 1.0e99), ("f64", 1.0e120), ("f32", 1.0e18)])
+def test_a_free_node_feels_nothing_wherever_it_is(build, far):
+    """A node whose bonds are all broken has no force, however far it has gone."""
+    import paper_2105_04150_amd as pd
+    x = _lattice((9, 8, 7))
+    n, free = len(x), 250
+    with pd.Simulation(0, pd.PD_FP32 if build == "f32" else pd.PD_FP64) as sim:
+        sim.set_mapping("staged")
+        sim.build_family(x, 3.015 * DX)
+        sim.set_integrator("euler_cromer", 1.0e-9)
+        sim.set_material(2400.0, 1.0e20, 10.0, 0.0, DX ** 3)
+        rp, col = sim.family()
+        row = np.repeat(np.arange(n), np.diff(rp))
+        u = 1e-3 * x
+        u[free] = far
+        sim.set_state(u=u, broken=((row == free) | (col == free)).astype(np.uint8))
+        f = sim.force()
+    assert not f[free].any()
+    assert np.isfinite(f).all() and np.abs(f).max() > 0.0
