@@ -692,11 +692,6 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
         F1 = __builtin_elementwise_fma(coef, m.y1, F1);
         F2 = __builtin_elementwise_fma(coef, m.y2, F2);
     };
-    auto one = [&](const NodeRec& r, uint32_t idx, double k, auto level) {
-        const MidTerm<Real> m = term(r, level);
-        add(WEIGHT ? m.coef * weight(idx, k, m.L2, fvi) : m.coef, m);
-        return m.hi;
-    };
     uint32_t en[B];  // the next block's entries and stiffness
     double2 kn[B];
     auto fetch = [&](int t) {
@@ -731,14 +726,15 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     };
     // The pairs [t, end), after fetch(t), block by block at level 0 or 1, up to the first block with
     // a slot that the level does not cover; that block is taken back, and `need` is the level
-    // that covers it.  ZONES: level 1 with the decision edge ignored on slots that may not break
-    // (three more operations a slot): where a zone's bonds are over it, its tiles stay there.
+    // that covers it.  kMark: level 1 with the slots at the decision edge left out and marked
+    // (eight more operations a slot), also the level of zone bonds over the edge, which stay
+    // in: once a share needs it, it keeps it.
     int need = 0;
-    constexpr int kZones = 3;
+    constexpr int kMark = 3;
     auto rows = [&](int t, int end, auto level) {
-        constexpr bool wide = decltype(level)::value > 0, ZONES = decltype(level)::value == kZones;
+        constexpr bool wide = decltype(level)::value > 0, MARK = decltype(level)::value == kMark;
         using Level = std::integral_constant<int, wide ? 1 : 0>;
-        const int32_t pos = min(static_cast<int32_t>(wide ? wrange : range), edge);
+        const int32_t pos = MARK ? static_cast<int32_t>(wrange) : min(static_cast<int32_t>(wide ? wrange : range), edge);
 #pragma unroll 1
         for (; t < end; t += B) {
             uint32_t e[B];
@@ -750,13 +746,22 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
             }
             fetch(t + B);
             if constexpr (EXT) mark_soft(e, t, end);
-            auto high = [&](int32_t hi, uint32_t shifted) {  // shifted: the no-failure bit in the sign's place
-                if constexpr (!ZONES) return hi;
-                return __builtin_elementwise_sub_sat(hi, (static_cast<int32_t>(wrange) - pos) & (static_cast<int32_t>(shifted) >> 31));
-            };
             const Real B0 = F0, B1 = F1, B2 = F2;
             int32_t himax = std::numeric_limits<int32_t>::min();  // of the block's d: the largest high word
             uint32_t himin = 0;  // and the one furthest below zero (sign bit set: large)
+            uint32_t bits = 0;
+            auto one = [&](const NodeRec& r, uint32_t idx, double kslot, uint32_t word, int bit) {
+                const MidTerm<Real> m = term(r, Level{});
+                Real coef = WEIGHT ? m.coef * weight(idx, kslot, m.L2, fvi) : m.coef;
+                if constexpr (MARK) {
+                    const bool over = m.hi >= edge && (word & (EXT ? kEntBroken | kEntSoft | kEntNoFail : kEntBroken)) == 0;
+                    coef = over ? Real(0) : coef;
+                    bits |= over ? 1u << bit : 0u;
+                }
+                add(coef, m);
+                himax = max(himax, m.hi);
+                himin = max(himin, static_cast<uint32_t>(m.hi));
+            };
             uint32_t v = live_indices<EXT>(e[0]);
             NodeRec ra = staged_record(lrec, v & 0xffffu);
 #pragma unroll
@@ -766,26 +771,21 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 const NodeRec rb = staged_record(lrec, ib);
                 if (u + 1 < B) v = live_indices<EXT>(t + u + 1 < end ? e[u + 1] : 0x80008000u);
                 __builtin_amdgcn_sched_barrier(0);
-                const int32_t ha = one(ra, ia, STIFF ? k[u].x : 0.0, Level{});
+                one(ra, ia, STIFF ? k[u].x : 0.0, e[u], 2 * u);
                 if (u + 1 < B) ra = staged_record(lrec, v & 0xffffu);
                 __builtin_amdgcn_sched_barrier(0);
-                const int32_t hb = one(rb, ib, STIFF ? k[u].y : 0.0, Level{});
-                himax = max(max(himax, high(ha, e[u] << 17)), high(hb, e[u] << 1));
-                himin = max(max(himin, static_cast<uint32_t>(ha)), static_cast<uint32_t>(hb));
+                one(rb, ib, STIFF ? k[u].y : 0.0, e[u] >> 16, 2 * u + 1);
             }
             if (__builtin_amdgcn_ballot_w64(himax >= pos || himin >= (wide ? wneg : neg)) != 0) {
                 F0 = B0;
                 F1 = B1;
                 F2 = B2;
-                need = __builtin_amdgcn_ballot_w64(himax >= min(static_cast<int32_t>(wrange), edge) || himin >= wneg) != 0 ? 2 : 1;
-                if constexpr (EXT && !ZONES && BREAKS) {
-                    uint32_t zone = 0;
-#pragma unroll
-                    for (int u = 0; u < B; ++u) zone |= e[u] & 0x40004000u;
-                    if (need == 2 && __builtin_amdgcn_ballot_w64(zone != 0) != 0) need = kZones;
-                }
+                need = __builtin_amdgcn_ballot_w64(himax >= static_cast<int32_t>(wrange) || himin >= wneg) != 0 ? 2
+                       : __builtin_amdgcn_ballot_w64(himax >= edge) != 0                                        ? kMark
+                                                                                                                : 1;
                 return t;
             }
+            if constexpr (MARK) todo |= static_cast<uint64_t>(bits) << (2 * (t - base));
         }
         return t;
     };
@@ -967,13 +967,13 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
             } else {
                 if (level == 0)
                     t = rows(t, stop, std::integral_constant<int, 0>{});
-                else if (EXT && BREAKS && level == kZones)
-                    t = rows(t, stop, std::integral_constant<int, kZones>{});
+                else if (BREAKS && level == kMark)
+                    t = rows(t, stop, std::integral_constant<int, kMark>{});
                 else
                     t = rows(t, stop, std::integral_constant<int, 1>{});
                 if (t < stop) {
                     level = need;
-                    if (EXT && level == kZones) usual = kZones;
+                    if (level == kMark) usual = kMark;
                     fetch(t);
                 }
             }
