@@ -499,18 +499,15 @@ static StageRoom stage_room(const pd_ctx* ctx)
 }
 
 // Slices of a tile, from the slices of all instances: large tiles stage each record for more
-// bonds, but a launch wants about three a CU.  us/step with 4, 2, 1 slices a tile: 1M nodes
-// (15625 slices) 183, 206, 276; 262144 nodes 48, 51, 63; 125000 nodes 35.5, 34.4, 38; 50000
-// nodes 18.9, 18.2, 21; 1000 nodes 14.9, 9.8, 7.5.  With damage laws one: the softened bonds
-// gather in few tiles, whose slot-by-slot work is the launch's tail (127k nodes with a grown
-// crack: 67, 81, 107 us a step with 1, 2, 4).  The mapping's lanes have no say in it.
+// bonds, but a launch wants about two a CU.  us/step with 4, 2, 1 slices a tile: 1M nodes
+// (15625 slices) 194, 220, 291; 262144 nodes 52.9, 56.0, 69.5; 125000 nodes 36.0, 37.1, 41.7; 50000
+// nodes 17.6, 17.2, 18.6; 1000 nodes 16.1, 10.6, 8.1.  Damage laws follow the same rule (1M nodes,
+// nothing softened: 204, 227, 307; 127k nodes with a grown crack, 2 and 1: 39.1, 45.0).  The
+// mapping's lanes have no say in it.
 static int64_t tile_slices(const pd_ctx* ctx)
 {
     int64_t nsl = 0;
-    for (const Inst& I : ctx->inst) {
-        if (!I.laws.empty()) return 1;
-        nsl += (I.n + kWave - 1) / kWave;
-    }
+    for (const Inst& I : ctx->inst) nsl += (I.n + kWave - 1) / kWave;
     return nsl >= 3072 ? kTileSlices : nsl >= 512 ? 2 : 1;
 }
 
