@@ -326,49 +326,68 @@ static void reached(const Inst& I, int64_t slice, int64_t nsl, std::vector<uint8
     for (int32_t j : nodes) seen[j] = 0;
 }
 
+// A tile before it is laid out: its slices and the records it stages.
+struct Part {
+    int64_t slice = 0, nsl = 0;
+    std::vector<int32_t> nodes;  // user nodes reached, ascending
+    int32_t nphase = 0, per = 0;
+    std::vector<int32_t> at;     // record index of every one in its phase
+    std::vector<int32_t> n;      // records per phase
+    std::vector<int32_t> pairs;  // per phase and slice of the tile
+};
+
+// Two workgroups a CU hide each other's staging, so a part of more than `least` slices whose
+// records do not fit a CU's LDS twice is cut in two, and so on.
+static void cut_part(const Inst& I, int64_t slice, int64_t nsl, int64_t least, int64_t two, std::vector<uint8_t>& seen,
+                     std::vector<Part>& out)
+{
+    Part p;
+    p.slice = slice;
+    p.nsl = nsl;
+    reached(I, slice, nsl, seen, p.nodes);
+    if (nsl > least && static_cast<int64_t>(p.nodes.size()) > two) {
+        const int64_t left = (nsl + 1) / 2;
+        cut_part(I, slice, left, least, two, seen, out);
+        cut_part(I, slice + left, nsl - left, least, two, seen, out);
+    } else {
+        out.push_back(std::move(p));
+    }
+}
+
 // Staged layout of one instance: tiles of up to `group` consecutive slices.  The nodes that
-// a tile's bonds reach are cut into phases of at most room.one records (one phase unless
-// the families are very large); each lane's slots of a phase, in ascending neighbour order,
-// fill its slice's row pairs.  Fills the tile, phase and segment tables, dslot_user and
-// ent_idx (index of the slot's record in its phase, from 1); returns the slot count.
+// a tile's bonds reach are cut into phases (one unless the families are very large); each
+// lane's slots of a phase, in ascending neighbour order, fill its slice's row pairs.  Fills
+// the tile, phase and segment tables, dslot_user and ent_idx (index of the slot's record in
+// its phase, from 1); returns the slot count.
 static int64_t build_staged(Inst& I, int64_t group, const StageRoom& room, const std::vector<uint8_t>& bank)
 {
-    struct Part {
-        int64_t slice = 0, nsl = 0;
-        std::vector<int32_t> nodes;  // user nodes reached, ascending
-        int32_t nphase = 0, per = 0;
-        std::vector<int32_t> at;     // record index of every one in its phase
-        std::vector<int32_t> n;      // records per phase
-        std::vector<int32_t> pairs;  // per phase and slice of the tile
-    };
     const int64_t ng = (I.nslices + group - 1) / group;
     std::vector<std::vector<Part>> parts(static_cast<size_t>(ng));
-    parallel_for(ng, [&](int64_t g0, int64_t g1) {
-        std::vector<uint8_t> seen(static_cast<size_t>(I.n), 0);
-        for (int64_t g = g0; g < g1; ++g) {
-            std::vector<Part>& out = parts[g];
-            out.emplace_back();
-            out[0].slice = g * group;
-            out[0].nsl = std::min(group, I.nslices - g * group);
-            reached(I, out[0].slice, out[0].nsl, seen, out[0].nodes);
-            // Two workgroups a CU hide each other's staging: a tile of three or four slices that
-            // does not fit twice is cut in two (node weights on the 1M-node cube: 119 us, uncut
-            // 166).  Two slices stay together (horizon 5.015: 185 us, cut 208).
-            if (out[0].nsl > 2 && static_cast<int64_t>(out[0].nodes.size()) > room.two) {
-                Part a, b;
-                a.slice = out[0].slice;
-                a.nsl = (out[0].nsl + 1) / 2;
-                b.slice = a.slice + a.nsl;
-                b.nsl = out[0].nsl - a.nsl;
-                reached(I, a.slice, a.nsl, seen, a.nodes);
-                reached(I, b.slice, b.nsl, seen, b.nodes);
-                out.clear();
-                out.push_back(std::move(a));
-                out.push_back(std::move(b));
+    // Tiles of one slice, if nearly all of them then fit twice and the others do in two phases
+    // (1M nodes at horizon 5.015: 785 us a step, two slices a tile and one tile a CU 885), else of two
+    // at least, with one tile a CU where they do not fit twice (125000 nodes at 8.015: 450, cut
+    // 464).  A problem whose tiles have a CU each has no use for room for two (15625 nodes at 5.015:
+    // 20 us in one phase, 23 in two).
+    int64_t phase = group > 1 ? room.two : room.one;
+    for (int64_t least : {1, 2}) {
+        std::atomic<int64_t> tiles{0}, over{0};
+        parallel_for(ng, [&](int64_t g0, int64_t g1) {
+            std::vector<uint8_t> seen(static_cast<size_t>(I.n), 0);
+            for (int64_t g = g0; g < g1; ++g) {
+                parts[g].clear();
+                cut_part(I, g * group, std::min(group, I.nslices - g * group), least, room.two, seen, parts[g]);
+                for (const Part& P : parts[g]) over += static_cast<int64_t>(P.nodes.size()) > room.two;
+                tiles += static_cast<int64_t>(parts[g].size());
             }
-            for (Part& P : out) {
+        }, 64);
+        if (over <= tiles / 4) break;
+        phase = room.one;
+    }
+    parallel_for(ng, [&](int64_t g0, int64_t g1) {
+        for (int64_t g = g0; g < g1; ++g) {
+            for (Part& P : parts[g]) {
                 const int64_t R = static_cast<int64_t>(P.nodes.size());
-                P.nphase = static_cast<int32_t>((R + room.one - 1) / room.one);
+                P.nphase = static_cast<int32_t>((R + phase - 1) / phase);
                 P.per = P.nphase ? static_cast<int32_t>((R + P.nphase - 1) / P.nphase) : 0;
                 P.at.resize(static_cast<size_t>(R));
                 for (int ph = 0; ph < P.nphase; ++ph) {
