@@ -668,7 +668,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     constexpr uint32_t range = range_bits<FP32>(kMidRange, kMidRange32), wrange = range_bits<FP32>(kWideRange, kWideRange32);
     constexpr uint32_t neg = 0x80000000u | range, wneg = 0x80000000u | wrange;
     constexpr uint32_t nan_neg = FP32 ? 0xff800000u : 0xfff00000u;
-    Real F0 = 0, F1 = 0, F2 = 0;   // sums without kMidScale and the factors shared by the node's bonds
+    Real F0 = 0, F1 = 0, F2 = 0;   // sums without kMidScale and (FP64; FP32: uniform ones) the factors shared by the node's bonds
 
     auto term = [&](const NodeRec& r, auto level) {
         if constexpr (FP32)
@@ -676,17 +676,20 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
         else
             return slot_mid<decltype(level)::value>(r, X0, X1, X2, U0, U1, U2, mc);
     };
-    // the factor of a slot that its node's bonds do not share
-    auto weight = [&](uint32_t idx, double k, Real L2, double fv) -> Real {
+    // the factor of a slot that its node's bonds do not share (FP32: the whole of it, formed in
+    // double precision, whose parts may leave the single one's range while their product, a force
+    // density, does not; of the corrections the ratio to 2 V0)
+    auto weight = [&](uint32_t idx, double k, Real L2, double fv, double own) -> Real {
         if constexpr (CORR != kCorrNone) {
-            return corr_factor<CORR>(P, L2, static_cast<Real>(fv + lw[idx]));
+            return corr_factor<CORR>(P, L2, static_cast<Real>(FP32 ? (fv + lw[idx]) * own : fv + lw[idx]));
         } else if constexpr (NODEW) {
             const double v = lw[idx];
-            return static_cast<Real>(STIFF ? k * v : v);
+            return static_cast<Real>(STIFF ? k * v : FP32 ? own * v : v);
         } else {
-            return static_cast<Real>(STIFF ? k : 1.0);
+            return static_cast<Real>(!STIFF ? 1.0 : FP32 ? k * own : k);
         }
     };
+    const double own = !FP32 ? 1.0 : CORR ? 1.0 / P.cr_2v0 : KNODE ? A.na[node] : STIFF ? P.volume : P.c;
     auto add = [&](Real coef, const MidTerm<Real>& m) {
         F0 = __builtin_elementwise_fma(coef, m.y0, F0);
         F1 = __builtin_elementwise_fma(coef, m.y1, F1);
@@ -752,7 +755,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
             uint32_t bits = 0;
             auto one = [&](const NodeRec& r, uint32_t idx, double kslot, uint32_t word, int bit) {
                 const MidTerm<Real> m = term(r, Level{});
-                Real coef = WEIGHT ? m.coef * weight(idx, kslot, m.L2, fvi) : m.coef;
+                Real coef = WEIGHT ? m.coef * weight(idx, kslot, m.L2, fvi, own) : m.coef;
                 if constexpr (MARK) {
                     const bool over = m.hi >= edge && (word & (EXT ? kEntBroken | kEntSoft | kEntNoFail : kEntBroken)) == 0;
                     coef = over ? Real(0) : coef;
@@ -828,7 +831,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                                   (m.hi >= edge || static_cast<uint32_t>(m.hi) >= nan_neg);
                 bits |= over ? 1u << u : 0u;
                 // a slot that is not live adds nothing, whatever its numbers
-                if (live && !over) add(WEIGHT ? m.coef * weight(idx, kh, m.L2, fvi) : m.coef, m);
+                if (live && !over) add(WEIGHT ? m.coef * weight(idx, kh, m.L2, fvi, own) : m.coef, m);
                 const int32_t hi = live ? m.hi : 0;
                 himax = max(himax, hi);
                 himin = max(himin, static_cast<uint32_t>(hi));
@@ -875,7 +878,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
             const uint32_t word = A.ent[ds];
             const double sold = laws ? A.smax[ds] : 0.0, k = STIFF ? A.kslot[ds] : 0.0;
             const double x0 = __shfl(X0, owner), x1 = __shfl(X1, owner), x2 = __shfl(X2, owner);
-            const double fv = CORR ? __shfl(fvi, owner) : 0.0;
+            const double fv = CORR ? __shfl(fvi, owner) : 0.0, ow = FP32 && KNODE ? __shfl(own, owner) : own;
             const uint32_t e = on ? word : kEntBroken;
             const bool live = !(e & kEntBroken), soft = EXT && live && (e & kEntSoft) != 0;
             const uint32_t idx = live ? e & kEntIdx : 0u;
@@ -927,7 +930,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
             coef = bw.broke || bw.share == 0.0 ? 0.0 : coef * bw.share;
             double f0 = 0.0, f1 = 0.0, f2 = 0.0;
             if (coef != 0.0) {
-                if (WEIGHT) coef *= static_cast<double>(weight(idx, k, m.L2, fv));
+                if (WEIGHT) coef *= static_cast<double>(weight(idx, k, m.L2, fv, ow));
                 f0 = coef * static_cast<double>(m.y0);
                 f1 = coef * static_cast<double>(m.y1);
                 f2 = coef * static_cast<double>(m.y2);
@@ -1006,8 +1009,9 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     double G[3] = {F0 + E0, F1 + E1, F2 + E2};
     tile_reduce(tl, reinterpret_cast<double*>(lds), G);
     if (tl.sub > 0 || !tl.has) return;
-    const double share = (FP32 ? kMidScale32 : kMidScale) *
-                         (CORR ? P.cr_2v0 : 1.0) * (KNODE ? A.na[node] : STIFF ? (VOLN ? 1.0 : P.volume) : VOLN ? P.c : P.c * P.volume);
+    const double share = FP32 ? kMidScale32 * (!WEIGHT || CORR ? P.c * P.volume : 1.0)
+                              : kMidScale * (CORR ? P.cr_2v0 : 1.0) *
+                                    (KNODE ? A.na[node] : STIFF ? (VOLN ? 1.0 : P.volume) : VOLN ? P.c : P.c * P.volume);
     node_update<MODE, FP32>(A, P, node, U0, U1, U2, share * G[0], share * G[1], share * G[2]);
 }
 
