@@ -248,7 +248,8 @@ def batched_extra(P, pi, sync, count: int, steps: int, seq_sample: int, tune: bo
     seq = seq_slots * steps / seq_t if seq_t > 0 else float("nan")
     return {"config": f"{count} beams, dims {ws[0].dims}..{ws[-1].dims}, {steps} Euler-Cromer steps, f64",
             "instances": count, "nodes": info["n_nodes"], "bond_slots": nnz,
-            "mapping": mapping if mapping == "staged" else f"sliced-{lanes}", "node_order": order,
+            "mapping": mapping if mapping == "staged" else f"sliced-{lanes}",
+            "node_order": "compact slices" if mapping == "staged" else order,
             "setup_s": setup, "batched_rate": batched, "ms_per_step": t_b * 1e3 / steps,
             "sequential_rate": seq, "sequential_sample": [int(b) for b in idx],
             "batched_vs_sequential": batched / seq}
@@ -589,7 +590,7 @@ def main():
                                f"horizon {w.horizon / w.dx:.3f} dx, {w.scheme}"
                                + (", state-based linear solid" if args.model == "state_based" else ""),
                    "nodes": info["n_nodes"], "bond_slots": nnz, "mapping": mapping, "lanes_per_node": lanes,
-                   "device_node_order": order,
+                   "device_node_order": "compact slices" if mapping == "staged" else order,
                    "parallelism": "1 GPU"},
         # the method's roofline is HBM bandwidth over its compulsory bytes per step (4 B
         # per slot, node state read and written); beside it the method's own FP64

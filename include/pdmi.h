@@ -50,6 +50,8 @@ extern "C" {
 #define PD_FP64 0           /* state and arithmetic in double precision */
 #define PD_FP32 1           /* state (u, v, a) and bond arithmetic in single precision */
 
+/* Device node order of the sliced mapping (the staged mapping always renumbers nodes into
+   compact slices of 64; the order is then kept for a later pd_set_mapping). */
 #define PD_ORDER_NATURAL 0  /* keep the caller's node order in device memory */
 #define PD_ORDER_MORTON 1   /* renumber nodes internally along a Morton (Z-order) curve */
 #define PD_ORDER_AUTO 2     /* natural order until pd_autotune, which also tries Morton order */
@@ -97,7 +99,7 @@ typedef struct pd_info {
     int32_t precision;      /* PD_FP64 / PD_FP32 */
     int32_t scheme;         /* integrator */
     int32_t mapping;        /* PD_MAP_SLICED / PD_MAP_STAGED */
-    int32_t order;          /* device node order in use: PD_ORDER_NATURAL / PD_ORDER_MORTON */
+    int32_t order;          /* device node order of the sliced mapping: PD_ORDER_NATURAL / PD_ORDER_MORTON */
     double model_bytes_per_step; /* algorithmic HBM bytes of one step (see the design notes) */
     int32_t waves_per_slice; /* staged mapping: the lanes of pd_set_mapping (1 otherwise) */
     int32_t reserved_;
@@ -476,8 +478,9 @@ int pd_set_lanes_per_node(pd_ctx *ctx, int lanes);
 /* Time `trial_steps` steps (after as many untimed ones) of every mapping candidate on
  * the current problem (and both device node orders if the family was built with
  * PD_ORDER_AUTO) and keep the fastest; the state is restored afterwards.
+ * The sliced mapping is tried with 1, 4, 16 and 64 lanes per node, the staged one once.
  * *chosen (may be NULL) receives the lanes-per-node of the chosen sliced mapping, or
- * minus the wavefronts per slice of the chosen staged mapping. */
+ * minus the lanes given for the staged mapping (1 if the mapping was sliced). */
 int pd_autotune(pd_ctx *ctx, int64_t trial_steps, int32_t *chosen);
 
 /* Problem and layout sizes. */

@@ -426,12 +426,12 @@ int pd_set_mapping(pd_ctx* ctx, int mapping, int lanes)
             return;
         }
         if (lanes == ctx->lanes && mapping == ctx->mapping) return;
-        set_device(ctx);
-        if (mapping == ctx->mapping && mapping == PD_MAP_STAGED) {  // other tiles; break steps are kept
+        if (mapping == ctx->mapping && mapping == PD_MAP_STAGED) {  // the tiles do not depend on it
             ctx->lanes = lanes;
-            relayout(ctx);
+            ctx->tape_valid = false;  // as any change of the mapping
             return;
         }
+        set_device(ctx);
         HostState S = snapshot(ctx);
         const bool av = ctx->a_valid;
         ctx->mapping = mapping;
@@ -458,12 +458,13 @@ int pd_autotune(pd_ctx* ctx, int64_t trial_steps, int32_t* chosen)
         };
         std::vector<Cand> cands;
         const int orders[] = {PD_ORDER_NATURAL, PD_ORDER_MORTON};
-        for (int o : orders) {
-            if (!ctx->order_auto && o != ctx->order) continue;
-            if (!fp32(ctx) && !ctx->has_osb)
+        if (!fp32(ctx) && !ctx->has_osb)
+            for (int o : orders) {
+                if (!ctx->order_auto && o != ctx->order) continue;
                 for (int L : {1, 4, 16, 64}) cands.push_back({PD_MAP_SLICED, L, o});
-            for (int S : {1, 2, 4}) cands.push_back({PD_MAP_STAGED, S, o});
-        }
+            }
+        // the staged layout follows from neither lanes nor order
+        cands.push_back({PD_MAP_STAGED, ctx->mapping == PD_MAP_STAGED ? ctx->lanes : 1, ctx->order});
         Cand best{ctx->mapping, ctx->lanes, ctx->order};
         double best_ms = std::numeric_limits<double>::infinity();
         for (const Cand& cd : cands) {
