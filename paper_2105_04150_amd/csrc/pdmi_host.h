@@ -299,6 +299,7 @@ struct HostState {
     std::vector<std::vector<uint8_t>> broken;   // per instance, nnz
     std::vector<std::vector<double>> smax;      // per instance, nnz (empty without damage laws)
     std::vector<std::vector<int32_t>> bstep;    // per instance, nnz (empty: restart from the broken flags)
+    int32_t status = 0;                         // the device's status word (a non-finite value was produced)
 };
 
 // ---- pdmi_layout.cpp

@@ -655,6 +655,7 @@ void upload_bstep(pd_ctx* ctx, const Inst& I, const int32_t* bstep)
 HostState snapshot(pd_ctx* ctx)
 {
     HostState S;
+    download(&S.status, ctx->status, sizeof S.status, 0, ctx->stream);
     for (auto& I : ctx->inst) {
         S.u.push_back(u_of(ctx, I));
         S.v.push_back(soa_of(ctx, I, ctx->v));
