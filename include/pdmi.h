@@ -18,6 +18,11 @@
  *  - Return value: PD_OK (0) or a negative PD_E* code; pd_last_error() gives a
  *    message.  No C++ exception crosses this boundary.
  *  - Setters are all-or-nothing: on error the context is unchanged.
+ *  - Device memory is allocated and filled by the first call that needs it (a state set or
+ *    read, pd_prepare, pd_step), once for all setters before it.  A later change of what the
+ *    staged mapping keeps in LDS (volumes, a node stiffness, corrections, the model, the first
+ *    pd_adj_forward) may make the next call that steps or evaluates forces lay the problem
+ *    out anew, synchronising, with its state kept.
  *  - Host pointers are read during the call only; the caller keeps ownership.
  *  - Node ids, slot ids and every per-node / per-slot array are in the caller's
  *    ("user") order: node ids as passed to pd_build_family, slots in the CSR order
@@ -124,7 +129,7 @@ const char *pd_last_error(const pd_ctx *ctx);
 /* Build the family of a single-instance problem (Eq. family: every j != i with
  * |x_j - x_i| <= horizon, tested as ((dx^2 + dy^2) + dz^2) <= horizon^2 without
  * fused multiply-add) from `coords` (host, n x 3 row-major doubles, metres), sorted
- * ascending per row, and upload it.  `order` picks the device node order.  Resets
+ * ascending per row.  `order` picks the device node order.  Resets
  * the state: u = v = a = 0, no broken bonds, no BCs, no body force, step 0.
  * Errors: PD_EINVAL (n < 1, NULL coords, non-finite coords, two nodes at the same
  * position, horizon <= 0 or not finite, bad order), PD_ERANGE (n or nnz >= 2^31, or
@@ -301,7 +306,7 @@ int pd_step(pd_ctx *ctx, int64_t nsteps);
 /* Capture and instantiate now the step graphs that pd_step would otherwise build on
  * first use (chunks of several steps recorded once and replayed), for the current
  * integrator, layout and loads, so that a later pd_step spends no host time on them.
- * Runs nothing on the device and changes no state.  Calls that change the layout,
+ * Lays the problem out on the device if that is due; steps nothing and changes no state.  Calls that change the layout,
  * the integrator, the loads or the no-failure zones discard the graphs again. */
 int pd_prepare(pd_ctx *ctx);
 
@@ -438,7 +443,8 @@ int pd_load_state(pd_ctx *ctx, int32_t inst, const pd_state *in);
  * every ckpt_every >= 1 steps ((nn + 1) * 48 + nn * 24 bytes each, nn = padded node
  * count; with ckpt_every = 1 every level is kept, v is not, and the reverse pass
  * recomputes nothing).  Any later change to the problem or state (pd_step included)
- * discards the recording.  Asynchronous like pd_step.  *recording (may be NULL)
+ * discards the recording.  Asynchronous like pd_step (the first one of a problem may
+ * lay it out anew).  *recording (may be NULL)
  * receives an id of this recording, unique in the process and > 0 (0 on error), which
  * pd_adj_backward takes to make sure its gradient belongs to this run. */
 int pd_adj_forward(pd_ctx *ctx, int64_t nsteps, int32_t ckpt_every, int64_t *recording);

@@ -213,7 +213,7 @@ int pd_break_bonds(pd_ctx* ctx, int32_t inst, const uint8_t* broken)
     return guarded(ctx, [&] {
         Inst& I = instance(ctx, inst);
         if (!broken) fail(PD_EINVAL, "broken is NULL");
-        set_device(ctx);
+        laid_out(ctx);
         std::vector<uint8_t> cur = broken_of(ctx, I);
         for (int64_t b = 0; b < I.nnz; ++b) cur[b] = cur[b] || broken[b];
         const std::vector<double> sm = smax_of(ctx, I);
@@ -291,8 +291,8 @@ int pd_set_no_fail(pd_ctx* ctx, int32_t inst, int64_t m, const int64_t* nodes)
         for (int64_t i = 0; i < m; ++i)
             if (nodes[i] < 0 || nodes[i] >= I.n) fail(PD_EINVAL, "no-failure node id out of range");
         set_device(ctx);
-        const std::vector<uint8_t> br = broken_of(ctx, I);
-        const std::vector<double> sm = smax_of(ctx, I);
+        const std::vector<uint8_t> br = ctx->laid ? broken_of(ctx, I) : std::vector<uint8_t>();
+        const std::vector<double> sm = ctx->laid ? smax_of(ctx, I) : std::vector<double>();
         I.nofail.clear();
         if (m > 0) {
             I.nofail.assign(static_cast<size_t>(I.n), 0);
@@ -300,6 +300,7 @@ int pd_set_no_fail(pd_ctx* ctx, int32_t inst, int64_t m, const int64_t* nodes)
         }
         ctx->has_nofail = false;
         for (auto& J : ctx->inst) ctx->has_nofail |= !J.nofail.empty();
+        if (!ctx->laid) return;
         upload_col(ctx, I, br.data(), /*keep_bsteps=*/true, sm.data());
         ctx->drop_graphs();
     });
@@ -332,7 +333,6 @@ int pd_set_damage_law(pd_ctx* ctx, int32_t inst, int32_t cls, int32_t nb, const 
         else
             I.laws[cls] = L;
         reset_laws(ctx);
-        fit_stage(ctx);
     });
 }
 

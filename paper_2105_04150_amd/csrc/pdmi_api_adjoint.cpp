@@ -21,11 +21,11 @@ int pd_adj_forward(pd_ctx* ctx, int64_t nsteps, int32_t ckpt_every, int64_t* rec
         if (ckpt_every < 1) fail(PD_EINVAL, "ckpt_every must be >= 1");
         if (ctx->step + nsteps >= std::numeric_limits<int32_t>::max())
             fail(PD_ERANGE, "step counter would exceed 2^31 - 1");
-        set_device(ctx);
         Inst& I = ctx->inst[0];
         check_symmetric(I);
         ctx->adjoint = true;
         fit_stage(ctx);
+        ready(ctx);
         init_break_steps(ctx, I);
         const int64_t nn = ctx->nn;
         const size_t Rb = rec_bytes(nn), Vb = static_cast<size_t>(3 * nn) * sizeof(double);

@@ -15,7 +15,7 @@ int pd_step(pd_ctx* ctx, int64_t nsteps)
         if (nsteps < 0) fail(PD_EINVAL, "nsteps must be >= 0");
         if (ctx->step + nsteps >= std::numeric_limits<int32_t>::max())
             fail(PD_ERANGE, "step counter would exceed 2^31 - 1");
-        set_device(ctx);
+        ready(ctx);
         do_steps(ctx, nsteps);
     });
 }
@@ -25,7 +25,7 @@ int pd_prepare(pd_ctx* ctx)
     if (!ctx) return PD_EINVAL;
     return guarded(ctx, [&] {
         require_built(ctx);
-        set_device(ctx);
+        ready(ctx);
         osb_checks(ctx);
         if (!ctx->use_graphs) return;
         const int mode = step_mode(ctx->scheme);
@@ -39,7 +39,7 @@ int pd_sync(pd_ctx* ctx)
     return guarded(ctx, [&] {
         set_device(ctx);
         sync(ctx);
-        if (ctx->built) check_status(ctx);
+        if (ctx->laid) check_status(ctx);
     });
 }
 
@@ -56,7 +56,7 @@ int pd_get_u(pd_ctx* ctx, int32_t inst, double* out)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
-        set_device(ctx);
+        laid_out(ctx);
         auto u = u_of(ctx, I);
         std::memcpy(out, u.data(), u.size() * sizeof(double));
         check_status(ctx);
@@ -69,7 +69,7 @@ int pd_get_v(pd_ctx* ctx, int32_t inst, double* out)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
-        set_device(ctx);
+        laid_out(ctx);
         auto v = soa_of(ctx, I, ctx->v);
         std::memcpy(out, v.data(), v.size() * sizeof(double));
         check_status(ctx);
@@ -82,7 +82,7 @@ int pd_get_a(pd_ctx* ctx, int32_t inst, double* out)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
-        set_device(ctx);
+        laid_out(ctx);
         auto a = soa_of(ctx, I, ctx->a);
         std::memcpy(out, a.data(), a.size() * sizeof(double));
     });
@@ -94,7 +94,7 @@ int pd_get_damage(pd_ctx* ctx, int32_t inst, double* out)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
-        set_device(ctx);
+        laid_out(ctx);
         launch_damage_now(ctx);
         std::vector<double> h(static_cast<size_t>(I.n_pad));
         download(h.data(), ctx->phi, h.size() * 8, I.node_off * 8, ctx->stream);
@@ -138,7 +138,7 @@ int pd_get_dilation(pd_ctx* ctx, int32_t inst, double* out)
         if (!out) fail(PD_EINVAL, "out is NULL");
         if (!I.osb) fail(PD_EINVAL, "the instance does not run the state-based model");
         osb_checks(ctx);
-        set_device(ctx);
+        ready(ctx);
         // the dilation pass at the current level, breaking nothing
         hip_check(launch_osb_dilation(step_args(ctx, ctx->cur, 1 - ctx->cur, 0), false, fp32(ctx),
                                       ctx->stream),
@@ -161,7 +161,7 @@ int pd_get_broken(pd_ctx* ctx, int32_t inst, uint8_t* out)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
-        set_device(ctx);
+        laid_out(ctx);
         auto b = broken_of(ctx, I);
         std::memcpy(out, b.data(), b.size());
     });
@@ -173,7 +173,7 @@ int pd_get_max_stretch(pd_ctx* ctx, int32_t inst, double* out)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
-        set_device(ctx);
+        laid_out(ctx);
         const std::vector<double> sm = smax_of(ctx, I);
         std::memcpy(out, sm.data(), sm.size() * sizeof(double));
     });
@@ -188,7 +188,7 @@ int pd_set_max_stretch(pd_ctx* ctx, int32_t inst, const double* smax)
         if (!ctx->has_laws) fail(PD_ESTATE, "no damage laws");
         for (int64_t b = 0; b < I.nnz; ++b)
             if (!std::isfinite(smax[b]) || smax[b] < 0.0) fail(PD_EINVAL, "stretch state must be finite and >= 0");
-        set_device(ctx);
+        laid_out(ctx);
         const std::vector<uint8_t> br = broken_of(ctx, I);
         upload_col(ctx, I, br.data(), true, smax);
         ctx->drop_graphs();
@@ -201,7 +201,7 @@ int pd_get_force(pd_ctx* ctx, int32_t inst, double* out)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
-        set_device(ctx);
+        ready(ctx);
         eval_force(ctx);
         auto f = soa_of(ctx, I, ctx->force);
         std::memcpy(out, f.data(), f.size() * sizeof(double));
@@ -214,8 +214,8 @@ int pd_get_resultant(pd_ctx* ctx, int32_t inst, int64_t m, const int64_t* nodes,
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
+        ready(ctx);
         const std::vector<int64_t> idx = device_nodes(I, m, nodes);
-        set_device(ctx);
         eval_force(ctx);
         set_sum(ctx, idx, ctx->force.as<double>(), 1, ctx->nn, ctx->has_vol ? ctx->vol.as<double>() : nullptr,
                 I.volume, out);
@@ -228,8 +228,8 @@ int pd_get_mean_displacement(pd_ctx* ctx, int32_t inst, int64_t m, const int64_t
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
+        laid_out(ctx);
         const std::vector<int64_t> idx = device_nodes(I, m, nodes);
-        set_device(ctx);
         const double w = 1.0 / static_cast<double>(m);
         if (fp32(ctx))  // the f64 master displacement, structure of arrays
             set_sum(ctx, idx, ctx->um[ctx->cur].as<double>(), 1, ctx->nn, nullptr, w, out);
@@ -249,7 +249,7 @@ int pd_get_mean_displacement_noalloc(pd_ctx* ctx, int32_t inst, int64_t m, const
         for (int64_t p = 0; p < m; ++p)
             if (nodes[p] < 0 || nodes[p] >= I.n) fail(PD_EINVAL, "node id out of range");
         require_built(ctx);
-        set_device(ctx);
+        laid_out(ctx);
         int64_t* scr = nullptr;  // this GPU's scratch array: node ids, then the three sums
         hip_check(scratch_address(ctx->device, &scr), "scratch address");
         double* sums = reinterpret_cast<double*>(scr + kScratchNodes);
@@ -280,7 +280,7 @@ int pd_set_state(pd_ctx* ctx, int32_t inst, const double* u, const double* v, co
             if (p)
                 for (int64_t q = 0; q < 3 * I.n; ++q)
                     if (!std::isfinite(p[q])) fail(PD_EINVAL, "state must be finite");
-        set_device(ctx);
+        laid_out(ctx);
         if (u) {
             // both buffers: the current one and the one the next step writes
             upload_state(ctx, I, u, nullptr, nullptr);
@@ -300,7 +300,7 @@ int pd_set_step(pd_ctx* ctx, int64_t step)
     return guarded(ctx, [&] {
         require_built(ctx);
         if (step < 0 || step >= std::numeric_limits<int32_t>::max()) fail(PD_EINVAL, "step out of range");
-        set_device(ctx);
+        laid_out(ctx);
         ctx->tape_valid = false;
         ctx->step = step;
         upload(ctx->step_base, &step, sizeof step, 0, ctx->stream);
@@ -316,7 +316,7 @@ int pd_get_state(pd_ctx* ctx, int32_t inst, pd_state* out)
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
         require_built(ctx);
-        set_device(ctx);
+        laid_out(ctx);
         auto put = [](auto* dst, const auto& src) { std::memcpy(dst, src.data(), src.size() * sizeof(src[0])); };
         if (out->u) put(out->u, u_of(ctx, I));
         if (out->v) put(out->v, soa_of(ctx, I, ctx->v));
@@ -363,7 +363,7 @@ int pd_load_state(pd_ctx* ctx, int32_t inst, const pd_state* in)
             }
         }
         if (in->step < 0 || in->step >= std::numeric_limits<int32_t>::max()) fail(PD_EINVAL, "step out of range");
-        set_device(ctx);
+        laid_out(ctx);
         if (in->u) upload_state(ctx, I, in->u, nullptr, nullptr);  // both displacement levels
         upload_state(ctx, I, nullptr, in->v, in->a);
         if (in->broken || smax_in) {
@@ -432,12 +432,29 @@ int pd_set_mapping(pd_ctx* ctx, int mapping, int lanes)
             return;
         }
         set_device(ctx);
-        HostState S = snapshot(ctx);
-        const bool av = ctx->a_valid;
-        ctx->mapping = mapping;
-        ctx->lanes = lanes;
-        build_layout(ctx, &S);
-        ctx->a_valid = av;
+        const bool laid = ctx->laid;
+        std::vector<std::vector<int32_t>> bstep;
+        if (laid) {
+            ctx->kept = std::make_shared<HostState>(snapshot(ctx));
+            for (const Inst& I : ctx->inst) bstep.push_back(bstep_of(ctx, I));
+        }
+        auto change = [&](int to, int with) {
+            ctx->laid = false;
+            ctx->mapping = to;
+            ctx->lanes = with;
+            upload_stiffness(ctx);  // (which kernels form the corrections depends on the mapping)
+            upload_node_weights(ctx);
+        };
+        const int was = ctx->mapping, had = ctx->lanes;
+        change(mapping, lanes);
+        if (!laid) return;
+        try {
+            build_layout(ctx);  // (break steps start anew)
+        } catch (...) {  // the next call that needs it makes the former layout again
+            if (ctx->kept) ctx->kept->bstep = std::move(bstep);
+            change(was, had);
+            throw;
+        }
     });
 }
 
@@ -449,8 +466,8 @@ int pd_autotune(pd_ctx* ctx, int64_t trial_steps, int32_t* chosen)
     return guarded(ctx, [&] {
         require_built(ctx);
         if (trial_steps < 1) fail(PD_EINVAL, "trial_steps must be >= 1");
-        set_device(ctx);
-        HostState S = snapshot(ctx);
+        laid_out(ctx);
+        const auto S = std::make_shared<HostState>(snapshot(ctx));
         const int64_t step0 = ctx->step;
         const bool av = ctx->a_valid;
         struct Cand {
@@ -466,13 +483,28 @@ int pd_autotune(pd_ctx* ctx, int64_t trial_steps, int32_t* chosen)
         // the staged layout follows from neither lanes nor order
         cands.push_back({PD_MAP_STAGED, ctx->mapping == PD_MAP_STAGED ? ctx->lanes : 1, ctx->order});
         Cand best{ctx->mapping, ctx->lanes, ctx->order};
-        double best_ms = std::numeric_limits<double>::infinity();
-        for (const Cand& cd : cands) {
+        auto restart = [&](const Cand& cd) {
             ctx->mapping = cd.mapping;
             ctx->lanes = cd.lanes;
             ctx->order = cd.order;
-            build_layout(ctx, &S);
+            ctx->step = step0;
             ctx->a_valid = av;
+            ctx->kept = S;
+            ctx->laid = false;
+        };
+        struct Unfinished {  // a failed trial leaves the problem as it was, to be laid out again
+            decltype(restart)& f;
+            Cand was;
+            bool on = true;
+            ~Unfinished()
+            {
+                if (on) f(was);
+            }
+        } unfinished{restart, best};
+        double best_ms = std::numeric_limits<double>::infinity();
+        for (const Cand& cd : cands) {
+            restart(cd);
+            build_layout(ctx);
             for (int rep = 0; rep < 2; ++rep)  // first pass builds graphs and warms caches
                 do_steps(ctx, trial_steps);
             float ms = 0.f;
@@ -482,17 +514,10 @@ int pd_autotune(pd_ctx* ctx, int64_t trial_steps, int32_t* chosen)
                 best_ms = ms;
                 best = cd;
             }
-            ctx->step = step0;
         }
-        ctx->order = best.order;
-        ctx->mapping = best.mapping;
-        ctx->lanes = best.lanes;
-        build_layout(ctx, &S);
-        ctx->step = step0;
-        const int64_t st = step0;
-        upload(ctx->step_base, &st, sizeof st, 0, ctx->stream);
-        sync(ctx);
-        ctx->a_valid = av;
+        restart(best);
+        build_layout(ctx);
+        unfinished.on = false;
         reset_flags_after_state_change(ctx, av);
         if (chosen) *chosen = best.mapping == PD_MAP_STAGED ? -best.lanes : best.lanes;
     });
@@ -505,7 +530,7 @@ int pd_get_break_steps(pd_ctx* ctx, int32_t inst, int32_t* out)
         const Inst& I = instance(ctx, inst);
         if (!out) fail(PD_EINVAL, "out is NULL");
         require_built(ctx);
-        set_device(ctx);
+        laid_out(ctx);
         std::vector<int32_t> h(static_cast<size_t>(I.n_dslots));
         download(h.data(), ctx->bstep, h.size() * sizeof(int32_t), static_cast<size_t>(I.dslot_off) * sizeof(int32_t),
                  ctx->stream);
@@ -522,6 +547,8 @@ int pd_get_info(const pd_ctx* ctx, pd_info* info)
     if (!ctx || !info) return PD_EINVAL;
     std::memset(info, 0, sizeof *info);
     if (!ctx->built) return PD_OK;
+    const int rc = guarded(const_cast<pd_ctx*>(ctx), [&] { laid_out(const_cast<pd_ctx*>(ctx)); });
+    if (rc != PD_OK) return rc;
     int64_t n = 0, nnz = 0;
     for (auto& I : ctx->inst) {
         n += I.n;

@@ -125,6 +125,15 @@ struct Inst {
     int64_t node_off = 0, n_pad = 0, slice_off = 0, nslices = 0, dslot_off = 0, n_dslots = 0;
 };
 
+// The state of every instance in user order, kept across a rebuild of the device problem.
+struct HostState {
+    std::vector<std::vector<double>> u, v, a;   // per instance, n*3
+    std::vector<std::vector<uint8_t>> broken;   // per instance, nnz
+    std::vector<std::vector<double>> smax;      // per instance, nnz (empty without damage laws)
+    std::vector<std::vector<int32_t>> bstep;    // per instance, nnz (empty: restart from the broken flags)
+    int32_t status = 0;                         // the device's status word (a non-finite value was produced)
+};
+
 }  // namespace host
 }  // namespace pdmi
 
@@ -148,13 +157,19 @@ struct pd_ctx {
     int cur = 0;                     // node-record buffer holding u of level `step`
     bool a_valid = false;            // velocity Verlet: a holds the acceleration of level `step`
     bool vv_ahead = false;           // velocity Verlet: buffer 1-cur holds u of level step+1
-    bool built = false;
+    bool built = false;              // there is a problem
+    // The device problem is laid out at the first call that needs it (laid_out), once whatever
+    // the setters before it change; `kept` is the state it starts from (null: zeros).  A failed
+    // layout leaves `laid` false and the state in `kept`, and the next such call tries again.
+    bool laid = false;
+    bool recut = false;              // staged: a setter changed what the tiles hold; ready() cuts them anew
+    std::shared_ptr<pdmi::host::HostState> kept;
     bool use_graphs = true;
 
     int64_t nn = 0, ns = 0, nslices = 0;
     int64_t ntiles = 0, stage_max = 0;  // staged layout: tiles, records of the largest phase
-    int64_t stage_slices = 0;  // slices per tile
     int64_t stage_two = 0;  // records that fitted a CU twice when the layout was made
+    bool stage_cut = false; // some tile was cut, or takes several phases, for want of room
     bool adjoint = false;               // the reverse pass has been asked for: its LDS counts
     bool has_stiff = false, has_vol = false, has_body = false, has_knode = false;
     bool has_nofail = false;         // some slot carries the no-failure bit
@@ -293,20 +308,12 @@ inline bool fp32(const pd_ctx* ctx) { return ctx->precision == PD_FP32; }
 // Bytes of one node-record buffer: nn records and the sentinel.
 inline size_t rec_bytes(int64_t nn) { return static_cast<size_t>(nn + 1) * 48; }
 
-// The state of every instance in user order, kept across a rebuild of the device problem.
-struct HostState {
-    std::vector<std::vector<double>> u, v, a;   // per instance, n*3
-    std::vector<std::vector<uint8_t>> broken;   // per instance, nnz
-    std::vector<std::vector<double>> smax;      // per instance, nnz (empty without damage laws)
-    std::vector<std::vector<int32_t>> bstep;    // per instance, nnz (empty: restart from the broken flags)
-    int32_t status = 0;                         // the device's status word (a non-finite value was produced)
-};
-
 // ---- pdmi_layout.cpp
 void family_search(int64_t n, const double* x, double delta, std::vector<int64_t>& row_ptr,
                    std::vector<int32_t>& col);
-void build_layout(pd_ctx* ctx, const HostState* S);
-void relayout(pd_ctx* ctx);
+void build_layout(pd_ctx* ctx);
+void laid_out(pd_ctx* ctx);
+void ready(pd_ctx* ctx);
 void fit_stage(pd_ctx* ctx);
 void validate_coords(int64_t n, const double* coords, double horizon);
 double validate_family(int64_t n, const double* x, const int64_t* row_ptr, const int32_t* col);

@@ -530,28 +530,48 @@ static int64_t tile_slices(const pd_ctx* ctx)
     return nsl >= 3072 ? kTileSlices : nsl >= 512 ? 2 : 1;
 }
 
-// A new layout with the state kept, break steps and the acceleration's validity included.
-void relayout(pd_ctx* ctx)
+static void check_nodes(int64_t nn)
 {
-    HostState S = snapshot(ctx);
-    for (const Inst& I : ctx->inst) S.bstep.push_back(bstep_of(ctx, I));
-    const bool av = ctx->a_valid;
-    build_layout(ctx, &S);
-    for (size_t ii = 0; ii < ctx->inst.size(); ++ii) upload_bstep(ctx, ctx->inst[ii], S.bstep[ii].data());
-    ctx->a_valid = av;
+    if (nn >= std::numeric_limits<int32_t>::max()) fail(PD_ERANGE, "device problem needs 2^31 or more nodes or slots");
+    if (nn + 1 >= (int64_t(1) << 24))
+        fail(PD_ERANGE, "device problem needs 2^24 or more node records (the gather uses 24-bit indices)");
 }
 
-// After a change of what the kernels stage: a phase that no longer fits is cut anew.
+// After a change of what the kernels stage: a phase that no longer fits (twice, where it did) is
+// cut anew, and so are tiles that were cut for want of room there is now.  Done by the next call
+// that runs a kernel.
 void fit_stage(pd_ctx* ctx)
 {
-    if (!ctx->built || ctx->mapping != PD_MAP_STAGED) return;
+    if (!ctx->laid || ctx->mapping != PD_MAP_STAGED) return;
     const StageRoom r = stage_room(ctx);
-    if ((r.two < ctx->stage_two && ctx->stage_max > r.two) || tile_slices(ctx) != ctx->stage_slices) relayout(ctx);
+    ctx->recut = (r.two < ctx->stage_two && ctx->stage_max > r.two) || (r.two > ctx->stage_two && ctx->stage_cut);
 }
 
-// Allocate and fill the device problem for ctx->lanes from the instances' user data.
-void build_layout(pd_ctx* ctx, const HostState* S)
+// Called by every entry point that needs the device problem: the device, and the problem on it.
+void laid_out(pd_ctx* ctx)
 {
+    set_device(ctx);
+    if (ctx->built && !ctx->laid) build_layout(ctx);
+}
+
+// The same for those that run its kernels: with tiles for what the problem holds now.  The state
+// is kept, break steps and the acceleration's validity included.
+void ready(pd_ctx* ctx)
+{
+    laid_out(ctx);
+    if (!ctx->recut) return;
+    auto S = std::make_shared<HostState>(snapshot(ctx));
+    for (const Inst& I : ctx->inst) S->bstep.push_back(bstep_of(ctx, I));
+    ctx->kept = std::move(S);
+    build_layout(ctx);
+}
+
+// Allocate and fill the device problem for ctx->lanes from the instances' user data and the
+// kept state.
+void build_layout(pd_ctx* ctx)
+{
+    const HostState* const S = ctx->kept.get();
+    ctx->laid = false;
     const bool staged = ctx->mapping == PD_MAP_STAGED;
     const int G = staged ? 1 : ctx->lanes, W = kWave / G;
     ctx->drop_graphs();
@@ -568,7 +588,7 @@ void build_layout(pd_ctx* ctx, const HostState* S)
     const StageRoom room = stage_room(ctx);
     const int64_t group = tile_slices(ctx);
     ctx->stage_two = room.two;
-    ctx->stage_slices = group;
+    ctx->stage_cut = false;
     for (size_t ii = 0; ii < ctx->inst.size(); ++ii) {
         Inst& I = ctx->inst[ii];
         const double h = spacing_estimate(I);
@@ -588,6 +608,7 @@ void build_layout(pd_ctx* ctx, const HostState* S)
         int64_t nds = 0;
         if (ctx->mapping == PD_MAP_STAGED) {
             nds = build_staged(I, group, room, bank);
+            ctx->stage_cut |= static_cast<int64_t>(I.tiles.size()) > (I.nslices + group - 1) / group || I.phases.size() > I.tiles.size();
             if (ns + nds >= std::numeric_limits<int32_t>::max())
                 fail(PD_ERANGE, "device problem needs 2^31 or more nodes or slots");
             for (TileRec t : I.tiles) {
@@ -645,10 +666,8 @@ void build_layout(pd_ctx* ctx, const HostState* S)
         nsl += I.nslices;
         ns += nds;
     }
-    if (nn >= std::numeric_limits<int32_t>::max() || ns >= std::numeric_limits<int32_t>::max())
-        fail(PD_ERANGE, "device problem needs 2^31 or more nodes or slots");
-    if (nn + 1 >= (int64_t(1) << 24))
-        fail(PD_ERANGE, "device problem needs 2^24 or more node records (the gather uses 24-bit indices)");
+    if (ns >= std::numeric_limits<int32_t>::max()) fail(PD_ERANGE, "device problem needs 2^31 or more nodes or slots");
+    check_nodes(nn);
     ctx->nn = nn;
     ctx->nslices = nsl;
     ctx->ns = ns;
@@ -715,6 +734,14 @@ void build_layout(pd_ctx* ctx, const HostState* S)
     const double sentinel[6] = {1e10, 1e10, 1e10, 0.0, 0.0, 0.0};
     for (int b = 0; b < 2; ++b) upload(ctx->rec[b], sentinel, sizeof sentinel, static_cast<size_t>(nn) * 48, ctx->stream);
     sync(ctx);
+    struct Unfinished {  // (the uploads below need the flag)
+        pd_ctx* ctx;
+        ~Unfinished()
+        {
+            if (ctx) ctx->laid = false;
+        }
+    } unfinished{ctx};
+    ctx->laid = true;
     upload_params(ctx);
     upload_bcs(ctx);
     upload_stiffness(ctx);
@@ -730,6 +757,7 @@ void build_layout(pd_ctx* ctx, const HostState* S)
                      S ? S->a[ii].data() : nullptr);
         const double* sm = (S && !S->smax[ii].empty()) ? S->smax[ii].data() : nullptr;
         upload_col(ctx, I, S ? S->broken[ii].data() : nullptr, false, sm);
+        if (S && !S->bstep.empty()) upload_bstep(ctx, I, S->bstep[ii].data());
     }
     {  // device node of every user node, for readouts into device memory
         std::vector<int64_t> dn;
@@ -742,7 +770,9 @@ void build_layout(pd_ctx* ctx, const HostState* S)
     }
     ctx->cur = 0;
     ctx->vv_ahead = false;
-    ctx->built = true;
+    ctx->recut = false;
+    ctx->kept.reset();
+    unfinished.ctx = nullptr;
 }
 
 void validate_coords(int64_t n, const double* coords, double horizon)
@@ -822,7 +852,10 @@ void new_problem(pd_ctx* ctx, int32_t ninst, const int64_t* n, const double* con
     }
     (void)total;
     set_device(ctx);
-    ctx->built = false;
+    ctx->built = ctx->laid = ctx->recut = false;
+    ctx->kept.reset();
+    ctx->drop_graphs();
+    ctx->tape_valid = false;
     ctx->inst = std::move(insts);
     ctx->order = order == PD_ORDER_AUTO ? PD_ORDER_NATURAL : order;
     ctx->order_auto = order == PD_ORDER_AUTO;
@@ -833,7 +866,17 @@ void new_problem(pd_ctx* ctx, int32_t ninst, const int64_t* n, const double* con
     ctx->step = 0;
     ctx->a_valid = false;
     ctx->vv_ahead = false;
-    build_layout(ctx, nullptr);
+    const int W = ctx->mapping == PD_MAP_STAGED ? kWave : kWave / ctx->lanes;
+    int64_t nn = 0;
+    for (const Inst& I : ctx->inst) nn += (I.n + W - 1) / W * W;
+    check_nodes(nn);
+    ctx->built = true;
+    upload_stiffness(ctx);  // (the flags of what a problem holds)
+    upload_volumes(ctx);
+    upload_node_weights(ctx);
+    upload_body(ctx);
+    upload_laws(ctx);
+    upload_osb(ctx);
 }
 
 }  // namespace host

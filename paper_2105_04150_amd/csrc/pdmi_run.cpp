@@ -250,7 +250,7 @@ int get_nodes_dev(pd_ctx* ctx, int32_t inst, double* out, int what)
     return guarded(ctx, [&] {
         const Inst& I = instance(ctx, inst);
         require_device_buffer(ctx, out);
-        set_device(ctx);
+        laid_out(ctx);
         const int64_t* dn = ctx->unode.as<int64_t>() + I.user_off;
         const int64_t nn = ctx->nn;
         hipError_t e;
@@ -273,6 +273,12 @@ int get_nodes_dev(pd_ctx* ctx, int32_t inst, double* out, int what)
 // (broken flags and recorded break steps kept).
 void reset_laws(pd_ctx* ctx)
 {
+    if (!ctx->laid) {
+        if (ctx->kept)
+            for (auto& s : ctx->kept->smax) s.clear();
+        upload_laws(ctx);
+        return;
+    }
     std::vector<std::vector<uint8_t>> br;
     for (auto& I : ctx->inst) br.push_back(broken_of(ctx, I));
     upload_params(ctx);

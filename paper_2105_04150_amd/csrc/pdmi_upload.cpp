@@ -64,9 +64,12 @@ static InstParams make_params(const Inst& I, int32_t law_off)
     return p;
 }
 
+// The upload_* functions set the flags of what the problem holds; without a device problem
+// that is all (build_layout uploads everything).
 void upload_params(pd_ctx* ctx)
 {
     ctx->tape_valid = false;
+    if (!ctx->laid) return;
     std::vector<InstParams> p;
     int32_t law_off = 0;
     for (auto& I : ctx->inst) {
@@ -79,6 +82,7 @@ void upload_params(pd_ctx* ctx)
 void upload_bcs(pd_ctx* ctx)
 {
     ctx->tape_valid = false;
+    if (!ctx->laid) return;
     std::vector<int32_t> id(static_cast<size_t>(ctx->nn), kNodePad);
     std::vector<BCRec> recs;
     for (auto& I : ctx->inst) {
@@ -207,7 +211,7 @@ void upload_stiffness(pd_ctx* ctx, int32_t only)
     if (ctx->corr_k) {
         ctx->has_stiff = false;
         ctx->kslot.release();
-        upload_family_volumes(ctx);
+        if (ctx->laid) upload_family_volumes(ctx);
         upload_params(ctx);
         return;
     }
@@ -221,6 +225,7 @@ void upload_stiffness(pd_ctx* ctx, int32_t only)
     }
     const bool fresh = !ctx->has_stiff || !ctx->kslot.p;
     ctx->has_stiff = true;
+    if (!ctx->laid) return;
     if (fresh) {
         ctx->kslot.alloc((static_cast<size_t>(ctx->ns) + kSpareRows * kWave) * sizeof(double));
         hip_check(hipMemsetAsync(ctx->kslot.p, 0, ctx->kslot.bytes, ctx->stream), "hipMemsetAsync");
@@ -268,6 +273,7 @@ void upload_node_weights(pd_ctx* ctx)
         ctx->nw.release();
         return;
     }
+    if (!ctx->laid) return;
     std::vector<double> a(static_cast<size_t>(ctx->nn) + 1, 0.0), w(static_cast<size_t>(ctx->nn) + 1, 0.0);
     for (auto& I : ctx->inst)
         for (int64_t l = 0; l < I.n_pad; ++l) {
@@ -291,6 +297,7 @@ void upload_volumes(pd_ctx* ctx)
         ctx->vol.release();
         return;
     }
+    if (!ctx->laid) return;
     // entry nn: the sentinel record, volume 0; then spare zero entries for the state-based
     // kernels' fixed copy window
     std::vector<double> V(static_cast<size_t>(ctx->nn) + kCorrPad, 0.0);
@@ -316,6 +323,7 @@ void upload_osb(pd_ctx* ctx)
         ctx->minv.release();
         return;
     }
+    if (!ctx->laid) return;
     std::vector<double> b(static_cast<size_t>(ctx->nn) + 1, 0.0);
     for (auto& I : ctx->inst) {
         if (!I.osb) continue;
@@ -370,6 +378,7 @@ void upload_body(pd_ctx* ctx)
         ctx->bhat.release();
         return;
     }
+    if (!ctx->laid) return;
     const int64_t nn = ctx->nn;
     std::vector<double> B(static_cast<size_t>(3 * nn), 0.0);
     for (auto& I : ctx->inst) {
@@ -475,6 +484,7 @@ void upload_laws(pd_ctx* ctx)
         ctx->smax.release();
         return;
     }
+    if (!ctx->laid) return;
     ctx->laws.alloc(all.size() * sizeof(LawRec));
     upload(ctx->laws, all.data(), all.size() * sizeof(LawRec), 0, ctx->stream);
     const size_t nslot = static_cast<size_t>(ctx->ns) + kSpareRows * kWave;
