@@ -31,6 +31,7 @@
 #include <new>
 #include <numeric>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -265,6 +266,8 @@ inline unsigned n_threads()
     return std::max(1u, std::min(t, 16u));
 }
 
+// f(lo, hi) over shares of [0, n) in threads.  What f throws in one of them is thrown here once
+// all have ended; a share that finds no thread is done by the caller.
 template <typename F>
 void parallel_for(int64_t n, F&& f, int64_t least = 4096)
 {
@@ -274,13 +277,28 @@ void parallel_for(int64_t n, F&& f, int64_t least = 4096)
         return;
     }
     std::vector<std::thread> th;
+    th.reserve(nt);
+    std::vector<std::exception_ptr> thrown(nt);
     const int64_t chunk = (n + nt - 1) / nt;
     for (unsigned t = 0; t < nt; ++t) {
         const int64_t lo = t * chunk, hi = std::min(n, lo + chunk);
         if (lo >= hi) break;
-        th.emplace_back([&f, lo, hi] { f(lo, hi); });
+        auto share = [&f, &thrown, t, lo, hi] {
+            try {
+                f(lo, hi);
+            } catch (...) {
+                thrown[t] = std::current_exception();
+            }
+        };
+        try {
+            th.emplace_back(share);
+        } catch (const std::system_error&) {
+            share();
+        }
     }
     for (auto& x : th) x.join();
+    for (auto& e : thrown)
+        if (e) std::rethrow_exception(e);
 }
 
 // Setup-path copy from pageable host memory; returns once the source may be freed.

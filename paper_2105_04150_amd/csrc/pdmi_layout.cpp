@@ -246,14 +246,16 @@ static void bisect(CellNode* p, int64_t lo, int64_t hi, int64_t nsl, int64_t gro
             if (a.q[d] != b.q[d]) return a.q[d] < b.q[d];
         return a.id < b.id;
     });
+    std::thread t;
     if (depth > 0 && hi - lo > 8192) {
-        std::thread t([&] { bisect(p, lo, mid, left, group, depth - 1); });
-        bisect(p, mid, hi, nsl - left, group, depth - 1);
-        t.join();
-    } else {
-        bisect(p, lo, mid, left, group, 0);
-        bisect(p, mid, hi, nsl - left, group, 0);
+        try {
+            t = std::thread([&] { bisect(p, lo, mid, left, group, depth - 1); });
+        } catch (const std::system_error&) {  // no thread to be had: in turn
+        }
     }
+    if (!t.joinable()) bisect(p, lo, mid, left, group, 0);
+    bisect(p, mid, hi, nsl - left, group, depth > 0 ? depth - 1 : 0);  // (throws nothing)
+    if (t.joinable()) t.join();
 }
 
 // Device-local node order of one instance on the staged layout: compact slices, and within
@@ -274,7 +276,10 @@ static void slice_nodes(Inst& I, int64_t group, double h, std::vector<uint8_t>& 
     // bank class: 48-byte records at indices equal mod 16 share their LDS banks; on a lattice
     // a 4 x 4 patch of nodes covers all 16 classes
     bank.resize(static_cast<size_t>(I.n));
-    for (int64_t i = 0; i < I.n; ++i) bank[i] = static_cast<uint8_t>((c[i].q[0] + 12 * c[i].q[1] + 3 * c[i].q[2]) & 15);
+    for (int64_t i = 0; i < I.n; ++i) {
+        const auto q = [&](int d) { return static_cast<uint32_t>(c[i].q[d]); };
+        bank[i] = static_cast<uint8_t>((q(0) + 12 * q(1) + 3 * q(2)) & 15);
+    }
     bisect(c.data(), 0, I.n, (I.n + kWave - 1) / kWave, group, 4);
     I.perm.resize(static_cast<size_t>(I.n));
     I.iperm.resize(static_cast<size_t>(I.n));
