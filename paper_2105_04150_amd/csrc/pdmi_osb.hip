@@ -32,7 +32,7 @@
 //     the |xi| of the scalar state cancelling the 1 / |xi| of y / |y|.
 // A share of rows goes by short series (|d| < kMidRange, FP32 build kMidRange32) up to the
 // first block with a slot beyond them or at the decision edge, then by longer ones, and a
-// block with slots beyond those too slot by slot.
+// blocks with slots beyond those too slot by slot.
 #include "pdmi_step.h"
 
 namespace pdmi {
@@ -220,9 +220,11 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
         return high(m);
     };
     auto ent_at = [&](int t) { return ent[static_cast<int64_t>(t) * kWave]; };
-    // The pairs [t, end), with a look at every slot at the decision edge or beyond the long
-    // series (force: at all).
-    auto rows_apart = [&](int t, int end, bool force) {
+    // One block or more from pair t on, with a look at every slot at the decision edge or beyond the
+    // long series; goes on as long as blocks have slots beyond it.
+    auto rows_apart = [&](int t, int end, bool always) {
+        int block = t + B;
+        bool far = false;
         uint32_t e2 = ent_at(t), en = t + 1 < end ? ent_at(t + 1) : 0x80008000u;
         NodeRec r = staged_record(lrec, live_indices<true>(e2) & 0xffffu);
         int h = 0;
@@ -234,7 +236,8 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
             Real v = series(m, std::true_type{});
             bool live = !(e & kEntBroken);
             const int32_t hi = high(m);
-            const bool beyond = live && (hi >= hi_wpos || static_cast<uint32_t>(hi) >= hi_wneg || force);
+            const bool beyond = live && (hi >= hi_wpos || static_cast<uint32_t>(hi) >= hi_wneg);
+            far |= live && (hi >= static_cast<int32_t>(wrange) || static_cast<uint32_t>(hi) >= hi_wneg);
             if (__builtin_amdgcn_ballot_w64(beyond) != 0 && beyond) {
                 Real q;
                 if constexpr (FP32)
@@ -265,8 +268,14 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
                 ++t;
                 e2 = en;
                 en = t + 1 < end ? ent_at(t + 1) : 0x80008000u;
+                if (t == block) {
+                    if (!always && __builtin_amdgcn_ballot_w64(far) == 0) break;
+                    far = false;
+                    block += B;
+                }
             }
         }
+        return t;
     };
     uint32_t en[B];  // the next block's entries
     auto fetch = [&](int t) {
@@ -274,7 +283,9 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
         for (int u = 0; u < B; ++u) en[u] = ent_at(t + u);
     };
     // The pairs [t, end), after fetch(t), block by block by the short or the long series, up to
-    // the first block with a slot that it does not cover; that block is taken back.
+    // the first block with a slot that it does not cover; that block is taken back (covered: the
+    // long series does).
+    bool covered = true;
     auto rows = [&](int t, int end, auto wide) {
         const int32_t pos = wide ? hi_wpos : hi_pos;
         const uint32_t neg = wide ? hi_wneg : hi_neg;
@@ -308,27 +319,40 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
                 F0 = S0;
                 F1 = S1;
                 F2 = S2;
+                covered = __builtin_amdgcn_ballot_w64(himax >= hi_wpos || himin >= hi_wneg) == 0;
                 return t;
             }
         }
         return end;
     };
+    // The sentinel's term is exactly zero as long as its distance does not round; a node beyond
+    // that takes its slots apart, where padding and broken ones add nothing.
+    constexpr double kFar = FP32 ? 1e15 : 1e80;
+    auto near = [&](double x) { return fabs(x) < kFar; };
+    const bool moderate = near(X0) && near(X1) && near(X2) && (FP32 ? near(Uf0) && near(Uf1) && near(Uf2) : near(U0) && near(U1) && near(U2));
+    const bool apart = __builtin_amdgcn_ballot_w64(!moderate) != 0;
     auto share_rows = [&](int2 pr) {  // after fetch(pr.x)
+        if (apart) {
+            rows_apart(pr.x, pr.y, true);
+            return;
+        }
         int t = rows(pr.x, pr.y, std::false_type{});
 #pragma unroll 1
         while (t < pr.y) {  // once the short series does not do, the long one for the rest
-            fetch(t);
-            t = rows(t, pr.y, std::true_type{});
-            if (t >= pr.y) break;
-            rows_apart(t, min(t + B, pr.y), false);
-            t += B;
+            if (covered) {
+                fetch(t);
+                t = rows(t, pr.y, std::true_type{});
+                if (t >= pr.y) break;
+            }
+            t = rows_apart(t, pr.y, false);
+            covered = true;
         }
     };
     auto stage_weights = [&](const int32_t* l, int n) {
         if (PASS == 1) stage_pairs(pairs_in, l, n, tl.wv, lane, lpair);
         if (VOLN) stage_doubles(A.vol, l, n, tl.wv, lane, lvol);
     };
-    auto stage_phase = [&](int ph) {  // a later phase, or one staged again
+    auto stage_phase = [&](int ph) {  // a later phase
         const int2 pd = phases[T.phase + ph];
         __syncthreads();  // the records before are no longer read
         stage_records(A.rec_in, list + pd.x, pd.y, tl.wv, lane, lrec);
@@ -346,20 +370,6 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
         __builtin_amdgcn_s_setprio(0);
         if (pr.x < pr.y) share_rows(pr);
         __builtin_amdgcn_s_setprio(3);
-    }
-    // squares beyond the range of their type leave no finite sum: every slot in the general form
-    const bool unsound = !(__builtin_isfinite(D) && __builtin_isfinite(F0) && __builtin_isfinite(F1) && __builtin_isfinite(F2));
-    if (T.nphases <= 1 ? __builtin_amdgcn_ballot_w64(unsound) != 0 : __syncthreads_or(unsound) != 0) {
-        D = F0 = F1 = F2 = 0;
-#pragma unroll 1
-        for (int ph = 0; ph < T.nphases; ++ph) {
-            if (T.nphases > 1) {
-                stage_phase(ph);
-                tile_staged();
-            }
-            pr = tl.pairs(T, segs, ph);
-            if (pr.x < pr.y) rows_apart(pr.x, pr.y, true);
-        }
     }
     if constexpr (PASS == 0) {
         double E[1] = {D};

@@ -99,3 +99,32 @@ def test_a_free_node_feels_nothing_wherever_it_is(build, far):
         f = sim.force()
     assert not f[free].any()
     assert np.isfinite(f).all() and np.abs(f).max() > 0.0
+
+
+@pytest.mark.parametrize("build,far", [("f64", 1.0e99), ("f64", 1.0e120), ("f32", 1.0e18)])
+def test_a_free_node_has_no_dilation_wherever_it_is(build, far):
+    """The same with the state-based model: neither force nor dilation, and none is passed on."""
+    import paper_2105_04150_amd as pd
+    x = _lattice((9, 8, 7))
+    n, free = len(x), 250
+    out = []
+    for where in (far, 0.0):
+        with pd.Simulation(0, pd.PD_FP32 if build == "f32" else pd.PD_FP64) as sim:
+            sim.set_mapping("staged")
+            sim.build_family(x, 3.015 * DX)
+            sim.set_integrator("euler_cromer", 1.0e-9)
+            sim.set_material(2400.0, 1.0, 10.0, 0.0, DX ** 3)
+            sim.set_model("state_based", 1.4e10, 1.0e10)
+            rp, col = sim.family()
+            row = np.repeat(np.arange(n), np.diff(rp))
+            u = 1e-3 * x
+            u[free] = where
+            sim.set_state(u=u, broken=((row == free) | (col == free)).astype(np.uint8))
+            out.append((sim.dilation(), sim.force()))
+    for t, f in out:
+        assert t[free] == 0.0 and not f[free].any()
+        assert np.abs(t).max() > 0.0 and np.abs(f).max() > 0.0
+    # the rest is untouched by where the free node is (its wavefront may take another series)
+    eps = 1e-5 if build == "f32" else 1e-12
+    assert np.abs(out[0][0] - out[1][0]).max() <= eps * np.abs(out[1][0]).max()
+    assert np.abs(out[0][1] - out[1][1]).max() <= eps * np.abs(out[1][1]).max()
