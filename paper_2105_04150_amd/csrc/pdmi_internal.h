@@ -127,9 +127,9 @@ struct InstParams {
     // stiffness corrections evaluated per slot (kernels with CORR): the conical profile
     // max(1 - |xi|/delta, 0), the partial volume clamp((delta + dx/2 - |xi|)/dx, 0, 1), the
     // surface factor 2 V0 / (V_i + V_j) over family volumes
-    double cr_idelta;  // 1/delta (0 without the profile)
+    double cr_hidelta; // 1 / (2 delta) (0 without the profile)
     double cr_pvhi;    // (delta + dx/2)/dx (1 without partial volumes)
-    double cr_idx;     // 1/dx (0 without)
+    double cr_hidx;    // 1 / (2 dx) (0 without)
     double cr_2v0;     // 2 V0 (2 without the surface factor, whose family volumes are then 1)
 };
 

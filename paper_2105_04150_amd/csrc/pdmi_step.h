@@ -327,26 +327,30 @@ __device__ __forceinline__ BondWeight bond_weight(const StepArgs& A, const InstP
 constexpr int kCorrNone = 0, kCorrPlain = 1, kCorrPartial = 2;
 
 // The correction factor of a slot of squared reference length L2, without the instance's
-// 2 V0 of the surface factor; V the sum of the two ends' family volumes.  The parameters of a
-// factor that the instance does not have make it 1.  One reciprocal square root
-// t = 1 / (L V) gives both 1 / L = V t and 1 / V = L t.
+// 2 V0 of the surface factor (FP64: and four times it); V the sum of the two ends' family
+// volumes.  The parameters of a factor that the instance does not have make it 1.  One
+// reciprocal square root t = 1 / (L V) gives both 1 / L = V t and 1 / V = L t; its Newton step
+// as in slot_mid, t (3 - x t^2) = 2 t.
+struct CorrCoef {
+    double hidelta, hidx, pvhi;  // 1 / (2 delta), 1 / (2 dx), (delta + dx/2) / dx
+};
 template <int CORR>
-__device__ __forceinline__ double corr_factor(const InstParams& P, double L2, double V)
+__device__ __forceinline__ double corr_factor(const CorrCoef& P, double L2, double V)
 {
-    const double t = rsq64<1>(L2 * (V * V));
-    const double L = L2 * (V * t);
-    double f = fmax(__builtin_fma(-L, P.cr_idelta, 1.0), 0.0);
-    if constexpr (CORR == kCorrPartial) f *= fmin(fmax(__builtin_fma(-L, P.cr_idx, P.cr_pvhi), 0.0), 1.0);
-    return f * (L * t);
+    const double x = L2 * (V * V), t = __builtin_amdgcn_rsq(x), t2 = t * __builtin_fma(-x, t * t, 3.0);
+    const double L = L2 * (V * t2);  // twice |xi|
+    double f = fmax(__builtin_fma(-L, P.hidelta, 1.0), 0.0);
+    if constexpr (CORR == kCorrPartial) f *= fmin(fmax(__builtin_fma(-L, P.hidx, P.pvhi), 0.0), 1.0);
+    return f * (L * t2);
 }
 
 template <int CORR>
-__device__ __forceinline__ float corr_factor(const InstParams& P, float L2, float V)
+__device__ __forceinline__ float corr_factor(const CorrCoef& P, float L2, float V)
 {
-    const float L = L2 * __builtin_amdgcn_rsqf(L2);
-    float f = fmaxf(__builtin_fmaf(-L, static_cast<float>(P.cr_idelta), 1.0f), 0.0f);
+    const float L = 2.0f * (L2 * __builtin_amdgcn_rsqf(L2));
+    float f = fmaxf(__builtin_fmaf(-L, static_cast<float>(P.hidelta), 1.0f), 0.0f);
     if constexpr (CORR == kCorrPartial)
-        f *= fminf(fmaxf(__builtin_fmaf(-L, static_cast<float>(P.cr_idx), static_cast<float>(P.cr_pvhi)), 0.0f), 1.0f);
+        f *= fminf(fmaxf(__builtin_fmaf(-L, static_cast<float>(P.hidx), static_cast<float>(P.pvhi)), 0.0f), 1.0f);
     return f * __builtin_amdgcn_rcpf(V);
 }
 
@@ -662,6 +666,15 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 Uf1 = __uint_as_float(static_cast<uint32_t>(ub1 >> 32)),
                 Uf2 = __uint_as_float(static_cast<uint32_t>(ub2));  // FP32 build
     const double fvi = CORR ? A.cfv[node] : 0.0;
+    // scalar loads, once: the kernel's own stores make the compiler load a parameter again for
+    // every slot otherwise (corrections 2 % of a step)
+    CorrCoef cc{0.0, 0.0, 1.0};
+    if (CORR) {
+        const auto& Q = *(const __attribute__((address_space(4))) InstParams*)(params + T.inst);
+        cc = CorrCoef{Q.cr_hidelta, CORR == kCorrPartial ? Q.cr_hidx : 0.0, CORR == kCorrPartial ? Q.cr_pvhi : 1.0};
+        asm volatile("" : "+s"(cc.hidelta));
+        if (CORR == kCorrPartial) asm volatile("" : "+s"(cc.hidx), "+s"(cc.pvhi));
+    }
     const float q0f = static_cast<float>(P.q0);
     // where the levels end, as high words of a slot's d: their ranges, above zero the decision edge too
     const int32_t edge = !BREAKS ? std::numeric_limits<int32_t>::max() : FP32 ? P.hi_edge32 : P.hi_edge;
@@ -681,7 +694,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     // density, does not; of the corrections the ratio to 2 V0)
     auto weight = [&](uint32_t idx, double k, Real L2, double fv, double own) -> Real {
         if constexpr (CORR != kCorrNone) {
-            return corr_factor<CORR>(P, L2, static_cast<Real>(FP32 ? (fv + lw[idx]) * own : fv + lw[idx]));
+            return corr_factor<CORR>(cc, L2, static_cast<Real>(FP32 ? (fv + lw[idx]) * own : fv + lw[idx]));
         } else if constexpr (NODEW) {
             const double v = lw[idx];
             return static_cast<Real>(STIFF ? k * v : FP32 ? own * v : v);
@@ -1010,7 +1023,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     tile_reduce(tl, reinterpret_cast<double*>(lds), G);
     if (tl.sub > 0 || !tl.has) return;
     const double share = FP32 ? kMidScale32 * (!WEIGHT || CORR ? P.c * P.volume : 1.0)
-                              : kMidScale * (CORR ? P.cr_2v0 : 1.0) *
+                              : kMidScale * (CORR ? 0.25 * P.cr_2v0 : 1.0) *
                                     (KNODE ? A.na[node] : STIFF ? (VOLN ? 1.0 : P.volume) : VOLN ? P.c : P.c * P.volume);
     node_update<MODE, FP32>(A, P, node, U0, U1, U2, share * G[0], share * G[1], share * G[2]);
 }

@@ -54,9 +54,9 @@ static InstParams make_params(const Inst& I, int32_t law_off)
     p.cr_pvhi = 1.0;
     p.cr_2v0 = 2.0;
     if (I.has_corr) {
-        if (I.corr.micromodulus == PD_MICRO_CONICAL) p.cr_idelta = 1.0 / I.corr.delta;
+        if (I.corr.micromodulus == PD_MICRO_CONICAL) p.cr_hidelta = 0.5 / I.corr.delta;
         if (I.corr.partial_volumes) {
-            p.cr_idx = 1.0 / I.corr.dx;
+            p.cr_hidx = 0.5 / I.corr.dx;
             p.cr_pvhi = (I.corr.delta + 0.5 * I.corr.dx) / I.corr.dx;
         }
         if (I.corr.surface) p.cr_2v0 = 2.0 * I.corr_v0;
