@@ -52,6 +52,21 @@ __device__ __forceinline__ double adj_slot(bool active, const double2 p0, const 
     return active ? h * Vj * sr * yn : 0.0;
 }
 
+// Adjoint velocities: nn + 1 pairs (components 0 and 1), then nn + 1 third components (the last
+// node, the sentinel, zero): a 16-byte and an 8-byte load a node, also on its way into LDS.
+__device__ __forceinline__ void nu_load(const double* nu, int64_t nn, int64_t node, double (&n)[3])
+{
+    const double2 a = reinterpret_cast<const double2*>(nu)[node];
+    n[0] = a.x;
+    n[1] = a.y;
+    n[2] = nu[2 * (nn + 1) + node];
+}
+__device__ __forceinline__ void nu_store(double* nu, int64_t nn, int64_t node, const double (&n)[3])
+{
+    reinterpret_cast<double2*>(nu)[node] = double2{n[0], n[1]};
+    nu[2 * (nn + 1) + node] = n[2];
+}
+
 // Node tail of a reverse pass: body-force gradient, boundary masks, lam_u and next nu.
 __device__ __forceinline__ void adj_node(const AdjArgs& A, const InstParams& P, int64_t node, const double ni[3],
                                          const double J[3], double h)
@@ -64,13 +79,15 @@ __device__ __forceinline__ void adj_node(const AdjArgs& A, const InstParams& P, 
     if (P.has_body)
         A.gacc[node] += h * (A.bhat[node] * ni[0] + A.bhat[nn + node] * ni[1] + A.bhat[2 * nn + node] * ni[2]);
     const double damp = 1.0 - A.dt * P.eta / P.rho;
+    double out[3];
     for (int d = 0; d < 3; ++d) {
         const int kind = (code >> (2 * d)) & 3;
         const double lu = A.lam_u[d * nn + node];
         const double ln = (kind == 1 ? 0.0 : lu) + h * J[d];
         A.lam_u[d * nn + node] = ln;
-        A.nu_out[3 * node + d] = kind == 0 ? damp * ni[d] + A.dt * ln : 0.0;
+        out[d] = kind == 0 ? damp * ni[d] + A.dt * ln : 0.0;
     }
+    nu_store(A.nu_out, nn, node, out);
 }
 
 // Per-slot streams of one row (index ds) and the neighbour data they point at.
@@ -97,9 +114,7 @@ __device__ __forceinline__ void adj_load(const AdjArgs& A, const InstParams& P, 
     r.p0 = rec[3 * j];
     r.p1 = rec[3 * j + 1];
     r.p2 = rec[3 * j + 2];
-    r.nj[0] = A.nu_in[3 * j];
-    r.nj[1] = A.nu_in[3 * j + 1];
-    r.nj[2] = A.nu_in[3 * j + 2];
+    nu_load(A.nu_in, A.nn, j, r.nj);
     r.kb = KM == kKSlot ? A.kslot[ds] : KM == kKNode ? ai * A.na[j] : P.c;
     r.Vj = VOLN ? A.vol[j] : P.volume;
     r.g = A.grad[ds];
@@ -122,7 +137,8 @@ __global__ __launch_bounds__(kBlock) void adjoint_sliced(AdjArgs A)
     const int64_t node = slice * W + w;
     const double2* __restrict__ rec = reinterpret_cast<const double2*>(A.rec);
     const double2 o0 = rec[3 * node], o1 = rec[3 * node + 1], o2 = rec[3 * node + 2];
-    const double ni[3] = {A.nu_in[3 * node], A.nu_in[3 * node + 1], A.nu_in[3 * node + 2]};
+    double ni[3];
+    nu_load(A.nu_in, A.nn, node, ni);
     const double Vi = VOLN ? A.vol[node] : P.volume;
     const double ai = KM == kKNode ? A.na[node] : 0.0;
     const double h = A.dt / P.rho;
@@ -151,13 +167,28 @@ __global__ __launch_bounds__(kBlock) void adjoint_sliced(AdjArgs A)
     adj_node(A, P, node, ni, J, h);
 }
 
+typedef int int2v __attribute__((ext_vector_type(2)));
+typedef double double2v __attribute__((ext_vector_type(2)));
+template <bool NT, typename V>
+__device__ __forceinline__ V stream_load(const V* p)
+{
+    if constexpr (NT)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
 // Staged layout: one workgroup a tile (pdmi_tile.h), one lane a node, 2 to 8 wavefronts
 // a slice.  The tile's records (x, u^k), adjoint velocities and per-node weights are copied into LDS
 // once; the per-slot streams (entries, break steps, stiffness, gradient: 28 to 36 bytes a
 // slot, the pass's bound beside latency) come a row pair ahead, 16 bytes a lane and load.
 // Padding entries point at the sentinel (far record, zero adjoint velocity and weights).
 // Partial sums of J meet in LDS in a fixed order.
-template <int KM, bool VOLN>
+// NT: the streams bypass the caches, for problems whose streams exceed them anyway (they then
+// leave the nodes' records in L2; 54M slots: 431 us a pass, 383 with, 5.4M: 42.5 and 48.9).
+// With the scalar addresses and three loads a node for its adjoint velocity 5.4M slots take 38.9,
+// with six loads and four addresses a lane 42.8.
+template <int KM, bool VOLN, bool NT>
 __global__ __launch_bounds__(kTileWaves * kWave, 4) void adjoint_lds(AdjArgs A, const TileRec* __restrict__ tiles,
                                                                      const int2* __restrict__ phases,
                                                                      const int2* __restrict__ segs,
@@ -171,27 +202,41 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void adjoint_lds(AdjArgs A, 
     const int lane = tl.lane;
     double2* const lrec = lds;
     const int R = A.stage_max + 1;
-    double* const lnu = reinterpret_cast<double*>(lrec + 3 * R);
-    double* const lvol = lnu + 3 * R;
+    double2* const lnu = lrec + 3 * R;                            // components 0 and 1
+    double* const lnu2 = reinterpret_cast<double*>(lnu + R);      // 2
+    double* const lvol = lnu2 + R;
     double* const lna = lvol + (VOLN ? R : 0);
-    if (T.nphases > 0) stage_records(A.rec, list + T.list, T.n, tl.wv, lane, lrec);
+    auto stage_weights = [&](const int32_t* l, int n) {
+        stage_pairs(reinterpret_cast<const double2*>(A.nu_in), l, n, tl.wv, lane, lnu);
+        stage_doubles(A.nu_in + 2 * (A.nn + 1), l, n, tl.wv, lane, lnu2);
+        if (VOLN) stage_doubles(A.vol, l, n, tl.wv, lane, lvol);
+        if (KNODE) stage_doubles(A.na, l, n, tl.wv, lane, lna);
+    };
+    if (T.nphases > 0) {
+        stage_records(A.rec, list + T.list, T.n, tl.wv, lane, lrec);
+        stage_weights(list + T.list, T.n);
+    }
     const InstParams& P = A.params[T.inst];
+    // the parameters that every slot needs as scalars, once: the kernel's own stores make the
+    // compiler load them again for every row pair otherwise
+    const auto& Q = *(const __attribute__((address_space(4))) InstParams*)(A.params + T.inst);
+    double c = Q.c, volume = Q.volume, h = A.dt / Q.rho;
+    asm volatile("" : "+s"(c), "+s"(volume));
     const int64_t node = tl.node(T);
     const double2* __restrict__ rec = reinterpret_cast<const double2*>(A.rec);
     const double2 o0 = rec[3 * node], o1 = rec[3 * node + 1], o2 = rec[3 * node + 2];
-    const double ni[3] = {A.nu_in[3 * node], A.nu_in[3 * node + 1], A.nu_in[3 * node + 2]};
-    const double Vi = VOLN ? A.vol[node] : P.volume;
+    double ni[3];
+    nu_load(A.nu_in, A.nn, node, ni);
+    const double Vi = VOLN ? A.vol[node] : volume;
     const double ai = KNODE ? A.na[node] : 0.0;
-    const double h = A.dt / P.rho;
-    const uint32_t* __restrict__ ent = reinterpret_cast<const uint32_t*>(A.ent) + lane;
-    const int2* __restrict__ bstep = reinterpret_cast<const int2*>(A.bstep) + lane;
-    const double2* __restrict__ kslot = reinterpret_cast<const double2*>(A.kslot) + lane;
-    double2* __restrict__ grad = reinterpret_cast<double2*>(A.grad) + lane;
 
     // sentinels: record far from every node; zero adjoint velocity and weights
     if (threadIdx.x < 3) {
         lrec[threadIdx.x] = threadIdx.x == 0 ? double2{1e10, 1e10} : threadIdx.x == 1 ? double2{1e10, 0.0} : double2{0.0, 0.0};
-        lnu[threadIdx.x] = 0.0;
+    }
+    if (threadIdx.x == 0) {
+        lnu[0] = double2{0.0, 0.0};
+        lnu2[0] = 0.0;
     }
     if (VOLN && threadIdx.x == 0) lvol[0] = 0.0;
     if (KNODE && threadIdx.x == 0) lna[0] = 0.0;
@@ -203,22 +248,23 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void adjoint_lds(AdjArgs A, 
         int2 bs;
         double2 kr, gr;
     };
+    // a row pair's words: uniform addresses, the lane as their offset (four addresses a lane are
+    // eight registers, which the loop does not have)
+    auto pair_of = [&](auto* p, int t) { return p + static_cast<int64_t>(t) * (2 * kWave); };
     auto streams = [&](int t) {
-        const int64_t at = static_cast<int64_t>(t) * kWave;
-        return Streams{ent[at], bstep[at], STIFF ? kslot[at] : double2{0.0, 0.0}, grad[at]};
+        const int2v bs = stream_load<NT>(reinterpret_cast<const int2v*>(pair_of(A.bstep, t)) + lane);
+        const double2v kr = STIFF ? stream_load<NT>(reinterpret_cast<const double2v*>(pair_of(A.kslot, t)) + lane) : double2v{0.0, 0.0};
+        const double2v gr = stream_load<NT>(reinterpret_cast<const double2v*>(pair_of(A.grad, t)) + lane);
+        return Streams{reinterpret_cast<const uint32_t*>(pair_of(A.ent, t))[lane], int2{bs.x, bs.y}, double2{kr.x, kr.y},
+                       double2{gr.x, gr.y}};
     };
     auto slot = [&](const NodeRec& r, uint32_t idx, bool active, double kr) {
-        const double nj[3] = {lnu[3 * idx], lnu[3 * idx + 1], lnu[3 * idx + 2]};
-        const double kb = STIFF ? kr : KNODE ? ai * lna[idx] : P.c;
-        const double Vj = VOLN ? lvol[idx] : P.volume;
+        const double2 n01 = lnu[idx];
+        const double nj[3] = {n01.x, n01.y, lnu2[idx]};
+        const double kb = STIFF ? kr : KNODE ? ai * lna[idx] : c;
+        const double Vj = VOLN ? lvol[idx] : volume;
         return adj_slot(active, r.p0, r.p1, r.p2, o0.x, o0.y, o1.x, o1.y, o2.x, o2.y, nj, ni, Vi, Vj, kb, h, J);
     };
-    auto stage_weights = [&](const int32_t* l, int n) {
-        stage_triples(A.nu_in, l, n, tl.wv, lane, lnu);
-        if (VOLN) stage_doubles(A.vol, l, n, tl.wv, lane, lvol);
-        if (KNODE) stage_doubles(A.na, l, n, tl.wv, lane, lna);
-    };
-    if (T.nphases > 0) stage_weights(list + T.list, T.n);
 #pragma unroll 1
     for (int ph = 0; ph < T.nphases; ++ph) {
         if (ph > 0) {
@@ -239,7 +285,12 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void adjoint_lds(AdjArgs A, 
             __builtin_amdgcn_sched_barrier(0);  // the two interleaved do not fit the registers
             const double db = slot(staged_record(lrec, ib), ib, k < a.bs.y, a.kr.y);
             // inactive slots keep their gradient (the increment is zero)
-            grad[static_cast<int64_t>(t) * kWave] = double2{a.gr.x + da, a.gr.y + db};
+            double2v* const out = reinterpret_cast<double2v*>(pair_of(A.grad, t)) + lane;
+            const double2v sum{a.gr.x + da, a.gr.y + db};
+            if constexpr (NT)
+                __builtin_nontemporal_store(sum, out);
+            else
+                *out = sum;
             a = b;
         }
         __builtin_amdgcn_s_setprio(3);
@@ -287,10 +338,12 @@ __global__ __launch_bounds__(kBlock) void adj_nu0_kernel(double* nu, const doubl
     if (i >= nn) return;
     const int32_t id = bc_id[i];
     const int code = id >= 0 ? bc[id].code : 0;
+    double out[3];
     for (int d = 0; d < 3; ++d) {
         const bool free_comp = id != kNodePad && ((code >> (2 * d)) & 3) == 0;
-        nu[3 * i + d] = free_comp ? dt * lam_u[d * nn + i] : 0.0;
+        out[d] = free_comp ? dt * lam_u[d * nn + i] : 0.0;
     }
+    nu_store(nu, nn, i, out);
 }
 
 // Deterministic single-workgroup sum.
@@ -320,10 +373,12 @@ void adj_launch_sliced(const AdjArgs& a, hipStream_t s)
                        dim3(kBlock), 0, s, a);
 }
 
+constexpr int64_t kCacheBytes = int64_t(256) << 20;  // the memory-side cache
 template <int KM, bool VOLN>
 hipError_t adj_launch_staged(const AdjArgs& a, hipStream_t s)
 {
-    auto* kernel = &adjoint_lds<KM, VOLN>;
+    const bool nt = a.ns * (2 + 4 + 8 + (KM == kKSlot ? 8 : 0)) > kCacheBytes;
+    auto* kernel = nt ? &adjoint_lds<KM, VOLN, true> : &adjoint_lds<KM, VOLN, false>;
     const size_t bytes = tile_lds(a.stage_max, 48 + 24 + (VOLN ? 8 : 0) + (KM == kKNode ? 8 : 0));
     const hipError_t e = tile_room(reinterpret_cast<const void*>(kernel), bytes);
     if (e != hipSuccess) return e;

@@ -103,7 +103,7 @@ int pd_adj_backward(pd_ctx* ctx, int64_t recording, int64_t m, const int64_t* se
         set_device(ctx);
         hipStream_t st = ctx->stream;
         const int64_t nn = ctx->nn, ns = ctx->ns, S = ctx->tape_every, T = ctx->tape_nsteps, step0 = ctx->tape_step0;
-        // adjoint velocities: nn + 1 triples (the last one, the sentinel's, zero)
+        // adjoint velocities of nn + 1 nodes (the last one's, the sentinel's, zero)
         const size_t Rb = rec_bytes(nn), Vb = static_cast<size_t>(3 * nn) * sizeof(double),
                      Nb = static_cast<size_t>(3 * (nn + 1)) * sizeof(double);
         const int64_t Lmax = std::min(S, T);
@@ -159,6 +159,7 @@ int pd_adj_backward(pd_ctx* ctx, int64_t recording, int64_t m, const int64_t* se
         a.bc = ctx->bc.as<BCRec>();
         a.nn = nn;
         a.nslices = ctx->nslices;
+        a.ns = ns;
         a.dt = ctx->dt;
         const bool staged = ctx->mapping == PD_MAP_STAGED;
         int nin = 0;

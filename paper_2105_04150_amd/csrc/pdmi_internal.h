@@ -264,7 +264,7 @@ constexpr int32_t kNeverBroke = 0x7fffffff;
 constexpr int32_t kBrokeBefore = -0x7fffffff - 1;
 
 // One reverse pass k.  nu_in holds the adjoint of the unconstrained velocity of level
-// k+1 (AoS, (nn+1) x 3, the last entry zero); lam_u (SoA) the adjoint of u^{k+1} on
+// k+1 ((nn+1) pairs, then nn+1 third components, the last node's zero); lam_u (SoA) the adjoint of u^{k+1} on
 // entry and of u^k on exit; nu_out receives the next pass's nu.
 struct AdjArgs {
     const double* rec;          // node records (x, u^k), nn+1 of them
@@ -294,6 +294,7 @@ struct AdjArgs {
     const BCRec* bc;
     int64_t nn;
     int64_t nslices;
+    int64_t ns;                 // device slots
     int64_t k;                  // pass index
     double dt;
 };

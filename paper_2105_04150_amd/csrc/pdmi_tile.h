@@ -109,8 +109,7 @@ __device__ __forceinline__ void stage(const void* src, const int32_t* __restrict
     }
 }
 
-// The listed nodes' records to lrec's record 1 on; a double, a pair, three doubles each to dst's
-// second on.  (No templates: the host's pass of a kernel would check the load's size against
+// The listed nodes' records to lrec's record 1 on; a double, a pair each to dst's second on.  (No templates: the host's pass of a kernel would check the load's size against
 // the host's features.)
 __device__ __forceinline__ void stage_records(const double* rec, const int32_t* __restrict__ list, int n, int wv, int lane,
                                               double2* lrec)
@@ -127,12 +126,6 @@ __device__ __forceinline__ void stage_pairs(const double2* src, const int32_t* _
 {
     stage<16, 1>(src, list, n, wv, lane, dst + 1);
 }
-__device__ __forceinline__ void stage_triples(const double* src, const int32_t* __restrict__ list, int n, int wv, int lane,
-                                              double* dst)
-{
-    stage<4, 6>(src, list, n, wv, lane, dst + 3);
-}
-
 // After the copies: every wavefront's loads have landed (s_waitcnt vmcnt = 0) and all see them.
 __device__ __forceinline__ void tile_staged()
 {
