@@ -35,8 +35,8 @@ int pd_adj_forward(pd_ctx* ctx, int64_t nsteps, int32_t ckpt_every, int64_t* rec
         const int64_t step0 = ctx->step;
         if (ckpt_every == 1) {
             // the whole trajectory: step k reads level k of the tape and writes level k+1
-            // straight into it (every level first gets the positions, sentinel and spare
-            // records); the last level then becomes the current state
+            // straight into it (every level first gets the positions and the
+            // sentinel); the last level then becomes the current state
             ctx->ck.alloc(static_cast<size_t>(nsteps + 1) * Rb);
             char* tape = ctx->ck.as<char>();
             for (int64_t k = 0; k <= nsteps; ++k)
@@ -121,7 +121,7 @@ int pd_adj_backward(pd_ctx* ctx, int64_t recording, int64_t m, const int64_t* se
         dsn.alloc(static_cast<size_t>(m) * sizeof(int64_t));
         ddl.alloc(static_cast<size_t>(3 * m) * sizeof(double));
         auto at = [](const DevBuf& b, size_t off) { return static_cast<char*>(b.p) + off; };
-        // every level carries the positions, the sentinel and the spare records
+        // every level carries the positions and the sentinel
         for (int64_t s = 1; s < Lmax; ++s)
             hip_check(hipMemcpyAsync(at(traj, s * Rb), ctx->rec[ctx->cur].p, Rb, hipMemcpyDeviceToDevice, st),
                       "trajectory init");

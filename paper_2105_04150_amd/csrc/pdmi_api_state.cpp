@@ -575,7 +575,7 @@ int pd_get_info(const pd_ctx* ctx, pd_info* info)
     info->model_bytes_per_step = static_cast<double>(nnz) * (4.0 + (ctx->has_stiff ? 8.0 : 0.0)) +
                                  static_cast<double>(n) * per_node;
     if (ctx->has_osb)  // two passes: the neighbour index twice; x and u read again, the node pair
-                       // {theta/m, 1/m} written, then read, with 1/m read by the first pass
+                       // {a, b - a} written, then read, with 1/m read by the first pass
         info->model_bytes_per_step += static_cast<double>(nnz) * 4.0 + static_cast<double>(n) * (48.0 + 16.0 + 16.0 + 8.0);
     return PD_OK;
 }

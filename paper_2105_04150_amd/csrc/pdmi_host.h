@@ -118,7 +118,7 @@ struct Inst {
     std::vector<TileRec> tiles;
     std::vector<int2> phases, segs;
     std::vector<int32_t> list;
-    std::vector<int64_t> tile_rows;  // slot rows of every tile's longest slice
+    std::vector<int64_t> tile_rows;  // slot rows of every tile, all its slices and phases
     std::vector<uint16_t> ent_idx;   // record index of every device slot in its phase (0: padding)
     std::vector<int64_t> rev_slot;   // user slot of the reverse bond (filled on first use)
     bool k_sym = true;               // both slots of every bond carry the same stiffness
@@ -150,7 +150,7 @@ struct pd_ctx {
     std::vector<pdmi::host::Inst> inst;
     int order = PD_ORDER_NATURAL;
     bool order_auto = false;         // the autotuner may change the device node order
-    int lanes = pdmi::host::kDefaultLanes;  // sliced: lanes per node; staged: wavefronts per slice
+    int lanes = pdmi::host::kDefaultLanes;  // sliced: lanes per node; staged: as given, of no effect
     int mapping = PD_MAP_SLICED;
     int scheme = PD_EULER_CROMER;
     double dt = 1.0e-7;
@@ -181,7 +181,7 @@ struct pd_ctx {
         step_base, status, phi, tiles, phases, segs, list, ent;
     DevBuf force, rset, rsum;        // force readout: F (SoA), node list and sum of a resultant
     DevBuf laws, cls, smax;          // damage laws, per-slot law (several per instance), stretch state
-    DevBuf osb, minv;                // state-based model: node pairs {theta/m, 1/m}, 1/m
+    DevBuf osb, minv;                // state-based model: node pairs {a, b - a}, 1/m
     DevBuf cfv;                      // corrections per slot: family volume per node
     DevBuf unode;                    // device node of every user node (instances concatenated)
 

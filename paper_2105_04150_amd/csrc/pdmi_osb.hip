@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
     uint32_t en[B];  // the next block's entries
     auto fetch = [&](int t) {
 #pragma unroll
-        for (int u = 0; u < B; ++u) en[u] = ent_at(t + u);
+        for (int u = 0; u < B; ++u) en[u] = (ent + static_cast<int64_t>(t) * kWave)[u * kWave];
     };
     // The pairs [t, end), after fetch(t), block by block by the short or the long series, up to
     // the first block with a slot that it does not cover; that block is taken back (covered: the
@@ -305,7 +305,8 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void osb_staged(StepArgs A, 
                 if (t + u >= end) break;
                 const uint32_t ia = v & 0xffffu, ib = v >> 16;
                 const NodeRec rb = staged_record(lrec, ib);
-                if (u + 1 < B) v = live_indices<true>(t + u + 1 < end ? e[u + 1] : 0x80008000u);
+                // (past the share's end: another share's entry, read but not added)
+                if (u + 1 < B) v = live_indices<true>(e[u + 1]);
                 __builtin_amdgcn_sched_barrier(0);
                 const int32_t ha = one(ra, ia, wide);
                 if (u + 1 < B) ra = staged_record(lrec, v & 0xffffu);

@@ -21,8 +21,10 @@
 // The FP64 numerator cancels: q carries an absolute error of a few units of 2^-53 (plus
 // 1e-14 relative from 1/|xi|), the same order as the rounding of the oracle's own
 // (|y| - |xi|)/|xi|, and is exactly zero for an unstretched bond (y = xi).
-// 1 - (1+q)^(-1/2) is summed as its binomial series for |q| < 4e-3, so the force adds no
-// second cancellation.  The FP32 kernels keep the cancellation-free numerator
+// The sliced kernel sums 1 - (1+q)^(-1/2) as its binomial series for |q| < 4e-3, so the force
+// adds no second cancellation; the staged kernel takes the same force from an even series
+// about the mean square length (slot_mid).  Both carry about 1e-14 a slot beside the
+// numerator's rounding.  The FP32 kernels keep the cancellation-free numerator
 // eta.(xi + y): in single precision the difference of squares would lose most digits of
 // a small stretch.
 // The break decision is made on q except within a narrow margin around the threshold,
@@ -35,10 +37,11 @@
 // readout of the quasi-static examples, Sec. 6).
 //
 // EXT variants carry the bond-model branch: no-failure zones and n-linear damage laws
-// per bond class.  Their common path adds every live bond's elastic contribution; a slot
-// over the instance's threshold (or already softened) then takes a rare branch that asks
-// its damage state for a weight w and moves its contribution from 1 to w (breaking:
-// w = 0).  Problems without zones or laws run the plain kernels.
+// per bond class.  A slot over the instance's threshold (or already softened) takes a rare
+// branch that asks its damage state for a weight w (breaking: w = 0): the sliced kernel's common
+// path adds every live bond's elastic contribution and the branch moves it from 1 to w, the
+// staged one leaves such slots out and adds w times theirs.  Problems without zones or laws
+// run the plain kernels.
 #pragma once
 
 #include "pdmi_tile.h"
@@ -49,15 +52,10 @@ namespace pdmi {
 namespace {
 
 // What the bond-model branch needs of a slot: its q and its elastic contribution
-// coef * y to the force density (FP64 and FP32 builds).
+// coef * y to the force density.
 struct SlotTerm {
     double q, coef, y0, y1, y2;
 };
-struct SlotTerm32 {
-    double q;
-    float coef, y0, y1, y2;
-};
-
 // Contribution of one slot.  live: the slot holds an intact bond; breakable: the bond may
 // break in this pass (intact, outside the no-failure zones, not a force evaluation).
 // (X, U) are the owner's position and displacement, p0..p2 the neighbour's node record,
@@ -218,47 +216,6 @@ __device__ __forceinline__ MidTerm<float> slot_mid32(const NodeRec& n, double X0
     m.d = d;
     m.hi = static_cast<int32_t>(__float_as_uint(d));
     return m;
-}
-
-// FP32 bond arithmetic (same formulas): the bond vector is formed in f64 from the f64
-// coordinates and rounded once, displacements are the f32 values of the records.
-// 1 - (1+q)^(-1/2) uses four series terms (below 1.3e-10 relative for |q| < 4e-3).
-__device__ __forceinline__ bool slot_force32(bool live, bool breakable, const double2 p0, const double2 p1, const double2 p2,
-                                             double X0, double X1, double X2, float U0, float U1, float U2,
-                                             float kv, float q0, float& F0, float& F1, float& F2, SlotTerm32& st)
-{
-    const float xi0 = static_cast<float>(p0.x - X0), xi1 = static_cast<float>(p0.y - X1),
-                xi2 = static_cast<float>(p1.x - X2);
-    const uint64_t b1 = __double_as_longlong(p1.y), b2 = __double_as_longlong(p2.x);
-    const float uj0 = __uint_as_float(static_cast<uint32_t>(b1)), uj1 = __uint_as_float(static_cast<uint32_t>(b1 >> 32)),
-                uj2 = __uint_as_float(static_cast<uint32_t>(b2));
-    const float e0 = uj0 - U0, e1 = uj1 - U1, e2 = uj2 - U2;
-    const float y0 = xi0 + e0, y1 = xi1 + e1, y2 = xi2 + e2;
-    const float z0 = xi0 + y0, z1 = xi1 + y1, z2 = xi2 + y2;
-    const float tq = __builtin_fmaf(e2, z2, __builtin_fmaf(e1, z1, e0 * z0));
-    const float L2 = __builtin_fmaf(xi2, xi2, __builtin_fmaf(xi1, xi1, xi0 * xi0));
-    const float iL = __builtin_amdgcn_rsqf(L2);
-    const float q = tq * (iL * iL);
-    const bool brk = breakable && q >= q0;
-    const bool alive = live && !brk;
-    // the lanes that break as a mask (each ballot of a comparison is its lane mask)
-    const float qa = alive ? q : 0.0f;
-    float g;
-    if (fabsf(qa) < 4.0e-3f) {
-        float p = -35.0f / 128.0f;
-        p = __builtin_fmaf(p, qa, 5.0f / 16.0f);
-        p = __builtin_fmaf(p, qa, -3.0f / 8.0f);
-        p = __builtin_fmaf(p, qa, 0.5f);
-        g = qa * p;
-    } else {
-        g = 1.0f - __builtin_amdgcn_rsqf(1.0f + qa);
-    }
-    const float coef = (kv * iL) * g;
-    st = SlotTerm32{q, coef, y0, y1, y2};
-    F0 = __builtin_fmaf(coef, y0, F0);
-    F1 = __builtin_fmaf(coef, y1, F1);
-    F2 = __builtin_fmaf(coef, y2, F2);
-    return brk;
 }
 
 // Stretch from q without cancellation: s = q / (1 + sqrt(1 + q)).
@@ -620,7 +577,10 @@ __global__ __launch_bounds__(kBlock) void step_f64(StepArgs A)
 // decision edge.  Those and the softened ones are kept as bits of each lane's window of
 // 32 row pairs and settled after it (the tiles at a crack are the launch's tail).
 // The partial forces of a slice's wavefronts meet in LDS in a fixed order.
-// Bound: FP64 vector issue at the clock the chip holds under it.
+// Bound: FP64 vector issue at the clock the chip holds under it (248 of the 277 vector
+// instructions of four row pairs).  us a step, and where each wavefront staged runs of
+// consecutive records itself and took a reciprocal root and a six-term series per slot: 1M
+// nodes at horizon 3.015 191 and 233, 216000 at 5.015 161 and 327, 1000 at 3.015 8.0 and 14.1.
 // STIFF per-slot stiffness, VOLN per-node volumes, KNODE per-node stiffness factors, CORR
 // stiffness corrections formed per slot (uniform stiffness and volume), EXT no-failure zones
 // and damage laws.
@@ -710,11 +670,12 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     };
     uint32_t en[B];  // the next block's entries and stiffness
     double2 kn[B];
-    auto fetch = [&](int t) {
+    auto fetch = [&](int t) {  // (one address a stream, the pairs of the block by immediate offset)
+        const int64_t at = static_cast<int64_t>(t) * kWave;
 #pragma unroll
         for (int u = 0; u < B; ++u) {
-            en[u] = ent[static_cast<int64_t>(t + u) * kWave];
-            if (STIFF) kn[u] = kslot[static_cast<int64_t>(t + u) * kWave];
+            en[u] = (ent + at)[u * kWave];
+            if (STIFF) kn[u] = (kslot + at)[u * kWave];
         }
     };
     uint64_t todo = 0;  // slots of the window from pair `base` on that are settled after it
@@ -785,7 +746,8 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 if (t + u >= end) break;
                 const uint32_t ia = v & 0xffffu, ib = v >> 16;
                 const NodeRec rb = staged_record(lrec, ib);
-                if (u + 1 < B) v = live_indices<EXT>(t + u + 1 < end ? e[u + 1] : 0x80008000u);
+                // (past the share's end: another share's entry, read but not added)
+                if (u + 1 < B) v = live_indices<EXT>(e[u + 1]);
                 __builtin_amdgcn_sched_barrier(0);
                 one(ra, ia, STIFF ? k[u].x : 0.0, e[u], 2 * u);
                 if (u + 1 < B) ra = staged_record(lrec, v & 0xffffu);

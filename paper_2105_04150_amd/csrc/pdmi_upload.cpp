@@ -183,8 +183,7 @@ static bool corrections_in_kernel(const pd_ctx* ctx)
 }
 
 // Family volume of every device node for the per-slot corrections (1 for padding, for the
-// spare entries the kernels' fixed copy window reaches past the last node, for nodes
-// without bonds and for instances without the surface correction: every entry is positive,
+// sentinel, for nodes without bonds and for instances without the surface correction: every entry is positive,
 // so no slot divides by zero); sets each instance's V0.
 static void upload_family_volumes(pd_ctx* ctx)
 {
@@ -298,8 +297,7 @@ void upload_volumes(pd_ctx* ctx)
         return;
     }
     if (!ctx->laid) return;
-    // entry nn: the sentinel record, volume 0; then spare zero entries for the state-based
-    // kernels' fixed copy window
+    // entry nn: the sentinel record, volume 0
     std::vector<double> V(static_cast<size_t>(ctx->nn) + kCorrPad, 0.0);
     for (auto& I : ctx->inst)
         for (int64_t l = 0; l < I.n_pad; ++l) {
@@ -312,8 +310,7 @@ void upload_volumes(pd_ctx* ctx)
 }
 
 // State-based model: 1/m_i per device node, m_i = sum over the whole family of |xi|^2 V_j
-// (influence function 1, reference configuration); padding 0.  The pair
-// pair buffer starts zeroed, the sentinel's included.
+// (influence function 1, reference configuration); padding 0.  The pair buffer starts zeroed.
 void upload_osb(pd_ctx* ctx)
 {
     ctx->has_osb = false;
@@ -355,8 +352,8 @@ void upload_osb(pd_ctx* ctx)
     sync(ctx);
 }
 
-// What the state-based kernels support: every instance on the model, the staged layout, the constant micromodulus replaced by (K, G): no stiffness
-// fields, damage laws or corrections.
+// What the state-based kernels support: every instance on the model, the staged layout, the
+// constant micromodulus replaced by (K, G): no stiffness fields, damage laws or corrections.
 void osb_checks(const pd_ctx* ctx)
 {
     if (!ctx->has_osb) return;
