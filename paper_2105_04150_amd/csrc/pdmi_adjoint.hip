@@ -180,7 +180,7 @@ __device__ __forceinline__ V stream_load(const V* p)
 
 // Staged layout: one workgroup a tile (pdmi_tile.h), one lane a node, 2 to 8 wavefronts
 // a slice.  The tile's records (x, u^k), adjoint velocities and per-node weights are copied into LDS
-// once; the per-slot streams (entries, break steps, stiffness, gradient: 28 to 36 bytes a
+// once; the per-slot streams (entries, break steps, stiffness, gradient: 22 to 30 bytes a
 // slot, the pass's bound beside latency) come a row pair ahead, 16 bytes a lane and load.
 // Padding entries point at the sentinel (far record, zero adjoint velocity and weights).
 // Partial sums of J meet in LDS in a fixed order.
