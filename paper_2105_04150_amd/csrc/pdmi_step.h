@@ -136,6 +136,7 @@ __device__ __forceinline__ MidTerm<double> slot_mid(const NodeRec& n, double X0,
     const double xi0 = n.p0.x - X0, xi1 = n.p0.y - X1, xi2 = n.p1.x - X2;
     const double e0 = n.p1.y - U0, e1 = n.p2.x - U1, e2 = n.p2.y - U2;
     MidTerm<double> m;
+    m.q = 0.0;
     m.y0 = xi0 + e0;
     m.y1 = xi1 + e1;
     m.y2 = xi2 + e2;
@@ -686,20 +687,24 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
     auto& S0 = [&]() -> auto& { if constexpr (FP32) return E0; else return F0; }();
     auto& S1 = [&]() -> auto& { if constexpr (FP32) return E1; else return F1; }();
     auto& S2 = [&]() -> auto& { if constexpr (FP32) return E2; else return F2; }();
-    // softened and not broken slots of a block
+    // Marks the softened and not broken slots of a block; true if nothing is left for its rows.
     auto mark_soft = [&](const uint32_t (&e)[B], int t, int end) {
-        if (!laws) return;
+        if (!laws) return false;
         uint32_t s[B], any = 0;
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             s[u] = t + u < end ? e[u] & ~(e[u] >> 2) & 0x20002000u : 0u;
             any |= s[u];
         }
-        if (__builtin_amdgcn_ballot_w64(any != 0) == 0) return;
-        uint32_t bits = 0;
+        if (__builtin_amdgcn_ballot_w64(any != 0) == 0) return false;
+        uint32_t bits = 0, left = 0;
 #pragma unroll
-        for (int u = 0; u < B; ++u) bits |= ((s[u] >> 13 & 1u) | (s[u] >> 28 & 2u)) << (2 * u);
+        for (int u = 0; u < B; ++u) {
+            bits |= ((s[u] >> 13 & 1u) | (s[u] >> 28 & 2u)) << (2 * u);
+            left |= t + u < end ? live_indices<EXT>(e[u]) : 0u;
+        }
         todo |= static_cast<uint64_t>(bits) << (2 * (t - base));
+        return __builtin_amdgcn_ballot_w64(left != 0) == 0;
     };
     // The pairs [t, end), after fetch(t), block by block at level 0 or 1, up to the first block with
     // a slot that the level does not cover; that block is taken back, and `need` is the level
@@ -722,7 +727,8 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 if (STIFF) k[u] = kn[u];
             }
             fetch(t + B);
-            if constexpr (EXT) mark_soft(e, t, end);
+            if constexpr (EXT)
+                if (mark_soft(e, t, end)) continue;
             const Real B0 = F0, B1 = F1, B2 = F2;
             int32_t himax = std::numeric_limits<int32_t>::min();  // of the block's d: the largest high word
             uint32_t himin = 0;  // and the one furthest below zero (sign bit set: large)
@@ -780,7 +786,8 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
                 if (STIFF) k[u] = kn[u];
             }
             fetch(t + B);
-            if constexpr (EXT) mark_soft(e, t, end);
+            if constexpr (EXT)
+                if (mark_soft(e, t, end)) continue;
             int32_t himax = std::numeric_limits<int32_t>::min();
             uint32_t himin = 0, bits = 0;
 #pragma unroll 1
@@ -817,53 +824,87 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
         return t;
     };
     // The marked slots of the window: a break candidate is decided on its exact stretch, a
-    // softened one takes the weight of its damage state.  They are few and lie in few lanes (at a
-    // crack 9 of a wavefront's 2000, up to 7 in one lane), so they are listed and taken 64 at
-    // a time, one a lane whoever owns it; each owner then collects its sums in slot order.
-    // A slot of each lane in turn took a pass of 400 instructions for every slot of the
-    // fullest lane: 117 x 33 x 33 nodes with a grown crack 61.8 us a step, listed 43.4.
+    // softened one takes the weight of its damage state.  Where few lanes have some (at a crack 9
+    // of a wavefront's 2000 slots, up to 7 in one lane) a round takes several of each, so that all
+    // lanes work, each on one slot whoever owns it; the owners then collect their sums in slot order.
+    // A slot of each lane in turn takes a pass of 400 instructions for every slot of the
+    // fullest lane: 117 x 33 x 33 nodes with a grown crack 61.8 us a step, shared out 43.4.  None,
+    // 1 % and all of the slots softened: 37.8, 59.6 and 153 us, and 41.9, 116 and 146 where a
+    // slice's flagged rows were taken one by one.
+    // The next round's words are loaded during a round's arithmetic and waited for before its
+    // stores, so that the wave waits for no store.
     auto settle = [&] {
         if (__builtin_amdgcn_ballot_w64(todo != 0) == 0) return false;
-        const int count = __builtin_popcountll(todo);
-        int upto = count;  // marked slots of the lanes up to this one
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int o = __shfl_up(upto, d);
-            upto += lane >= d ? o : 0;
-        }
-        const int total = __builtin_amdgcn_readlane(upto, kWave - 1);
-        int at = upto - count;  // the lane's next slot in the list
+        struct Round {
+            int m;          // slots of a lane that has some, 0: nothing left
+            int at, n;      // this lane's: first place in the round, number
+            bool on;        // this lane works on a slot: its owner, place and words
+            int owner;
+            int64_t ds;
+            uint32_t word;
+            double sold, k;
+        };
+        auto next = [&] {
+            Round w;
+            const uint64_t some = __builtin_amdgcn_ballot_w64(todo != 0);
+            w.m = some ? kWave / __builtin_popcountll(some) : 0;
+            w.at = lane;
+            w.n = 0;
+            w.owner = lane;
+            w.on = todo != 0;
+            int bit = w.on ? __builtin_ctzll(todo) : 0;
+            if (w.m == 1) {
+                w.n = w.on;
+                todo &= todo - 1;
+            } else if (w.m > 1) {
+                w.at = w.m * static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(some >> 32),
+                                                                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(some), 0u)));
+                litem[lane] = 0xffff;
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
-        for (int i0 = 0; i0 < total; i0 += kWave) {
-            {
-                uint64_t left = todo;
-                int i = at;
-#pragma unroll 1
-                while (left != 0 && i < i0 + kWave) {
-                    litem[i++ - i0] = static_cast<uint16_t>(lane | __builtin_ctzll(left) << 8);
-                    left &= left - 1;
+                for (; w.n < w.m && todo != 0; ++w.n) {
+                    litem[w.at + w.n] = static_cast<uint16_t>(lane | __builtin_ctzll(todo) << 8);
+                    todo &= todo - 1;
                 }
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t item = litem[lane];
+                w.on = item != 0xffffu;
+                w.owner = w.on ? static_cast<int>(item & 63u) : lane;
+                bit = w.on ? static_cast<int>(item >> 8) : 0;
             }
-            __builtin_amdgcn_wave_barrier();
-            const bool on = i0 + lane < total;
-            const uint32_t item = on ? litem[lane] : 0u;
-            const int owner = item & 63u;
-            const uint32_t bit = item >> 8;
-            const int64_t ds = static_cast<int64_t>(base + static_cast<int>(bit >> 1)) * (2 * kWave) + 2 * owner + (bit & 1u);
-            const uint32_t word = A.ent[ds];
-            const double sold = laws ? A.smax[ds] : 0.0, k = STIFF ? A.kslot[ds] : 0.0;
-            const double x0 = __shfl(X0, owner), x1 = __shfl(X1, owner), x2 = __shfl(X2, owner);
-            const double fv = CORR ? __shfl(fvi, owner) : 0.0, ow = FP32 && KNODE ? __shfl(own, owner) : own;
-            const uint32_t e = on ? word : kEntBroken;
+            w.ds = static_cast<int64_t>(base + (bit >> 1)) * (2 * kWave) + 2 * w.owner + (bit & 1);
+            w.word = A.ent[w.ds];
+            w.sold = laws ? A.smax[w.ds] : 0.0;
+            w.k = STIFF ? A.kslot[w.ds] : 0.0;
+            return w;
+        };
+        Round w = next();
+#pragma unroll 1
+        while (w.m != 0) {
+            Round wn = next();
+            double x0 = X0, x1 = X1, x2 = X2, u0 = U0, u1 = U1, u2 = U2, fv = fvi, ow = own;
+            float v0 = Uf0, v1 = Uf1, v2 = Uf2;
+            if (w.m > 1) {
+                x0 = __shfl(X0, w.owner), x1 = __shfl(X1, w.owner), x2 = __shfl(X2, w.owner);
+                if constexpr (FP32)
+                    v0 = __shfl(Uf0, w.owner), v1 = __shfl(Uf1, w.owner), v2 = __shfl(Uf2, w.owner);
+                else
+                    u0 = __shfl(U0, w.owner), u1 = __shfl(U1, w.owner), u2 = __shfl(U2, w.owner);
+                if (CORR) fv = __shfl(fvi, w.owner);
+                if (FP32 && KNODE) ow = __shfl(own, w.owner);
+            }
+            const uint32_t e = w.on ? w.word : kEntBroken;
             const bool live = !(e & kEntBroken), soft = EXT && live && (e & kEntSoft) != 0;
             const uint32_t idx = live ? e & kEntIdx : 0u;
             const NodeRec r = staged_record(lrec, idx);
             MidTerm<Real> m;
-            double u0 = 0.0, u1 = 0.0, u2 = 0.0;
             if constexpr (FP32) {
-                m = slot_mid32<2>(r, x0, x1, x2, __shfl(Uf0, owner), __shfl(Uf1, owner), __shfl(Uf2, owner));
+                m = slot_mid32<2>(r, x0, x1, x2, v0, v1, v2);
+            } else if constexpr (EXT) {  // (softened slots are within the series, all but a few)
+                m = slot_mid<1>(r, x0, x1, x2, u0, u1, u2, mc);
+                if (__builtin_amdgcn_ballot_w64(!(fabs(m.d) < 4.0 * kWideRange)) != 0)
+                    m = slot_mid<2>(r, x0, x1, x2, u0, u1, u2, mc);
             } else {
-                u0 = __shfl(U0, owner), u1 = __shfl(U1, owner), u2 = __shfl(U2, owner);
                 m = slot_mid<2>(r, x0, x1, x2, u0, u1, u2, mc);
             }
             Real q = m.q;
@@ -891,39 +932,42 @@ __global__ __launch_bounds__(kTileWaves * kWave, 4) void step_staged(StepArgs A,
             BondWeight bw;
             if constexpr (EXT) {
                 if (live && (BREAKS ? (over || soft) : soft))
-                    bw = bond_weight<MODE, FP32>(A, P, ds, static_cast<double>(q), s, (e & kEntNoFail) != 0, soft, sold, exact);
+                    bw = bond_weight<MODE, FP32>(A, P, w.ds, static_cast<double>(q), s, (e & kEntNoFail) != 0, soft, w.sold, exact);
             } else if (BREAKS && live && over) {
                 bw.broke = FP32 ? q >= static_cast<Real>(q0f) : exact() >= P.s0;
             }
-            if (bw.broke) {  // irreversible; the pass is recorded
-                A.ent[ds] = static_cast<uint16_t>(e | kEntBroken);
-                A.bstep[ds] = static_cast<int32_t>(*A.step_base + A.step_local);
-            } else if (EXT && bw.newly_soft) {
-                A.ent[ds] = static_cast<uint16_t>(e | kEntSoft);
-            }
-            if (EXT && bw.grew) A.smax[ds] = bw.smax;
             coef = bw.broke || bw.share == 0.0 ? 0.0 : coef * bw.share;
             double f0 = 0.0, f1 = 0.0, f2 = 0.0;
             if (coef != 0.0) {
-                if (WEIGHT) coef *= static_cast<double>(weight(idx, k, m.L2, fv, ow));
+                if (WEIGHT) coef *= static_cast<double>(weight(idx, w.k, m.L2, fv, ow));
                 f0 = coef * static_cast<double>(m.y0);
                 f1 = coef * static_cast<double>(m.y1);
                 f2 = coef * static_cast<double>(m.y2);
             }
+            asm volatile("" : "+v"(wn.word), "+v"(wn.sold));
+            if (STIFF) asm volatile("" : "+v"(wn.k));
+            if (bw.broke) {  // irreversible; the pass is recorded
+                A.ent[w.ds] = static_cast<uint16_t>(e | kEntBroken);
+                A.bstep[w.ds] = static_cast<int32_t>(*A.step_base + A.step_local);
+            } else if (EXT && bw.newly_soft) {
+                A.ent[w.ds] = static_cast<uint16_t>(e | kEntSoft);
+            }
+            if (EXT && bw.grew) A.smax[w.ds] = bw.smax;
             // back to the owners
+            if (w.m == 1) {
+                S0 += f0;
+                S1 += f1;
+                S2 += f2;
+            } else {
 #pragma unroll 1
-            for (;;) {
-                const bool mine = todo != 0 && at < i0 + kWave;
-                if (__builtin_amdgcn_ballot_w64(mine) == 0) break;
-                const double g0 = __shfl(f0, at - i0), g1 = __shfl(f1, at - i0), g2 = __shfl(f2, at - i0);
-                S0 += mine ? g0 : 0.0;
-                S1 += mine ? g1 : 0.0;
-                S2 += mine ? g2 : 0.0;
-                if (mine) {
-                    todo &= todo - 1;
-                    ++at;
+                for (int j = 0; __builtin_amdgcn_ballot_w64(j < w.n) != 0; ++j) {
+                    const double g0 = __shfl(f0, w.at + j), g1 = __shfl(f1, w.at + j), g2 = __shfl(f2, w.at + j);
+                    S0 += j < w.n ? g0 : 0.0;
+                    S1 += j < w.n ? g1 : 0.0;
+                    S2 += j < w.n ? g2 : 0.0;
                 }
             }
+            w = wn;
         }
         return true;
     };

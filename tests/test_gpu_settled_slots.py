@@ -128,3 +128,44 @@ def test_a_free_node_has_no_dilation_wherever_it_is(build, far):
     eps = 1e-5 if build == "f32" else 1e-12
     assert np.abs(out[0][0] - out[1][0]).max() <= eps * np.abs(out[1][0]).max()
     assert np.abs(out[0][1] - out[1][1]).max() <= eps * np.abs(out[1][1]).max()
+
+
+@pytest.mark.parametrize("part", [0.002, 0.02, 0.1, 0.5, 1.0])
+@pytest.mark.parametrize("build", ["f64", "f32"])
+def test_any_number_of_softened_slots(part, build):
+    """From a few softened slots a wavefront, shared out among its lanes, to all of them: the
+    force of the state, against a direct sum over the bonds."""
+    import paper_2105_04150_amd as pd
+    dims = (17, 11, 9)
+    x, u = _state(dims, 2.0e-4)
+    u = u.astype(np.float32).astype(np.float64)
+    n = len(x)
+    (s1, s2, s3), (_, r2, _) = LAW
+    with pd.Simulation(0, pd.PD_FP32 if build == "f32" else pd.PD_FP64) as sim:
+        sim.set_mapping("staged")
+        sim.build_family(x, 3.015 * DX)
+        sim.set_integrator("euler_cromer", 1.0e-8)
+        sim.set_material(2400.0, 1.0e19, 1.0, 0.0, DX ** 3)
+        sim.set_damage_law(0, *LAW)
+        rp, col = sim.family()
+        row = np.repeat(np.arange(n), np.diff(rp))
+        rng = np.random.default_rng(6)
+        key = np.minimum(row, col) * n + np.maximum(row, col)
+        draw = rng.random(n * n)[key]
+        level = rng.uniform(s1 * 1.001, s3 * 0.99, n * n)[key]
+        sm = np.where(draw < part, level, 0.0)
+        sim.set_state(u=u)
+        sim.set_max_stretch(sm)
+        got = sim.force()
+        assert np.array_equal(sim.max_stretch(), sm)
+    xi, eta = x[col] - x[row], u[col] - u[row]
+    y = xi + eta
+    r, L = np.sqrt((y * y).sum(1)), np.sqrt((xi * xi).sum(1))
+    s = (eta * (xi + y)).sum(1) / (L * (r + L))
+    rho = np.where(sm < s2, 1.0 + (r2 - 1.0) * (sm - s1) / (s2 - s1), r2 * (s3 - sm) / (s3 - s2))
+    w = np.where(sm > 0, s1 * rho / np.where(sm > 0, sm, 1.0), 1.0)
+    f = (1.0e19 * DX ** 3 * w * s / r)[:, None] * y
+    want = np.stack([np.bincount(row, f[:, d], minlength=n) for d in range(3)], axis=1)
+    # the rounding of |y|^2 - |xi|^2 over the stretch, and of rho on its steep first branch (below 60 times)
+    tol = 1e-5 if build == "f32" else 4 * 2.0 ** -52 / 2.0e-4 + 60 * 8 * 2.0 ** -52
+    assert np.abs(got - want).max() <= tol * np.abs(want).max()
